@@ -167,8 +167,106 @@ def work(case):
 
 def tolerance(case):
     """About four times what the outputs are off from the same quantities in float64: at most 7e-7 and, at single
-    elements, 4e-6 (float32 attention), 3.0e-3 and 5e-2 (bf16 attention); in the block 2e-3 to 1e-2 for most gradients
-    and 1.9e-2 for those of the QK-norm gains (sums of large terms that cancel), 1.1e-1 at single elements."""
+    elements, 4e-6 (float32 attention), 3.0e-3 and 5e-2 (bf16 attention); in the block 2e-3 to 1.3e-2 for most gradients
+    and up to 2.7e-2 for those of the QK-norm gains (sums of large terms that cancel), 1.1e-1 at single elements."""
     if case["kind"] == "attention":
         return {"rel": 3e-6, "max": 5e-5} if case["dtype"] == "f32" else {"rel": 1e-2, "max": 0.2}
     return {"rel": 3e-2, "max": 0.45}
+
+
+def _rms64(t, tt):
+    """RMSNorm without gain over the last dimension, and its tangent, in float64."""
+    n = t.shape[-1]
+    r = torch.rsqrt((t * t).sum(-1, keepdim=True) / n + EPS)
+    return t * r, tt * r - t * r ** 3 * ((t * tt).sum(-1, keepdim=True) / n)
+
+
+def _attention64(q, k, v, tq, tk, tv):
+    """The definition on [..., M, d] and [..., N, d] tensors: (o, to, lse, stats)."""
+    a = q.shape[-1] ** -0.5
+    z = a * (q @ k.transpose(-1, -2))
+    zt = a * (tq @ k.transpose(-1, -2) + q @ tk.transpose(-1, -2))
+    p = torch.softmax(z, -1)
+    stats = (p * zt).sum(-1)
+    return p @ v, (p * (zt - stats.unsqueeze(-1))) @ v + p @ tv, torch.logsumexp(z.detach(), -1), stats
+
+
+def _exact_attention(case, t):
+    """Head by head: the score matrices of one head at a time are materialised."""
+    B, H, step = case["B"], case["H"], case["step"]
+    train = step != "forward"
+    names = ("q", "k", "v", "tq", "tk", "tv")
+    outs = None
+    for b in range(B):
+        for h in range(H):
+            six = [t[n][b, h].double().requires_grad_(train) for n in names]
+            o, to, lse, stats = _attention64(*six)
+            parts = [o.detach(), to.detach()]
+            if train:
+                loss = 0
+                if t["gO"] is not None:
+                    loss = loss + (t["gO"][b, h].double() * o).sum()
+                if t["gTO"] is not None:
+                    loss = loss + (t["gTO"][b, h].double() * to).sum()
+                g = torch.autograd.grad(loss, six, allow_unused=True)
+                if step == "detached":
+                    g = list(g[:3]) + [None] * 3
+                parts += [lse, stats.detach()] + list(g)
+            if outs is None:
+                outs = [None if p is None else torch.empty(B, H, *p.shape, dtype=torch.float64, device=p.device) for p in parts]
+            for out, p in zip(outs, parts):
+                if out is not None:
+                    out[b, h] = p
+    return tuple(outs)
+
+
+def _exact_block(case, t):
+    B, T, H, d = case["B"], case["T"], case["H"], case["d"]
+    C, train = H * d, case["step"] == "train"
+    leaf = lambda s: s.double().requires_grad_(train)
+    x, tx = leaf(t["x"]), leaf(t["tx"])
+    mods, tmods, w = ({n: leaf(s) for n, s in t[key].items()} for key in ("mods", "tmods", "params"))
+    unit = {n: [s.unsqueeze(1) for s in _rms64(mods[n], tmods[n])] for n in mods}
+
+    def modulate(u, tu, a, b):
+        n, tn = _rms64(u, tu)
+        (a, ta), (b, tb) = unit[a], unit[b]
+        return n * a + b, tn * a + n * ta + tb
+
+    def gate(u, tu, c, h, th):
+        c, tc = unit[c]
+        return u + c * h, tu + c * th + tc * h
+
+    def linear(u, tu, weight, bias):
+        return u @ w[weight].T + w[bias], tu @ w[weight].T
+
+    def gelu(u, tu):
+        s = math.sqrt(2 / math.pi)
+        th = torch.tanh(s * (u + 0.044715 * u ** 3))
+        slope = 0.5 * (1 + th) + 0.5 * u * (1 - th * th) * s * (1 + 3 * 0.044715 * u * u)
+        return 0.5 * u * (1 + th), slope * tu
+
+    qkv, tqkv = (s.view(B, T, 3, H, d) for s in linear(*modulate(x, tx, "a1", "b1"), "wqkv", "bqkv"))
+    heads = lambda s, i: s[:, :, i].permute(0, 2, 1, 3)
+    (q, tq), (k, tk), (v, tv) = ((heads(qkv, i), heads(tqkv, i)) for i in range(3))
+    (q, tq), (k, tk) = (_rms64(q, tq), _rms64(k, tk))
+    o, to = _attention64(q * w["gq"], k * w["gk"], v, tq * w["gq"], tk * w["gk"], tv)[:2]
+    rows = lambda s: s.permute(0, 2, 1, 3).reshape(B, T, C)
+    x1, tx1 = gate(x, tx, "c1", *linear(rows(o), rows(to), "wo", "bo"))
+    h2 = linear(*gelu(*linear(*modulate(x1, tx1, "a2", "b2"), "w1", "b1")), "w2", "b2")
+    z, tz = gate(x1, tx1, "c2", *h2)
+    if not train:
+        return z, tz
+    leaves = {"x": x, "tx": tx}
+    for n in mods:                                           # the shifts share their names with two biases
+        key = "m" + n if n in w else n
+        leaves[key], leaves["t" + key] = mods[n], tmods[n]
+    leaves.update(w)
+    grads = torch.autograd.grad((t["gz"].double() * z).sum() + (t["gtz"].double() * tz).sum(), list(leaves.values()))
+    return z.detach(), tz.detach(), dict(zip(leaves, grads))
+
+
+def exact(case, seed):
+    """What `run` returns, from the definitions in float64 on the stored inputs."""
+    t = prepare(case, seed)["t"]
+    return _exact_attention(case, t) if case["kind"] == "attention" else _exact_block(case, t)
