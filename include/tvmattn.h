@@ -72,7 +72,7 @@ typedef enum {
 /* Per-call switches, OR-ed into tvmattn_desc.flags.  Unknown bits are TVMATTN_INVALID_ARG. */
 enum {
   /* Diagnostic: serve this call with the plain-ALU kernels even where the matrix-core kernels would take it
-   * (bf16 with D a multiple of 8 and D <= 128).  Both families compute the operation stated above. */
+   * (bf16 with D a multiple of 8, float32 with D a multiple of 4, D <= 128).  Both families compute the operation stated above. */
   TVMATTN_FLAG_PLAIN_ALU = 1
 };
 

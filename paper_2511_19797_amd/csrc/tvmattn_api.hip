@@ -5,7 +5,7 @@
 
 #include <mutex>
 
-#include "tvm_common.h"
+#include "f32_mfma.h"
 
 namespace {
 
@@ -162,6 +162,8 @@ inline Buf unless(bool unused, Buf b) {
   return b;
 }
 inline long long esz_of(int dtype) { return dtype == TVMATTN_F32 ? 4 : 2; }
+// The dtype as the launchers of everything but the bf16 matrix-core kernels take it
+inline int generic_dtype(const tvmattn_desc* d) { return d->dtype | ((d->flags & TVMATTN_FLAG_PLAIN_ALU) != 0 ? tvm::kPlainAlu : 0); }
 inline bool plain_alu(const tvmattn_desc* d) { return (d->flags & TVMATTN_FLAG_PLAIN_ALU) != 0; }
 
 }  // namespace
@@ -203,7 +205,7 @@ int tvmattn_jvp_fwd(const tvmattn_desc* desc, const void* q, const void* k, cons
   if (!plain_alu(desc) && tvm::mfma_supported(s, desc->dtype))
     e = tvm::launch_fwd_mfma(s, a, st);
   else
-    e = tvm::launch_fwd_generic(s, desc->dtype, a, st);
+    e = tvm::launch_fwd_generic(s, generic_dtype(desc), a, st);
   return e == hipSuccess ? TVMATTN_OK : TVMATTN_LAUNCH_FAILED;
 }
 
@@ -249,13 +251,13 @@ int bwd_impl(const tvmattn_desc* desc, const tvm::Shape& s, const void* q, const
   const bool mf = !plain_alu(desc) && tvm::mfma_supported(s, desc->dtype);
   hipError_t e = hipSuccess;
   mark(events, 0, st);
-  if (!mf) e = tvm::launch_bwd_pre(s, desc->dtype, a, st);  // the matrix-core query-side kernel does Step 1 itself
+  if (!mf) e = tvm::launch_bwd_pre(s, generic_dtype(desc), a, st);  // the matrix-core query-side kernel does Step 1 itself
   if (e != hipSuccess) return TVMATTN_LAUNCH_FAILED;
   mark(events, 1, st);
-  e = mf ? tvm::launch_bwd_row_mfma(s, a, st) : tvm::launch_bwd_row_generic(s, desc->dtype, a, st);
+  e = mf ? tvm::launch_bwd_row_mfma(s, a, st) : tvm::launch_bwd_row_generic(s, generic_dtype(desc), a, st);
   if (e != hipSuccess) return TVMATTN_LAUNCH_FAILED;
   mark(events, 2, st);
-  e = mf ? tvm::launch_bwd_col_mfma(s, a, st) : tvm::launch_bwd_col_generic(s, desc->dtype, a, st);
+  e = mf ? tvm::launch_bwd_col_mfma(s, a, st) : tvm::launch_bwd_col_generic(s, generic_dtype(desc), a, st);
   mark(events, 3, st);
   return e == hipSuccess ? TVMATTN_OK : TVMATTN_LAUNCH_FAILED;
 }
