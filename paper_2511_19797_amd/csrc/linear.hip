@@ -12,12 +12,13 @@
 // both sets.  Everything is computed transposed, D = Q-fragment x P-fragment, so that a lane owns one output ROW
 // (32 per 32x32 block) and 16 of its columns: results leave through LDS as whole rows (store_tile_coalesced).
 //
-// Workgroup: eight waves as 2 x 4 (two per SIMD), each with 4 x 2 blocks of 32 x 32 (128 accumulator registers): a
-// 256 x 256 output tile (128 flop per byte staged: smaller tiles are bound by L2->LDS traffic), contraction in
+// Four tile shapes (chosen by pick_shape and plan_dw below): 256 x 256 and 256 x 192 here, 128 x 128 and 64 x 64 in
+// gemm_small_kernel.  Workgroup: eight waves as 2 x 4 (two per SIMD), each with 4 x 2 blocks of 32 x 32 (128 accumulator
+// registers), or as 4 x 2 with 2 x 3 blocks: a 256 x 256 or 256 x 192 output tile (128 flop per byte staged: smaller tiles are bound by L2->LDS traffic), contraction in
 // tiles of 64 through two LDS stages filled by asynchronous global->LDS loads (mfma_tiles.h: the same swizzled
 // row-major tiles as the attention kernels; "row" fragments are 16-byte reads, "transposed" ones the transposing LDS
 // read, here with the contraction index in natural order so that both kinds pair up).  Per contraction step of 16
-// a wave reads 4 + 2 fragments for 8 products, a step ahead of the products that use them.  Workgroups are
+// a wave reads 4 + 2 fragments for 8 products (2 + 3 for 6), a step ahead of the products that use them.  Workgroups are
 // persistent, one per CU: each walks a list of output tiles in an order that keeps an XCD's workgroups on one patch
 // of tiles, requests the next tile's first operands during the last contraction tile of the current one, and writes
 // a tile's results while those land.
@@ -80,6 +81,30 @@ struct GemmArgs {
   int nz;             // row sets (forward, grad x: 2) or splits (grad W)
 };
 
+// float32 partial tile of one wave (kWI x kWJ blocks from row i, column jw of split zz): lane = output row, four
+// consecutive columns per register group.
+template <int kWI, int kWJ>
+__device__ __forceinline__ void store_partial(const GemmArgs& g, const f32x16 (&acc)[kWI][kWJ], int zz, int i_first, int jw,
+                                              int ic, int hh) {
+  typedef __attribute__((ext_vector_type(4))) float f32x4;
+  float* dst = g.part + (long long)zz * g.I * g.J;
+#pragma unroll
+  for (int a = 0; a < kWI; ++a) {
+    const int i = i_first + a * 32 + ic;
+    if (i >= g.I) continue;
+#pragma unroll
+    for (int b = 0; b < kWJ; ++b)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const int j = jw + b * 32 + 8 * q4 + 4 * hh;
+        if (j < g.J) {  // (J is a multiple of 8: four columns are in range together)
+          const f32x4 v = {acc[a][b][4 * q4], acc[a][b][4 * q4 + 1], acc[a][b][4 * q4 + 2], acc[a][b][4 * q4 + 3]};
+          *reinterpret_cast<f32x4*>(dst + (long long)i * g.J + j) = v;
+        }
+      }
+  }
+}
+
 template <bool PTR, bool QTR, bool PARTIAL, class C>
 __global__ __launch_bounds__(C::NT, C::OCC) void gemm_kernel(GemmArgs g) {
   constexpr int kNW = C::NW, kWI = C::WI, kWJ = C::WJ, kTI = C::TI, kTJ = C::TJ, NST = C::NST;
@@ -117,24 +142,7 @@ __global__ __launch_bounds__(C::NT, C::OCC) void gemm_kernel(GemmArgs g) {
   auto write_out = [&](int i0, int j0, int zz, int stage) {
     const int jw = j0 + wj * (kWJ * 32);  // first output column of this wave
     if (PARTIAL) {
-      // float32 partial tile: lane = output row, four consecutive columns per register group
-      float* dst = g.part + (long long)zz * g.I * g.J;
-#pragma unroll
-      for (int a = 0; a < kWI; ++a) {
-        const int i = i0 + (wi * kWI + a) * 32 + ic;
-        if (i >= g.I) continue;
-#pragma unroll
-        for (int b = 0; b < kWJ; ++b)
-#pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4) {
-            const int j = jw + b * 32 + 8 * q4 + 4 * hh;
-            if (j < g.J) {  // (J is a multiple of 8: four columns are in range together)
-              typedef __attribute__((ext_vector_type(4))) float f32x4;
-              const f32x4 v = {acc[a][b][4 * q4], acc[a][b][4 * q4 + 1], acc[a][b][4 * q4 + 2], acc[a][b][4 * q4 + 3]};
-              *reinterpret_cast<f32x4*>(dst + (long long)i * g.J + j) = v;
-            }
-          }
-      }
+      store_partial<kWI, kWJ>(g, acc, zz, i0 + wi * kWI * 32, jw, ic, hh);
     } else {
       const unsigned lw = lds0 + (unsigned)stage * BUF + (unsigned)wave * OUT_REGION;  // each wave stages its rows through a region of its own
       if (jw < g.J) {
@@ -186,14 +194,14 @@ __global__ __launch_bounds__(C::NT, C::OCC) void gemm_kernel(GemmArgs g) {
       c.op_full = TP::offsets(l, pitchP, kBK);
       c.op_last = TP::offsets(l, pitchP, clast);
     } else {
-      c.op_full = c.op_last = TP::offsets(TP::lane_setup(32, wave, lane), pitchP, g.I - c.i0);
+      c.op_full = c.op_last = TP::offsets(TP::lane_setup(32, wave, lane), pitchP, min(g.I - c.i0, kTI));
     }
     if (QTR) {
       const typename TQ::Lane l = TQ::lane_setup(min(g.J - c.j0, kTJ), wave, lane);
       c.oq_full = TQ::offsets(l, pitchQ, kBK);
       c.oq_last = TQ::offsets(l, pitchQ, clast);
     } else {
-      c.oq_full = c.oq_last = TQ::offsets(TQ::lane_setup(32, wave, lane), pitchQ, g.J - c.j0);
+      c.oq_full = c.oq_last = TQ::offsets(TQ::lane_setup(32, wave, lane), pitchQ, min(g.J - c.j0, kTJ));
     }
     return c;
   };
@@ -355,6 +363,150 @@ __global__ __launch_bounds__(C::NT, C::OCC) void gemm_kernel(GemmArgs g) {
   }
 }
 
+// The same product for shapes with few 256-row tiles: workgroups of four waves on 64 x 64 or 128 x 128 output tiles, one
+// tile each, many workgroups in flight.  What bounds it is latency (a contraction tile is 128 or 512 cycles of matrix
+// work per wave against some 2000 from L2), so the contraction runs NST - 1 tiles ahead through NST LDS stages, with one
+// barrier per tile and the loads in flight counted rather than drained.  Contraction tiles are taken in the same order
+// and every output element is the same chain of products as in gemm_kernel: results are bit for bit the same (with
+// equal splits).
+template <bool PTR, bool QTR, bool PARTIAL, class C>
+__global__ __launch_bounds__(C::NT, C::OCC) void gemm_small_kernel(GemmArgs g) {
+  constexpr int kNW = C::NW, kWI = C::WI, kWJ = C::WJ, kTI = C::TI, kTJ = C::TJ, NST = C::NST;
+  using TP = typename std::conditional<PTR, Tile<kBK, kTI / 8, kNW>, Tile<kTI, 4, kNW>>::type;
+  using TQ = typename std::conditional<QTR, Tile<kBK, kTJ / 8, kNW>, Tile<kTJ, 4, kNW>>::type;
+  constexpr int P_BYTES = PTR ? TP::BYTES : 2 * TP::BYTES, Q_BYTES = QTR ? TQ::BYTES : 2 * TQ::BYTES;
+  constexpr int BUF = P_BYTES + Q_BYTES;
+  constexpr int LOADS = (PTR ? 1 : 2) * TP::IPW + (QTR ? 1 : 2) * TQ::IPW;
+  constexpr int OUT_REGION = 32 * (64 * kWJ + 16);
+  static_assert(NST >= 3 && (NST - 2) * LOADS < 64 && kNW * OUT_REGION <= NST * BUF, "stages");
+  __shared__ __attribute__((aligned(16))) char lds[NST * BUF];
+  const int nI = (g.I + kTI - 1) / kTI, nJ = (g.J + kTJ - 1) / kTJ, total = g.nz * nI * nJ;
+  // XCD x owns the x-th eighth of the tile list (as in gemm_kernel: groups of kGI tile rows, down the group first)
+  const int wg = (int)(blockIdx.x & 7) * ((total + 7) >> 3) + (int)(blockIdx.x >> 3);
+  if (wg >= min(total, ((int)(blockIdx.x & 7) + 1) * ((total + 7) >> 3))) return;
+  const int tid = threadIdx.x, lane = tid & 63, ic = lane & 31, hh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wi = wave % C::NWI, wj = wave / C::NWI;
+  const int zz = wg / (nI * nJ), id = wg - zz * (nI * nJ);
+  const int grp = id / (kGI * nJ), it_first = grp * kGI, gs = min(nI - it_first, kGI);
+  const int rem = id - grp * (kGI * nJ), jt = rem / gs, it = it_first + (rem - jt * gs);
+  const int i0 = it * kTI, j0 = jt * kTJ;
+  const int nct = (g.C + kBK - 1) / kBK, ntot = g.csets * nct;
+  const int t_begin = PARTIAL ? (int)((long long)zz * ntot / g.splits) : 0;
+  const int t_end = PARTIAL ? (int)((long long)(zz + 1) * ntot / g.splits) : ntot;
+  const bool two = g.csets == 2;  // grad W: contraction over both row sets
+  const int clast = g.C - (nct - 1) * kBK;
+  const unsigned lds0 = lds_addr_of(lds);
+  const unsigned pitchP = (unsigned)(g.ldP * 2), pitchQ = (unsigned)(g.ldQ * 2);
+  typename TP::Offs op_full, op_last;
+  typename TQ::Offs oq_full, oq_last;
+  if (PTR) {
+    const typename TP::Lane l = TP::lane_setup(min(g.I - i0, kTI), wave, lane);
+    op_full = TP::offsets(l, pitchP, kBK);
+    op_last = TP::offsets(l, pitchP, clast);
+  } else {
+    op_full = op_last = TP::offsets(TP::lane_setup(32, wave, lane), pitchP, min(g.I - i0, kTI));
+  }
+  if (QTR) {
+    const typename TQ::Lane l = TQ::lane_setup(min(g.J - j0, kTJ), wave, lane);
+    oq_full = TQ::offsets(l, pitchQ, kBK);
+    oq_last = TQ::offsets(l, pitchQ, clast);
+  } else {
+    oq_full = oq_last = TQ::offsets(TQ::lane_setup(32, wave, lane), pitchQ, min(g.J - j0, kTJ));
+  }
+  const typename TP::RAddr rp = TP::raddr(ic, hh);
+  const typename TQ::RAddr rq = TQ::raddr(ic, hh);
+  const TrNat<TP> tp = TrNat<TP>::make(ic, hh);
+  const TrNat<TQ> tq = TrNat<TQ>::make(ic, hh);
+  f32x16 acc[kWI][kWJ];
+  {
+    const bool with_bias = !PARTIAL && g.bias != nullptr && zz == 0;
+    const int jw = j0 + wj * (kWJ * 32);
+#pragma unroll
+    for (int b = 0; b < kWJ; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int j = jw + b * 32 + drow(r, hh);
+        const float v = with_bias && j < g.J ? (float)g.bias[j] : 0.f;
+#pragma unroll
+        for (int a = 0; a < kWI; ++a) acc[a][b][r] = v;
+      }
+  }
+  // all wave-loads of contraction tile t (beyond the end: the last one again, never used) into the stage at `buf`
+  auto issue = [&](int t, unsigned buf) {
+    t = min(t, t_end - 1);
+    const int set = two && t >= nct ? 1 : 0, ct = t - set * nct;
+    const long long c0 = (long long)ct * kBK;
+    const bool last = ct == nct - 1;
+    const bf16* pb = g.P[two ? set : PARTIAL ? 0 : zz] + (PTR ? c0 * g.ldP + i0 : (long long)i0 * g.ldP + c0);
+    const bf16* qb = g.Q[set] + (QTR ? c0 * g.ldQ + j0 : (long long)j0 * g.ldQ + c0);
+    const int half2 = (last && clast <= 32) ? 0 : 32;
+#pragma unroll
+    for (int x = 0; x < TP::IPW; ++x) {
+      TP::issue_at(PTR && last ? op_last.o[x] : op_full.o[x], x, pb, buf, wave);
+      if (!PTR) TP::issue_at(op_full.o[x], x, pb + half2, buf + TP::BYTES, wave);
+    }
+#pragma unroll
+    for (int x = 0; x < TQ::IPW; ++x) {
+      TQ::issue_at(QTR && last ? oq_last.o[x] : oq_full.o[x], x, qb, buf + P_BYTES, wave);
+      if (!QTR) TQ::issue_at(oq_full.o[x], x, qb + half2, buf + P_BYTES + TQ::BYTES, wave);
+    }
+  };
+#pragma unroll
+  for (int x = 0; x < NST - 1; ++x) issue(t_begin + x, lds0 + x * BUF);
+  int n = 0;
+  for (int t = t_begin; t < t_end; ++t) {
+    dma_wait_keep<(NST - 2) * LOADS>();  // this wave's share of tile t has landed
+    const int ct = two && t >= nct ? t - nct : t;
+    if (ct == nct - 1 && clast < kBK) {  // entries beyond the set's end weigh nothing (see fix_ragged in gemm_kernel)
+      char* pt = lds + n * BUF;
+#pragma unroll
+      for (int x = 0; x < TP::IPW; ++x) {
+        const int pos = (wave + x * kNW) * 64 + lane;
+        if (PTR) {
+          if (pos / TP::PCH >= clast) *reinterpret_cast<uint4*>(pt + pos * 16) = make_uint4(0u, 0u, 0u, 0u);
+        } else if (clast <= 32) {
+          *reinterpret_cast<uint4*>(pt + TP::BYTES + pos * 16) = make_uint4(0u, 0u, 0u, 0u);
+        }
+      }
+    }
+    __syncthreads();  // it is there for everyone, and everyone is done with tile t-1, whose stage is refilled now
+    const int nf = n == 0 ? NST - 1 : n - 1;
+    issue(t + NST - 1, lds0 + nf * BUF);
+    const char* sp = lds + n * BUF;
+    const char* sq = sp + P_BYTES;
+#pragma unroll
+    for (int kk = 0; kk < kBK / 16; ++kk) {
+      bf16x8 pf[kWI], qf[kWJ];
+#pragma unroll
+      for (int a = 0; a < kWI; ++a)
+        pf[a] = PTR ? tp.frag(sp, kk, wi * kWI + a) : TP::frag_row(sp + (kk >> 1) * TP::BYTES, rp, wi * kWI + a, kk & 1);
+#pragma unroll
+      for (int b = 0; b < kWJ; ++b)
+        qf[b] = QTR ? tq.frag(sq, kk, wj * kWJ + b) : TQ::frag_row(sq + (kk >> 1) * TQ::BYTES, rq, wj * kWJ + b, kk & 1);
+#pragma unroll
+      for (int a = 0; a < kWI; ++a)
+#pragma unroll
+        for (int b = 0; b < kWJ; ++b) acc[a][b] = mfma(qf[b], pf[a], acc[a][b]);
+    }
+    n = n + 1 == NST ? 0 : n + 1;
+  }
+  const int jw = j0 + wj * (kWJ * 32);
+  if (PARTIAL) {
+    store_partial<kWI, kWJ>(g, acc, zz, i0 + wi * kWI * 32, jw, ic, hh);
+    dma_wait();  // (no load may land in LDS that the next workgroup owns)
+    return;
+  }
+  dma_wait();  // the loads past the end land in stages that the results are about to go through
+  __syncthreads();
+  if (jw < g.J) {
+    const unsigned lw = lds0 + (unsigned)wave * OUT_REGION;
+#pragma unroll
+    for (int a = 0; a < kWI; ++a)
+      store_tile_coalesced<kWJ>(lw, g.out[zz] + jw, g.ldo, i0 + (wi * kWI + a) * 32, g.I, g.J - jw, acc[a], 1.f, lane);
+  }
+}
+
 // Adds `splits` float32 partial matrices of n elements in order and rounds once to bf16.  8 elements per thread.
 __global__ __launch_bounds__(256) void sum_partials_kernel(const float* __restrict__ part, int splits, long long n,
                                                            bf16* __restrict__ out) {
@@ -445,14 +597,16 @@ __global__ __launch_bounds__(1024) void bias_sum_kernel(const float* __restrict_
   }
 }
 
-// The shapes in use: forward and grad x, grad W
-using CfgF = Cfg<2, 4, 4, 2, 2, 1>;
-using CfgX = Cfg<2, 4, 4, 2, 2, 1>;
-using CfgW = Cfg<2, 4, 4, 2, 2, 1>;
+// The tile shapes in use
+using Cfg256 = Cfg<2, 4, 4, 2, 2, 1>;  // 256 x 256, eight waves
+using Cfg192 = Cfg<4, 2, 2, 3, 2, 1>;  // 256 x 192, eight waves
+using Cfg128 = Cfg<2, 2, 2, 2, 3, 1>;  // 128 x 128, four waves
+using Cfg64 = Cfg<2, 2, 1, 1, 4, 2>;   // 64 x 64, four waves
 
 int dw_splits(int F, int K, int R) {
-  const int tiles = ((F + CfgW::TI - 1) / CfgW::TI) * ((K + CfgW::TJ - 1) / CfgW::TJ);
+  const int tiles = ((F + Cfg256::TI - 1) / Cfg256::TI) * ((K + Cfg256::TJ - 1) / Cfg256::TJ);
   const int ntot = 2 * ((R + kBK - 1) / kBK);
+  // (the most splits any tile shape uses, and what the workspace is sized for)
   // The fewest rounds of workgroups over the chip's 256 CUs (one workgroup each), each round costing its share of
   // the contraction plus a fixed part (start-up, the float32 partial tile); ties go to fewer splits.
   int best = 1;
@@ -475,6 +629,80 @@ int persistent_grid(int tiles) {
 int bias_chunks(int R) {
   const int c = (R + 63) / 64;
   return c > 256 ? 256 : c;
+}
+
+
+// ---- Which tile shape serves a product
+enum { k256, k192, k128, k64, kShapes };
+constexpr int kTileI[kShapes] = {Cfg256::TI, Cfg192::TI, Cfg128::TI, Cfg64::TI};
+constexpr int kTileJ[kShapes] = {Cfg256::TJ, Cfg192::TJ, Cfg128::TJ, Cfg64::TJ};
+int tiles_of(int c, int I, int J) { return (I + kTileI[c] - 1) / kTileI[c] * ((J + kTileJ[c] - 1) / kTileJ[c]); }
+
+// Time of `tiles` output tiles of shape c over `steps` contraction tiles each, in units of a hundredth of a contraction
+// tile of the 256 x 256 shape (1.5 us on an idle chip, 2 us on a full one): rounds of workgroups over the chip's 256
+// CUs times steps and a fixed part.  The weights are fits to measured times, R = 64 ... 16384 rows, widths 384, 768,
+// 1152 and their multiples by 3 and 4: they put the fastest shape first, or one within 3 % of it.  Some of both sides
+// (us; 256 | 192 | 128 | 64):
+//   forward, 256 x 4608 -> 1152:    104 |  99 |  52 |  32     few tiles: small ones fill the chip
+//   forward, 1024 x 4608 -> 1152:   101 |  94 |  53 |  60
+//   forward, 2048 x 1152 -> 3456:    40 |  58 |  63 |  75     224 tiles of 256 are one round, 288 of 192 are two
+//   forward, 16384 x 4608 -> 1152:  395 | 384 | 455 | 636     1152 = 6 x 192: no padded columns
+//   forward, 16384 x 1152 -> 4608:  321 | 355 | 524 | 690
+// The layers of a whole block with tangent, forward and backward (us, before / with this choice): B1 T256 C1152 forward 232 /
+// 198, B2 T250 C768 626 / 529 (both then bound by the host's calls), B32 T256 C1152 2727 / 2684, B16 T1024 5434 / 5359.
+long long tile_cost(int c, long long tiles, int steps) {
+  constexpr int kStep[kShapes] = {100, 88, 45, 28}, kFixed[kShapes] = {150, 130, 70, 50}, kSlots[kShapes] = {256, 256, 256, 512};
+  return (tiles + kSlots[c] - 1) / kSlots[c] * ((long long)steps * kStep[c] + kFixed[c]);
+}
+int pick_shape(int sets, int I, int J, int C) {
+  int best = k256;
+  for (int c = k192; c < kShapes; ++c) {
+    const int steps = (C + kBK - 1) / kBK;
+    if (tile_cost(c, (long long)sets * tiles_of(c, I, J), steps) < tile_cost(best, (long long)sets * tiles_of(best, I, J), steps)) best = c;
+  }
+  return best;
+}
+// Shape and number of contraction splits of grad W: what the partial tiles cost on top is two passes over them at
+// 5 TB/s and a launch (3 us).  The 128 and 64 shapes write bf16 directly when there is one split.  Never more splits
+// than dw_splits: the workspace is sized for those.
+// (us of the whole backward, R 500 768 -> 768: 53 with 16 splits of 256 x 256 tiles, 35 with one of 64 x 64; R 16384
+// 1152 -> 3456: 597 with 3 splits of 256 x 256, 581 with 3 of 256 x 192.)
+struct DwPlan {
+  int shape, splits;
+};
+DwPlan plan_dw(int F, int K, int R, int max_splits) {
+  const int ntot = 2 * ((R + kBK - 1) / kBK);
+  DwPlan best{k256, max_splits};
+  long long best_cost = -1;
+  for (int c = 0; c < kShapes; ++c)
+    for (int s = 1; s <= max_splits; ++s) {
+      const long long tiles = (long long)s * tiles_of(c, F, K);
+      // (grad W's 64 x 64 tiles fit one workgroup per CU: half as many at once)
+      long long cost = tile_cost(c, c == k64 ? 2 * tiles : tiles, (ntot + s - 1) / s);
+      if (s > 1 || c < k128) cost += 180 + (long long)s * F * K / 10000;  // 8 bytes per partial sum, 60 units per us
+      if (best_cost < 0 || cost < best_cost) {
+        best_cost = cost;
+        best = DwPlan{c, s};
+      }
+    }
+  return best;
+}
+
+// Launches a product with tile shape c.  (DIRECT: the 256-row shapes are left out, see plan_dw.)
+template <bool PTR, bool QTR, bool PARTIAL, bool DIRECT = false>
+hipError_t launch_gemm(int c, const GemmArgs& g, hipStream_t st) {
+  const int tiles = g.nz * tiles_of(c, g.I, g.J), small_grid = 8 * ((tiles + 7) / 8);
+  if (c == k64) {
+    hipLaunchKernelGGL((gemm_small_kernel<PTR, QTR, PARTIAL, Cfg64>), dim3(small_grid), dim3(Cfg64::NT), 0, st, g);
+  } else if (DIRECT || c == k128) {
+    hipLaunchKernelGGL((gemm_small_kernel<PTR, QTR, PARTIAL, Cfg128>), dim3(small_grid), dim3(Cfg128::NT), 0, st, g);
+  } else if constexpr (!DIRECT) {
+    if (c == k192)
+      hipLaunchKernelGGL((gemm_kernel<PTR, QTR, PARTIAL, Cfg192>), dim3(persistent_grid(tiles)), dim3(Cfg192::NT), 0, st, g);
+    else
+      hipLaunchKernelGGL((gemm_kernel<PTR, QTR, PARTIAL, Cfg256>), dim3(persistent_grid(tiles)), dim3(Cfg256::NT), 0, st, g);
+  }
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -508,9 +736,7 @@ hipError_t launch_linear_fwd(int R, int K, int F, long long ldx, long long ldy, 
   g.ldo = ldy;
   g.bias = (const bf16*)bias;
   g.nz = 2;
-  const int grid = persistent_grid(2 * ((R + CfgF::TI - 1) / CfgF::TI) * ((F + CfgF::TJ - 1) / CfgF::TJ));
-  hipLaunchKernelGGL((gemm_kernel<false, false, false, CfgF>), dim3(grid), dim3(CfgF::NT), 0, st, g);
-  return hipGetLastError();
+  return launch_gemm<false, false, false>(pick_shape(2, R, F, K), g, st);
 }
 
 hipError_t launch_linear_bwd(int R, int K, int F, long long ldx, long long ldy, const void* x, const void* tx,
@@ -531,12 +757,12 @@ hipError_t launch_linear_bwd(int R, int K, int F, long long ldx, long long ldy, 
     g.out[1] = (bf16*)gtx;
     g.ldo = ldx;
     g.nz = 2;
-    const int grid = persistent_grid(2 * ((R + CfgX::TI - 1) / CfgX::TI) * ((K + CfgX::TJ - 1) / CfgX::TJ));
-    hipLaunchKernelGGL((gemm_kernel<false, true, false, CfgX>), dim3(grid), dim3(CfgX::NT), 0, st, g);
-    const hipError_t e = hipGetLastError();
+    const hipError_t e = launch_gemm<false, true, false>(pick_shape(2, R, K, F), g, st);
     if (e != hipSuccess) return e;
   }
-  const int splits = dw_splits(F, K, R);
+  const int max_splits = dw_splits(F, K, R);
+  const DwPlan plan = plan_dw(F, K, R, max_splits);
+  const int splits = plan.splits;
   float* part = static_cast<float*>(workspace);
   {  // gW = gy^T x + gty^T tx: contraction over the tokens of both sets, both operands read transposed
     GemmArgs g{};
@@ -553,18 +779,23 @@ hipError_t launch_linear_bwd(int R, int K, int F, long long ldx, long long ldy, 
     g.part = part;
     g.splits = splits;
     g.nz = splits;
-    const int grid = persistent_grid(splits * ((F + CfgW::TI - 1) / CfgW::TI) * ((K + CfgW::TJ - 1) / CfgW::TJ));
-    hipLaunchKernelGGL((gemm_kernel<true, true, true, CfgW>), dim3(grid), dim3(CfgW::NT), 0, st, g);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const long long n = (long long)F * K;
-    hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)((n / 8 + 255) / 256)), dim3(256), 0, st, part, splits, n,
-                       (bf16*)gw);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    g.out[0] = (bf16*)gw;
+    g.ldo = K;
+    if (splits == 1 && plan.shape >= k128) {
+      const hipError_t e = launch_gemm<true, true, false, true>(plan.shape, g, st);
+      if (e != hipSuccess) return e;
+    } else {
+      hipError_t e = launch_gemm<true, true, true>(plan.shape, g, st);
+      if (e != hipSuccess) return e;
+      const long long n = (long long)F * K;
+      hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)((n / 8 + 255) / 256)), dim3(256), 0, st, part, splits, n,
+                         (bf16*)gw);
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
   }
   if (gbias != nullptr) {
-    const size_t dw = ((size_t)splits * F * K * sizeof(float) + 255) & ~(size_t)255;
+    const size_t dw = ((size_t)max_splits * F * K * sizeof(float) + 255) & ~(size_t)255;
     float* bp = reinterpret_cast<float*>(static_cast<char*>(workspace) + dw);
     const int chunks = bias_chunks(R);
     hipLaunchKernelGGL(colsum_kernel, dim3((F + 511) / 512, chunks), dim3(256), 0, st, (const bf16*)gy, R, F, ldy, chunks, bp);

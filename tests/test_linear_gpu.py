@@ -127,3 +127,15 @@ def test_unsupported_shapes_are_refused():
     with pytest.raises(tvm.TvmattnError) as e:
         tvm.tvmattn_linear_jvp_fwd(xf, xf.clone(), wf)
     assert e.value.status == -2
+
+
+@pytest.mark.parametrize("R,K,F", [
+    (64, 64, 64), (65, 96, 192), (1, 64, 2304),   # 64 x 64 tiles: one tile, one row over, contraction of 1.5 tiles
+    (127, 544, 160),      # ... with more contraction tiles than stages, ragged on every side
+    (160, 160, 4608), (1024, 3072, 768),          # 128 x 128 tiles: fewer contraction tiles than stages, many
+    (1000, 768, 3072), (1031, 1152, 1120),        # ... and a weight gradient of one split, of several
+    (2048, 1152, 1184), (4095, 4608, 384),        # 256 x 192 tiles: a ragged last column tile, a ragged last row
+])
+def test_linear_tile_shapes(R, K, F):
+    """Sizes at the edges of the tile shapes between which the layer's products choose."""
+    run(R, K, F, seed=3 + R % 7)
