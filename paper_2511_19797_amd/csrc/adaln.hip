@@ -13,6 +13,8 @@
 // for the row sums).  The sums over tokens are then per-thread registers: one partial row per workgroup straight
 // from registers, no atomics, added in a fixed order by a second, small kernel that also finishes the gradients of
 // a and b.
+#include <algorithm>
+
 #include "tvm_common.h"
 
 namespace tvm {
@@ -417,9 +419,10 @@ __device__ __forceinline__ void mod_bwd_body(const float* part, long long stride
 // With many partial rows per batch element the two (or one) workgroups per element of the kernels below would spend
 // their time fetching them (64 rows: 15 us, a CU's worth of bandwidth each): this kernel adds the nwg rows of W floats
 // of batch element blockIdx.y first, 64 chunks of 16 bytes per workgroup (wave q takes quarter q of the rows, the
-// quarters meet in LDS in a fixed order), and leaves one row per element for them.
-__global__ __launch_bounds__(256) void part_rows_sum_kernel(const float* __restrict__ part, int nwg, int W,
-                                                            float* __restrict__ out) {
+// quarters meet in LDS in a fixed order), and leaves one row per element for them (which may be the element's first
+// partial row: a workgroup has read its columns of all rows before it writes them).
+__global__ __launch_bounds__(256) void part_rows_sum_kernel(const float* part, int nwg, int W, float* out,
+                                                            long long out_pitch) {
   __shared__ float4 red[4][64];
   const int q = threadIdx.x >> 6, ct = threadIdx.x & 63, b = blockIdx.y;
   const int c = (blockIdx.x * 64 + ct) * 4;
@@ -438,10 +441,11 @@ __global__ __launch_bounds__(256) void part_rows_sum_kernel(const float* __restr
     const float4 r0 = red[0][ct], r1 = red[1][ct], r2 = red[2][ct], r3 = red[3][ct];
     const float4 t = make_float4((r0.x + r1.x) + (r2.x + r3.x), (r0.y + r1.y) + (r2.y + r3.y),
                                  (r0.z + r1.z) + (r2.z + r3.z), (r0.w + r1.w) + (r2.w + r3.w));
-    *reinterpret_cast<float4*>(out + (long long)b * W + c) = t;
+    *reinterpret_cast<float4*>(out + b * out_pitch + c) = t;
   }
 }
 constexpr int kPartRowsDirect = 16;  // up to this many partial rows the end kernels fetch them themselves
+constexpr int kGateRowsDirect = 32;  // (the gate's rows are half as wide)
 
 // Workgroup (which, b): which = 0: g_ah, g_tah and the gradients of a, ta; which = 1: g_bh, g_tbh and those of b, tb.
 __global__ __launch_bounds__(kModNT) void adaln_mod_bwd_kernel(AdalnArgs a) {
@@ -572,7 +576,8 @@ __global__ __launch_bounds__(kModNT) void gate_mod_bwd_kernel(GateArgs a) {
   __shared__ float red[kModWaves * 5];
   const int b = blockIdx.x;
   const long long o = (long long)b * a.C;
-  mod_bwd_body(a.part + (long long)b * a.nwg * 2 * a.C, (long long)2 * a.C, a.nwg, a.C, a.eps, a.c + o, a.tc + o,
+  const int rows = a.nwg > kGateRowsDirect ? 1 : a.nwg;  // (more were added into the first by part_rows_sum_kernel)
+  mod_bwd_body(a.part + (long long)b * a.nwg * 2 * a.C, (long long)2 * a.C, rows, a.C, a.eps, a.c + o, a.tc + o,
                a.gc + o, a.gtc + o, qsum, red);
 }
 
@@ -611,7 +616,11 @@ int adaln_wgs(int B, int T, bool backward, bool gate) {
   const int R = !backward ? kRowsFwd : gate ? kRowsGateBwd : kRowsBwd;
   const int total = !backward ? ADALN_TF : gate ? GATE_TB : ADALN_TB;
   const int groups = (T + R - 1) / R, cap = total / B > 1 ? total / B : 1;
-  const int passes = (groups + cap - 1) / cap;
+  int passes = (groups + cap - 1) / cap;
+  // Small batches: up to four passes per workgroup of the gate's backward where that still leaves 32 workgroups per
+  // element.  The tail kernel walks the partial rows with one workgroup per batch element (a fifth of a microsecond per
+  // row, against a microsecond per pass here): 2 x 250 tokens x 768, 4.5 + 22 us with 125 rows each, 6.4 + 8.6 us with 32.
+  if (backward && gate) passes = std::max(passes, std::min(4, (groups + kGateRowsDirect - 1) / kGateRowsDirect));
   return (groups + passes - 1) / passes;
 }
 
@@ -639,6 +648,13 @@ hipError_t launch_gate_bwd(const GateArgs& a, int dtype, hipStream_t st) {
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (a.nwg > kGateRowsDirect) {
+    const int W = 2 * a.C;
+    hipLaunchKernelGGL(part_rows_sum_kernel, dim3((W / 4 + 63) / 64, a.B), dim3(256), 0, st, a.part, a.nwg, W, a.part,
+                       (long long)a.nwg * W);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(gate_mod_bwd_kernel, dim3(a.B), dim3(kModNT), (size_t)kModQ * 2 * a.C * sizeof(float), st, a);
   return hipGetLastError();
 }
@@ -674,7 +690,7 @@ hipError_t launch_adaln_bwd(const AdalnArgs& a, int dtype, hipStream_t st) {
   if (a.nwg > kPartRowsDirect) {  // the partial rows of an element are added first, into [B][4][C] behind all of them
     const int W = 4 * a.C;
     float* sum = a.part + (long long)a.B * a.nwg * W;
-    hipLaunchKernelGGL(part_rows_sum_kernel, dim3((W / 4 + 63) / 64, a.B), dim3(256), 0, st, a.part, a.nwg, W, sum);
+    hipLaunchKernelGGL(part_rows_sum_kernel, dim3((W / 4 + 63) / 64, a.B), dim3(256), 0, st, a.part, a.nwg, W, sum, (long long)W);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     m.part = sum;

@@ -139,3 +139,11 @@ def test_unsupported_shapes_are_refused():
 def test_linear_tile_shapes(R, K, F):
     """Sizes at the edges of the tile shapes between which the layer's products choose."""
     run(R, K, F, seed=3 + R % 7)
+
+
+@pytest.mark.parametrize("R", [1, 127, 128, 129, 511, 513, 2048, 2049])
+def test_bias_gradient_row_counts(R):
+    """The bias gradient alone around the row counts where its kernel changes: fewer rows than a pass of 128, the
+    unrolled four passes, and the last count with one launch and the first with two."""
+    for F in (32, 96):
+        run(R, 32, F, seed=R % 11)
