@@ -114,7 +114,9 @@ int tvmattn_jvp_fwd(const tvmattn_desc* desc,
                     void* o, void* to, float* lse, float* stats,
                     void* hip_stream);
 
-/* Bytes of device scratch tvmattn_jvp_bwd needs for this descriptor (0 on a bad descriptor). */
+/* Bytes of device scratch tvmattn_jvp_bwd needs for this descriptor (0 on a bad descriptor).  Three float32 row vectors
+ * (12 bytes per query row) and, for bf16 calls with few rows and a long other side, float32 partial gradients (48 MiB at
+ * most).  A workspace that holds the row vectors alone is accepted too: such calls then leave most of the GPU idle. */
 size_t tvmattn_jvp_bwd_workspace_bytes(const tvmattn_desc* desc);
 
 /*
@@ -168,9 +170,9 @@ int tvmattn_jvp_bwd_timed(const tvmattn_desc* desc,
 /*
  * tvmattn_jvp_bwd for callers that cannot allocate device memory or carry a workspace (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): same arguments without the workspace, same
- * kernels, same results bit for bit.  The three float32 row vectors that the workspace otherwise holds live in a
- * static device array of 3 * TVMATTN_STATIC_MAX_ROWS floats (12 MiB on every GPU the library runs on, held until
- * the process ends).  The call allocates nothing and frees nothing.
+ * kernels, same results bit for bit.  What the workspace otherwise holds, the three float32 row vectors and the
+ * partial gradients, lives in a static device array of 3 * TVMATTN_STATIC_MAX_ROWS floats and 48 MiB (60 MiB on every
+ * GPU the library runs on, held until the process ends).  The call allocates nothing and frees nothing.
  *   - B*H*M (query rows) above TVMATTN_STATIC_MAX_ROWS: TVMATTN_SCRATCH_TOO_SMALL, nothing enqueued.
  *   - The device that is current at the call must be the one hip_stream belongs to; each GPU has its own array.
  *   - Every call on a GPU shares that GPU's array: calls that may overlap in time on one GPU (different streams,

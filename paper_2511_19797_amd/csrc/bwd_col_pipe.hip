@@ -68,7 +68,7 @@ __device__ __forceinline__ f32x4 lds_read_f4(unsigned addr, int imm) {
 }
 __device__ __forceinline__ float f4(const f32x4& v, int t) { return v[t]; }
 
-template <int DK, int DV, bool HAS_G, bool NORM>
+template <int DK, int DV, bool HAS_G, bool NORM, bool SPLIT>
 __global__ __launch_bounds__(kNT, 1) void bwd_col_pipe_kernel(
     Shape s, const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v,
     const bf16* __restrict__ tq, const bf16* __restrict__ tk, const bf16* __restrict__ tv,
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kNT, 1) void bwd_col_pipe_kernel(
     const bf16* __restrict__ gTO, const float* __restrict__ dsig, const float* __restrict__ sig1,
     bf16* __restrict__ dk, bf16* __restrict__ dtk, bf16* __restrict__ dv, bf16* __restrict__ dtv,
     const bf16* __restrict__ nx, const bf16* __restrict__ ntx, const float* __restrict__ ngain, float neps,
-    float* __restrict__ npart) {
+    float* __restrict__ npart, float* __restrict__ part, int parts) {
   using TX = Tile<64, DV / 8, kNT / 64>;  // Q, tQ, G, tG: read both ways
   constexpr int OFF_TQ = TX::BYTES, OFF_G = 2 * TX::BYTES, OFF_TG = 3 * TX::BYTES, OFF_ROW = 4 * TX::BYTES;
   constexpr int BUF = 4 * TX::BYTES + 4 * 256;  // one stage: four tiles and four float32 row vectors (64 each)
@@ -118,12 +118,21 @@ __global__ __launch_bounds__(kNT, 1) void bwd_col_pipe_kernel(
   const int tid = threadIdx.x, lane = tid & 63, ic = lane & 31, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: what depends on it alone stays out of the VALU
   const int nfb = (s.N + kFix - 1) / kFix;
-  const int wg = xcd_remap(blockIdx.x, gridDim.x);
+  int wg = xcd_remap(blockIdx.x, gridDim.x), z = 0, i_first = 0;
+  const int rows = s.M;
+  if (SPLIT) {  // part z of the queries: from here on a call with fewer queries that start further on
+    const int wgs = nfb * s.B * s.H, ntiles = (s.M + 63) >> 6;
+    z = wg / wgs;
+    wg -= z * wgs;
+    const int t0 = z * ntiles / parts, t1 = (z + 1) * ntiles / parts;
+    i_first = t0 * 64;
+    s.M = min(s.M, t1 * 64) - i_first;
+  }
   const int bh = wg / nfb, fb = wg - bh * nfb;
   const int b = bh / s.H, h = bh - b * s.H;
   const long long base = b * s.sb + h * s.sh;     // key side (fixed)
-  const long long qbase = b * s.qsb + h * s.qsh;  // query side (streamed)
-  const long long rbase = (long long)bh * s.M;
+  const long long qbase = b * s.qsb + h * s.qsh + (long long)i_first * s.qsn;  // query side (streamed)
+  const long long rbase = (long long)bh * rows + i_first;
   const int j = fb * kFix + wave * 32 + ic;  // this lane's key
 
   const unsigned pitch = (unsigned)(s.qsn * 2);  // row pitch of the streamed (query-side) tensors in bytes
@@ -439,7 +448,15 @@ __global__ __launch_bounds__(kNT, 1) void bwd_col_pipe_kernel(
     landed_acc(aV[db]);
     landed_acc(aTV[db]);
   }
-  {
+  if (SPLIT) {
+    const int row0 = fb * kFix + wave * 32;
+    const long long one = (long long)s.B * s.H * s.N * s.D;
+    float* const dst = part + z * 4 * one + ((long long)bh * s.N + row0) * s.D;
+    store_tile_f32<NDB>(dst, s.N - row0, s.D, aK, lane);
+    store_tile_f32<NDB>(dst + one, s.N - row0, s.D, aTK, lane);
+    store_tile_f32<NDB>(dst + 2 * one, s.N - row0, s.D, aV, lane);
+    store_tile_f32<NDB>(dst + 3 * one, s.N - row0, s.D, aTV, lane);
+  } else {
     // nobody reads the tile buffers any more and no tile load is in flight: each wave stages its
     // four output tiles through a region of its own
     constexpr unsigned REG = 32 * (64 * NDB + 16);
@@ -469,11 +486,23 @@ __global__ __launch_bounds__(kNT, 1) void bwd_col_pipe_kernel(
 template <int DK, int DV>
 hipError_t launch(const Shape& s, const BwdArgs& a, hipStream_t st) {
   const int nfb = (s.N + kFix - 1) / kFix;
-  hipLaunchKernelGGL((bwd_col_pipe_kernel<DK, DV, kHasG, kNorm>), dim3(nfb * s.B * s.H), dim3(kNT), 0, st, s, (const bf16*)a.q,
-                     (const bf16*)a.k, (const bf16*)a.v, (const bf16*)a.tq, (const bf16*)a.tk, (const bf16*)a.tv,
-                     a.lse2, a.stats, (const bf16*)a.gO, (const bf16*)a.gTO, a.dsig, a.sig1, (bf16*)a.dk,
-                     (bf16*)a.dtk, (bf16*)a.dv, (bf16*)a.dtv, (const bf16*)a.nk, (const bf16*)a.ntk, a.ngk, a.neps, a.npart_k);
-  return hipGetLastError();
+  const int parts = a.part != nullptr ? bwd_splits((long long)s.B * s.H, s.N, s.M, 4) : 1;
+  auto go = [&](auto split) {
+    hipLaunchKernelGGL((bwd_col_pipe_kernel<DK, DV, kHasG, kNorm, decltype(split)::value>), dim3(nfb * s.B * s.H * parts), dim3(kNT),
+                       0, st, s, (const bf16*)a.q, (const bf16*)a.k, (const bf16*)a.v, (const bf16*)a.tq, (const bf16*)a.tk,
+                       (const bf16*)a.tv, a.lse2, a.stats, (const bf16*)a.gO, (const bf16*)a.gTO, a.dsig, a.sig1, (bf16*)a.dk,
+                       (bf16*)a.dtk, (bf16*)a.dv, (bf16*)a.dtv, (const bf16*)a.nk, (const bf16*)a.ntk, a.ngk, a.neps,
+                       a.npart_k, a.part, parts);
+    return hipGetLastError();
+  };
+  if constexpr (!kNorm) {
+    if (parts > 1) {
+      const hipError_t e = go(std::true_type{});
+      void* const out[] = {a.dk, a.dtk, a.dv, a.dtv};
+      return e != hipSuccess ? e : launch_bwd_part_sum(s, false, a.part, parts, 4, out, st);
+    }
+  }
+  return go(std::false_type{});
 }
 
 }  // namespace

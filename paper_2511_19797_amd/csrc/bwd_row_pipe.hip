@@ -63,7 +63,7 @@ constexpr bool kNorm = false;
 #endif
 
 
-template <int DK, int DV, bool HAS_G, bool NORM>
+template <int DK, int DV, bool HAS_G, bool NORM, bool SPLIT>
 __global__ __launch_bounds__(kNT, 1) void bwd_row_pipe_kernel(
     Shape s, const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v,
     const bf16* __restrict__ tq, const bf16* __restrict__ tk, const bf16* __restrict__ tv,
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(kNT, 1) void bwd_row_pipe_kernel(
     const float* __restrict__ stats, const bf16* __restrict__ gO, const bf16* __restrict__ gTO,
     float* __restrict__ dsig, float* __restrict__ sig1, float* __restrict__ lse2w, bf16* __restrict__ dq,
     bf16* __restrict__ dtq, const bf16* __restrict__ nx, const bf16* __restrict__ ntx, const float* __restrict__ ngain,
-    float neps, float* __restrict__ npart) {
+    float neps, float* __restrict__ npart, float* __restrict__ part, int parts) {
   using TK = Tile<64, DV / 8, kNT / 64>;  // K, tK: read both ways
   using TV = Tile<64, DK / 8, kNT / 64>;  // V, tV: score-type products only
   constexpr int OFF_TK = TK::BYTES, OFF_V = 2 * TK::BYTES, OFF_TV = 2 * TK::BYTES + TV::BYTES;
@@ -94,10 +94,19 @@ __global__ __launch_bounds__(kNT, 1) void bwd_row_pipe_kernel(
   const int tid = threadIdx.x, lane = tid & 63, ic = lane & 31, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: what depends on it alone stays out of the VALU
   const int nfb = (s.M + kFix - 1) / kFix;
-  const int wg = xcd_remap(blockIdx.x, gridDim.x);
+  int wg = xcd_remap(blockIdx.x, gridDim.x), z = 0;
+  long long zoff = 0;
+  if (SPLIT) {  // part z of the keys: from here on a call with fewer keys that start further on
+    const int wgs = nfb * s.B * s.H, ntiles = (s.N + 63) >> 6;
+    z = wg / wgs;
+    wg -= z * wgs;
+    const int t0 = z * ntiles / parts, t1 = (z + 1) * ntiles / parts;
+    zoff = (long long)t0 * 64 * s.sn;
+    s.N = min(s.N, t1 * 64) - t0 * 64;
+  }
   const int bh = wg / nfb, fb = wg - bh * nfb;
   const int b = bh / s.H, h = bh - b * s.H;
-  const long long base = b * s.sb + h * s.sh;     // key side (streamed)
+  const long long base = b * s.sb + h * s.sh + zoff;  // key side (streamed)
   const long long qbase = b * s.qsb + h * s.qsh;  // query side (fixed)
   const int i = fb * kFix + wave * 32 + ic;  // this lane's query
   const bool iok = i < s.M;
@@ -185,7 +194,7 @@ __global__ __launch_bounds__(kNT, 1) void bwd_row_pipe_kernel(
     cDF[e] = -ds;
   }
   asm volatile("" : "+v"(cE), "+v"(cDF));  // materialised here, once
-  if (iok && hh == 0) {
+  if (iok && hh == 0 && z == 0) {
     dsig[r] = -ds;  // negated: the key-side kernel starts its DF and E tiles from these
     sig1[r] = -s1;
     lse2w[r] = lse2;
@@ -471,7 +480,12 @@ __global__ __launch_bounds__(kNT, 1) void bwd_row_pipe_kernel(
     landed_acc(aQ[db]);
     landed_acc(aTQ[db]);
   }
-  if (!NORM) {
+  if (SPLIT) {
+    const int row0 = fb * kFix + wave * 32;
+    float* const dst = part + (((long long)z * 2 * s.B * s.H + bh) * s.M + row0) * s.D;
+    store_tile_f32<NDB>(dst, s.M - row0, s.D, aQ, lane);
+    store_tile_f32<NDB>(dst + (long long)s.B * s.H * s.M * s.D, s.M - row0, s.D, aTQ, lane);
+  } else if (!NORM) {
     // nobody reads the tile buffers any more and no tile load is in flight: each wave stages its
     // two output tiles through a region of its own
     const unsigned lw = lds0 + wave * (32 * (64 * NDB + 16));
@@ -499,12 +513,23 @@ __global__ __launch_bounds__(kNT, 1) void bwd_row_pipe_kernel(
 template <int DK, int DV>
 hipError_t launch(const Shape& s, const BwdArgs& a, hipStream_t st) {
   const int nfb = (s.M + kFix - 1) / kFix;
-  hipLaunchKernelGGL((bwd_row_pipe_kernel<DK, DV, kHasG, kNorm>), dim3(nfb * s.B * s.H), dim3(kNT), 0, st, s, (const bf16*)a.q,
-                     (const bf16*)a.k, (const bf16*)a.v, (const bf16*)a.tq, (const bf16*)a.tk, (const bf16*)a.tv,
-                     (const bf16*)a.o, (const bf16*)a.to, a.lse, a.stats, (const bf16*)a.gO, (const bf16*)a.gTO,
-                     a.dsig, a.sig1, a.lse2, (bf16*)a.dq, (bf16*)a.dtq, (const bf16*)a.nq, (const bf16*)a.ntq, a.ngq, a.neps,
-                     a.npart_q);
-  return hipGetLastError();
+  const int parts = a.part != nullptr ? bwd_splits((long long)s.B * s.H, s.M, s.N, 2) : 1;
+  auto go = [&](auto split) {
+    hipLaunchKernelGGL((bwd_row_pipe_kernel<DK, DV, kHasG, kNorm, decltype(split)::value>), dim3(nfb * s.B * s.H * parts), dim3(kNT),
+                       0, st, s, (const bf16*)a.q, (const bf16*)a.k, (const bf16*)a.v, (const bf16*)a.tq, (const bf16*)a.tk,
+                       (const bf16*)a.tv, (const bf16*)a.o, (const bf16*)a.to, a.lse, a.stats, (const bf16*)a.gO,
+                       (const bf16*)a.gTO, a.dsig, a.sig1, a.lse2, (bf16*)a.dq, (bf16*)a.dtq, (const bf16*)a.nq,
+                       (const bf16*)a.ntq, a.ngq, a.neps, a.npart_q, a.part, parts);
+    return hipGetLastError();
+  };
+  if constexpr (!kNorm) {
+    if (parts > 1) {
+      const hipError_t e = go(std::true_type{});
+      void* const out[] = {a.dq, a.dtq};
+      return e != hipSuccess ? e : launch_bwd_part_sum(s, true, a.part, parts, 2, out, st);
+    }
+  }
+  return go(std::false_type{});
 }
 
 }  // namespace

@@ -378,6 +378,23 @@ __device__ __forceinline__ void store_tile_coalesced(unsigned lds_wave, bf16* __
   }
 }
 
+// The same tile as float32, unscaled, dense rows of D: dst = first of the wave's 32 rows; rows >= rows_left are skipped.
+template <int NDB>
+__device__ __forceinline__ void store_tile_f32(float* __restrict__ dst, int rows_left, int D, const f32x16 (&a)[NDB], int lane) {
+  typedef __attribute__((ext_vector_type(4))) float f32x4;
+  const int ic = lane & 31, hh = lane >> 5;
+  if (ic >= rows_left) return;
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int d0 = db * 32 + 8 * g + 4 * hh;
+      if (d0 < D) {  // (D is a multiple of 8: four columns are in range together)
+        const f32x4 v = {a[db][4 * g], a[db][4 * g + 1], a[db][4 * g + 2], a[db][4 * g + 3]};
+        *reinterpret_cast<f32x4*>(dst + (long long)ic * D + d0) = v;
+      }
+    }
+}
 
 // ---- Backward through an RMSNorm with gain that normalised the rows before the attention, in the epilogue.
 // Sum over the 16 lanes of a row group (lanes 16k .. 16k+15), the same bits in all of them: a butterfly of four

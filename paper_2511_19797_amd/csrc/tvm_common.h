@@ -60,7 +60,44 @@ struct BwdArgs {
   const float *ngq = nullptr, *ngk = nullptr;
   float neps = 0.f;
   float *npart_q = nullptr, *npart_k = nullptr;
+  // streamed side in several parts (bwd_splits): float32 partial gradients [parts][tensors][B*H*rows][D], null: one part
+  float* part = nullptr;
 };
+// Parts that the streamed side of a backward kernel is cut into, so that few rows occupy the chip all the same: `fixed` rows
+// per (batch, head) in workgroups of 128, `streamed` rows per (batch, head).  Every part is a workgroup of its own per 128
+// rows and leaves float32 sums of its tensors, which bwd_part_sum.hip adds in order.  Only where the workgroups of all
+// parts fit the 256 CUs at once (one each: a workgroup's LDS stages fill a CU), and at least four tiles of 64 rows to a
+// part.  Of those the fewest tiles one after the other, what the sum costs counted in tiles (1.5 - 2 us each): a launch
+// and the first tiles' latency are worth four, the partial sums of 256 workgroups two for each tensor (both ways at 5 TB/s).
+// Below 1024 streamed rows there is less than that to be had.  Whole backward (us, whole / in parts): one head of 1024, d = 64
+// 62 / 38; one head of 4096 209 / 74; one of 8192 403 / 178; four of 4096 213 / 177; 16 heads of 1024, d = 72 in two parts 77 / 79
+// (whole by this rule).
+constexpr int kBwdCUs = 256, kBwdFix = 128;
+inline int bwd_splits(long long heads, int fixed, int streamed, int tensors) {
+  const long long wgs = heads * ((fixed + kBwdFix - 1) / kBwdFix);
+  const int tiles = (streamed + 63) / 64;
+  if (tiles < 16 || 2 * wgs > kBwdCUs) return 1;
+  int best = 1, best_cost = tiles;
+  for (int p = 2; p <= tiles / 4 && p * wgs <= kBwdCUs; ++p) {
+    const int cost = (tiles + p - 1) / p + 4 + (int)(2 * tensors * p * wgs / kBwdCUs);
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = p;
+    }
+  }
+  return best;
+}
+// Bytes of the partial gradients of the larger of the two backward kernels (0: neither is cut).  At most
+// 256 workgroups x 128 rows x 96 columns x 4 tensors of float32 = 48 MiB.
+inline size_t bwd_part_bytes(const Shape& s, int dtype) {
+  if (dtype != 1 || s.D > 96 || s.D % 8 != 0) return 0;
+  const long long heads = (long long)s.B * s.H;
+  const int rs = bwd_splits(heads, s.M, s.N, 2), cs = bwd_splits(heads, s.N, s.M, 4);
+  const size_t row = rs > 1 ? (size_t)rs * 2 * heads * s.M * s.D * sizeof(float) : 0;
+  const size_t col = cs > 1 ? (size_t)cs * 4 * heads * s.N * s.D * sizeof(float) : 0;
+  return row > col ? row : col;
+}
+constexpr size_t kBwdPartMax = (size_t)kBwdCUs * kBwdFix * 96 * 4 * sizeof(float);
 
 hipError_t launch_fwd_generic(const Shape& s, int dtype, const FwdArgs& a, hipStream_t st);
 hipError_t launch_bwd_pre(const Shape& s, int dtype, const BwdArgs& a, hipStream_t st);
@@ -79,6 +116,10 @@ hipError_t launch_bwd_row_pipe(const Shape& s, const BwdArgs& a, hipStream_t st)
 hipError_t launch_bwd_col_pipe(const Shape& s, const BwdArgs& a, hipStream_t st);  // head dims up to 96, after the former
 hipError_t launch_bwd_row_pipe_qknorm(const Shape& s, const BwdArgs& a, hipStream_t st);  // the same two with the QK-norm's
 hipError_t launch_bwd_col_pipe_qknorm(const Shape& s, const BwdArgs& a, hipStream_t st);  // backward in their epilogues
+// Adds the partial gradients of `parts` parts in order, scales and rounds them: `tensors` outputs [B,H,rows,D] (query-side or
+// key-side strides), the first two scaled by alpha, the others by one (bwd_part_sum.hip).
+hipError_t launch_bwd_part_sum(const Shape& s, bool query_side, const float* part, int parts, int tensors, void* const* out,
+                               hipStream_t st);
 hipError_t launch_gain_grad_sum(const float* part_q, int rows_q, float* gg_q, const float* part_k, int rows_k, float* gg_k,
                                 int D, hipStream_t st);  // adds partial gain-gradient rows in order (qknorm.hip)
 

@@ -209,14 +209,23 @@ int tvmattn_jvp_fwd(const tvmattn_desc* desc, const void* q, const void* k, cons
   return e == hipSuccess ? TVMATTN_OK : TVMATTN_LAUNCH_FAILED;
 }
 
+namespace {
+inline size_t row_vector_bytes(const tvm::Shape& s) {  // one float32 per query row, padded to a 256-byte multiple
+  return ((size_t)s.B * s.H * s.M * sizeof(float) + 255) & ~(size_t)255;
+}
+// Partial gradients of a backward whose streamed side is cut into parts (0: it is not), padded likewise
+inline size_t part_bytes(const tvmattn_desc* desc, const tvm::Shape& s) {
+  if (plain_alu(desc) || !tvm::mfma_supported(s, desc->dtype)) return 0;
+  return (tvm::bwd_part_bytes(s, desc->dtype) + 255) & ~(size_t)255;
+}
+}  // namespace
+
 size_t tvmattn_jvp_bwd_workspace_bytes(const tvmattn_desc* desc) {
   tvm::Shape s;
   if (resolve(desc, &s)) return 0;
   // three float32 row vectors (delta + Sigma_2, Sigma_1, lse in log2 units), one entry per query row, each
-  // padded to a 256-byte multiple
-  const size_t rows = (size_t)s.B * s.H * s.M;
-  const size_t one = (rows * sizeof(float) + 255) & ~(size_t)255;
-  return 3 * one;
+  // padded to a 256-byte multiple, and behind them the partial gradients of a cut streamed side
+  return 3 * row_vector_bytes(s) + part_bytes(desc, s);
 }
 
 namespace {
@@ -225,7 +234,7 @@ namespace {
 int bwd_impl(const tvmattn_desc* desc, const tvm::Shape& s, const void* q, const void* k, const void* v, const void* tq,
              const void* tk, const void* tv, const void* o, const void* to, const float* lse, const float* stats,
              const void* gO, const void* gTO, void* dq, void* dk, void* dv, void* dtq, void* dtk, void* dtv, float* row0,
-             float* row1, float* row2, bool rows_fit, void* const* events, void* hip_stream) {
+             float* row1, float* row2, bool rows_fit, float* part, void* const* events, void* hip_stream) {
   if (!gO && !gTO) return TVMATTN_INVALID_ARG;
   // one upstream gradient only: 1 = gO (the tangent inputs and outputs take no part), 2 = gTO
   const int mode = !gTO ? 1 : !gO ? 2 : 0;
@@ -237,11 +246,13 @@ int bwd_impl(const tvmattn_desc* desc, const tvm::Shape& s, const void* q, const
                     unless(m1, qs(to)), plain(lse, rvb), unless(m1, plain(stats, rvb)), unless(mode == 2, qs(gO)),
                     unless(m1, qs(gTO))};
   const Buf out[] = {qs(dq), ks(dk), ks(dv), unless(m1, qs(dtq)), unless(m1, ks(dtk)), unless(m1, ks(dtv)),
-                     plain(row0, rvb), plain(row1, rvb), plain(row2, rvb)};
+                     plain(row0, rvb), plain(row1, rvb), plain(row2, rvb),
+                     unless(!part, plain(part, (long long)part_bytes(desc, s)))};
   const int rc = check_bufs(in, out);
   if (rc) return rc;
   if (!rows_fit) return TVMATTN_WORKSPACE_TOO_SMALL;
   tvm::BwdArgs a{q, k, v, tq, tk, tv, o, to, lse, stats, gO, gTO, dq, dk, dv, dtq, dtk, dtv, row0, row1, row2, mode};
+  a.part = part;
   if (m1) {  // not read, not written: whatever was passed
     a.tq = a.tk = a.tv = a.to = nullptr;
     a.stats = nullptr;
@@ -261,9 +272,6 @@ int bwd_impl(const tvmattn_desc* desc, const tvm::Shape& s, const void* q, const
   mark(events, 3, st);
   return e == hipSuccess ? TVMATTN_OK : TVMATTN_LAUNCH_FAILED;
 }
-inline size_t row_vector_bytes(const tvm::Shape& s) {  // one float32 per query row, padded to a 256-byte multiple
-  return ((size_t)s.B * s.H * s.M * sizeof(float) + 255) & ~(size_t)255;
-}
 }  // namespace
 
 int tvmattn_jvp_bwd_timed(const tvmattn_desc* desc, const void* q, const void* k, const void* v, const void* tq,
@@ -276,9 +284,14 @@ int tvmattn_jvp_bwd_timed(const tvmattn_desc* desc, const void* q, const void* k
   if (rc) return rc;
   const size_t one = row_vector_bytes(s);
   char* const ws = static_cast<char*>(workspace);  // (a null workspace fails the pointer checks in bwd_impl)
+  // (a workspace that only holds the row vectors serves too: the streamed side then stays whole.  With gO alone the
+  // partial gradients are not used.)
+  const size_t pb = part_bytes(desc, s);
+  const bool cut = ws && gTO && pb != 0 && workspace_bytes >= 3 * one + pb;
   return bwd_impl(desc, s, q, k, v, tq, tk, tv, o, to, lse, stats, gO, gTO, dq, dk, dv, dtq, dtk, dtv,
                   reinterpret_cast<float*>(ws), reinterpret_cast<float*>(ws ? ws + one : nullptr),
-                  reinterpret_cast<float*>(ws ? ws + 2 * one : nullptr), workspace_bytes >= 3 * one, events, hip_stream);
+                  reinterpret_cast<float*>(ws ? ws + 2 * one : nullptr), workspace_bytes >= 3 * one,
+                  cut ? reinterpret_cast<float*>(ws + 3 * one) : nullptr, events, hip_stream);
 }
 
 int tvmattn_jvp_bwd(const tvmattn_desc* desc, const void* q, const void* k, const void* v, const void* tq,
@@ -292,8 +305,9 @@ int tvmattn_jvp_bwd(const tvmattn_desc* desc, const void* q, const void* k, cons
 // ---- the same backward for callers that cannot allocate: the row vectors live in a static device array
 namespace {
 constexpr long long kStaticMaxRows = TVMATTN_STATIC_MAX_ROWS;  // query rows B*H*M served by the static scratch
-// Three row vectors of kStaticMaxRows floats each (12 MiB per GPU the library runs on, held until the process ends).
-static __device__ __align__(256) float scratch[3 * kStaticMaxRows];
+// Three row vectors of kStaticMaxRows floats each (60 MiB in all per GPU the library runs on, held until the process ends).
+// Behind them the partial gradients of a cut streamed side (48 MiB at most, bwd_part_bytes).
+static __device__ __align__(256) float scratch[3 * kStaticMaxRows + tvm::kBwdPartMax / sizeof(float)];
 constexpr int kMaxDevices = 64;
 float* g_scratch_ptr[kMaxDevices];         // device address of `scratch` on each GPU (its name is no device address)
 std::once_flag g_scratch_once[kMaxDevices];
@@ -321,7 +335,8 @@ int tvmattn_jvp_bwd_static(const tvmattn_desc* desc, const void* q, const void* 
   // nothing has to start at zero: the query-side kernel writes every row's three entries before the key-side
   // kernel, behind it on the same stream, reads them
   return bwd_impl(desc, s, q, k, v, tq, tk, tv, o, to, lse, stats, gO, gTO, dq, dk, dv, dtq, dtk, dtv, base,
-                  base + kStaticMaxRows, base + 2 * kStaticMaxRows, true, nullptr, hip_stream);
+                  base + kStaticMaxRows, base + 2 * kStaticMaxRows, true,
+                  gTO && part_bytes(desc, s) != 0 ? base + 3 * kStaticMaxRows : nullptr, nullptr, hip_stream);
 }
 
 // ---- RMSNorm with gain as QK-norm, with tangent
@@ -486,7 +501,7 @@ bool fused_supported(const tvmattn_desc* d, const tvm::Shape& s) {
 size_t tvmattn_jvp_bwd_qknorm_workspace_bytes(const tvmattn_desc* desc) {
   tvm::Shape s;
   if (resolve(desc, &s) || !fused_supported(desc, s)) return 0;
-  return tvmattn_jvp_bwd_workspace_bytes(desc) + fused_part_bytes(s, true) + fused_part_bytes(s, false);
+  return 3 * row_vector_bytes(s) + fused_part_bytes(s, true) + fused_part_bytes(s, false);
 }
 
 int tvmattn_jvp_bwd_qknorm(const tvmattn_desc* desc, const void* q, const void* tq, const void* k, const void* tk,
@@ -511,7 +526,7 @@ int tvmattn_jvp_bwd_qknorm(const tvmattn_desc* desc, const void* q, const void* 
   rc = check_bufs(in, out);
   if (rc) return rc;
   if (workspace_bytes < need) return TVMATTN_WORKSPACE_TOO_SMALL;
-  const size_t need0 = tvmattn_jvp_bwd_workspace_bytes(desc);
+  const size_t need0 = 3 * row_vector_bytes(s);
   char* const ws = static_cast<char*>(workspace);
   tvm::BwdArgs a{qn, kn, v, tqn, tkn, tv, o, to, lse, stats, gO, gTO, dq, dk, dv, dtq, dtk, dtv,
                  reinterpret_cast<float*>(ws), reinterpret_cast<float*>(ws + need0 / 3),

@@ -1,0 +1,68 @@
+"""Calls with few rows against a long other side: the backward's streamed side in parts (two or more workgroups per 128
+fixed rows, whose float32 sums a second kernel adds), at the edges of parts and tiles, with M != N, strided tensors and one
+upstream gradient alone, against the float64 oracle (the repository's bf16 tolerance)."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2511_19797_amd as tvm
+from oracle import tvmattn_oracle as orc
+from paper_2511_19797_amd import workloads as wl
+from tests import parity_util as pu
+
+pytestmark = pytest.mark.gpu
+
+# M, N: queries and keys both cut / keys alone / queries alone; whole tiles, one row over, parts of unequal length
+SIZES = [(1024, 1024), (1025, 1089), (40, 1100), (1537, 33), (64, 2049)]
+
+
+@pytest.mark.parametrize("d", [8, 32, 40, 64, 72, 96])
+@pytest.mark.parametrize("M,N", SIZES)
+def test_against_oracle(M, N, d):
+    w = dataclasses.replace(wl.custom(1, 2, N, d, "bf16"), M=M)
+    print(f"[case] {w}", flush=True)
+    inp = wl.make_inputs(w, 100 + d)
+    fwd, grads = pu.run_gpu(inp)
+    pu.check_heads(w, inp, fwd, grads, pu.all_heads(w))
+
+
+@pytest.mark.parametrize("d", [64, 72])
+def test_strided_static_and_small_workspace(d):
+    """[B,N,H,D] tensors against dense ones and the static-scratch call, bit for bit; a workspace of the row vectors alone
+    takes the route without parts: the same to bf16 rounding."""
+    w = dataclasses.replace(wl.custom(2, 2, 1300, d, "bf16"), M=1100)
+    inp = {n: t.cuda() for n, t in wl.make_inputs(w, 5).items()}
+    names = ("q", "k", "v", "tq", "tk", "tv")
+    six = [inp[n] for n in names]
+    fwd = tvm.tvmattn_jvp_fwd(*six)
+    plain = tvm.tvmattn_jvp_bwd(*six, *fwd, inp["gO"], inp["gTO"])
+    static = tvm.tvmattn_jvp_bwd_static(*six, *fwd, inp["gO"], inp["gTO"])
+    nhd = lambda t: t.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3)
+    strided = tvm.tvmattn_jvp_bwd(*[nhd(t) for t in six], nhd(fwd[0]), nhd(fwd[1]), *fwd[2:], nhd(inp["gO"]), nhd(inp["gTO"]))
+    rows = 3 * ((2 * 2 * 1100 * 4 + 255) // 256 * 256)
+    assert tvm.tvmattn_jvp_bwd_workspace_bytes(inp["q"], k=inp["k"]) > rows
+    whole = tvm.tvmattn_jvp_bwd(*six, *fwd, inp["gO"], inp["gTO"],
+                                workspace=torch.empty(rows, dtype=torch.uint8, device="cuda"))
+    for n, a, b, c, e in zip(pu.BWD_NAMES, plain, static, strided, whole):
+        assert torch.equal(a, b), n
+        assert torch.equal(a, c), n
+        assert pu.rel_err(a.float().cpu(), e.float().cpu()) <= 2 ** -7, n  # one bf16 rounding either side, at the largest
+
+
+@pytest.mark.parametrize("which", ["gO", "gTO"])
+def test_one_upstream_gradient(which):
+    w = dataclasses.replace(wl.custom(1, 1, 1500, 72, "bf16"), M=1030)
+    print(f"[case] {w} {which}", flush=True)
+    inp = wl.make_inputs(w, 11)
+    dev = {n: t.cuda() for n, t in inp.items()}
+    six = [dev[n] for n in ("q", "k", "v", "tq", "tk", "tv")]
+    fwd = tvm.tvmattn_jvp_fwd(*six)
+    got = tvm.tvmattn_jvp_bwd(*six, *fwd, dev["gO"] if which == "gO" else None, dev["gTO"] if which == "gTO" else None)
+    a = [wl.to_f64(inp[n][0, 0]) for n in wl.NAMES]
+    a[wl.NAMES.index("gTO" if which == "gO" else "gO")] = np.zeros_like(a[wl.NAMES.index("gO")])
+    ref = orc.attn_jvp_bwd_head(*a, None)
+    for n, g, r in zip(pu.BWD_NAMES, got, ref):
+        if g is not None:
+            assert pu.rel_err(g[0, 0].float().cpu().numpy(), r) <= pu.TOL["bf16"], n
