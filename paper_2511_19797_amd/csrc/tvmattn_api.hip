@@ -6,6 +6,7 @@
 #include <mutex>
 
 #include "f32_mfma.h"
+#include "fwd_few.h"
 
 namespace {
 
@@ -203,7 +204,7 @@ int tvmattn_jvp_fwd(const tvmattn_desc* desc, const void* q, const void* k, cons
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   hipError_t e;
   if (!plain_alu(desc) && tvm::mfma_supported(s, desc->dtype))
-    e = tvm::launch_fwd_mfma(s, a, st);
+    e = tvm::fwd_few_rows(s) ? tvm::launch_fwd_few(s, a, st) : tvm::launch_fwd_mfma(s, a, st);
   else
     e = tvm::launch_fwd_generic(s, generic_dtype(desc), a, st);
   return e == hipSuccess ? TVMATTN_OK : TVMATTN_LAUNCH_FAILED;

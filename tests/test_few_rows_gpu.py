@@ -1,6 +1,7 @@
-"""Calls with few rows against a long other side: the backward's streamed side in parts (two or more workgroups per 128
-fixed rows, whose float32 sums a second kernel adds), at the edges of parts and tiles, with M != N, strided tensors and one
-upstream gradient alone, against the float64 oracle (the repository's bf16 tolerance)."""
+"""Calls with few rows against a long other side: the forward whose four waves share 32 query rows and deal the keys out among
+themselves, and the backward's streamed side in parts (two or more workgroups per 128 fixed rows, whose float32 sums a
+second kernel adds), at the edges of parts and tiles, with M != N, strided tensors and one upstream gradient alone,
+against the float64 oracle (the repository's bf16 tolerance)."""
 import dataclasses
 
 import numpy as np
@@ -14,11 +15,12 @@ from tests import parity_util as pu
 
 pytestmark = pytest.mark.gpu
 
-# M, N: queries and keys both cut / keys alone / queries alone; whole tiles, one row over, parts of unequal length
-SIZES = [(1024, 1024), (1025, 1089), (40, 1100), (1537, 33), (64, 2049)]
+# M, N: queries and keys both cut / keys alone / queries alone; whole tiles, one row over, parts of unequal length; the fewest
+# keys the shared-rows forward takes, a last wave without a whole tile, one and two workgroups
+SIZES = [(1024, 1024), (1025, 1089), (40, 1100), (1537, 33), (64, 2049), (1, 128), (33, 129), (31, 257)]
 
 
-@pytest.mark.parametrize("d", [8, 32, 40, 64, 72, 96])
+@pytest.mark.parametrize("d", [8, 32, 40, 64, 72, 96, 104, 128])
 @pytest.mark.parametrize("M,N", SIZES)
 def test_against_oracle(M, N, d):
     w = dataclasses.replace(wl.custom(1, 2, N, d, "bf16"), M=M)
@@ -66,3 +68,18 @@ def test_one_upstream_gradient(which):
     for n, g, r in zip(pu.BWD_NAMES, got, ref):
         if g is not None:
             assert pu.rel_err(g[0, 0].float().cpu().numpy(), r) <= pu.TOL["bf16"], n
+
+
+def test_a_wave_without_finite_scores():
+    """All keys of one wave's tiles at score -inf (an overflowing product): the rows keep the other keys' result."""
+    inp = {n: t.cuda() for n, t in wl.make_inputs(wl.custom(1, 1, 128, 32, "bf16"), 5).items()}
+    q, k = inp["q"].clone(), inp["k"].clone()
+    q[..., 0], k[..., 0] = 1e20, 0.0
+    keep = [j for j in range(128) if not 32 <= j < 64]  # keys 32..63 are the second wave's tile
+    k[0, 0, 32:64, 0] = -1e38
+    z = torch.zeros_like(q)
+    o, to, lse, stats = tvm.tvmattn_jvp_fwd(q, k, inp["v"], z, z, inp["tv"])
+    args = (q[0, 0], k[0, 0, keep], inp["v"][0, 0, keep], z[0, 0], z[0, 0, keep], inp["tv"][0, 0, keep])
+    ref = orc.attn_jvp_fwd_head(*[wl.to_f64(t.cpu()) for t in args], None)
+    for g, r in zip((o, to, lse), ref):
+        assert pu.rel_err(g[0, 0].double().cpu().numpy(), r) <= pu.TOL["bf16"]
