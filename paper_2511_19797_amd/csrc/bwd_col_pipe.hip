@@ -499,7 +499,7 @@ hipError_t launch(const Shape& s, const BwdArgs& a, hipStream_t st) {
     if (parts > 1) {
       const hipError_t e = go(std::true_type{});
       void* const out[] = {a.dk, a.dtk, a.dv, a.dtv};
-      return e != hipSuccess ? e : launch_bwd_part_sum(s, false, a.part, parts, 4, out, st);
+      return e != hipSuccess ? e : launch_bwd_part_sum(s, false, a.part, parts, 4, 2, out, st);
     }
   }
   return go(std::false_type{});

@@ -13,7 +13,7 @@ struct PartSumArgs {
   const float* part;  // [parts][tensors][heads * rows][D]
   bf16* out[4];
   long long one;      // heads * rows * D
-  int parts, tensors, H, rows, D;
+  int parts, tensors, scaled, H, rows, D;  // scaled: how many of the tensors, from the first on, are scaled by alpha
   long long sb, sh, sn;
   float alpha;
 };
@@ -44,7 +44,7 @@ __global__ __launch_bounds__(256) void bwd_part_sum_kernel(PartSumArgs g) {
     a += *reinterpret_cast<const f32x4*>(src + p * pitch);
     b += *reinterpret_cast<const f32x4*>(src + p * pitch + 4);
   }
-  const float f = t < 2 ? g.alpha : 1.f;
+  const float f = t < g.scaled ? g.alpha : 1.f;
   bf16x8 o;
 #pragma unroll
   for (int x = 0; x < 4; ++x) {
@@ -60,8 +60,8 @@ __global__ __launch_bounds__(256) void bwd_part_sum_kernel(PartSumArgs g) {
 
 }  // namespace
 
-hipError_t launch_bwd_part_sum(const Shape& s, bool query_side, const float* part, int parts, int tensors, void* const* out,
-                               hipStream_t st) {
+hipError_t launch_bwd_part_sum(const Shape& s, bool query_side, const float* part, int parts, int tensors, int scaled,
+                               void* const* out, hipStream_t st) {
   PartSumArgs g{};
   g.part = part;
   for (int t = 0; t < tensors; ++t) g.out[t] = (bf16*)out[t];
@@ -71,6 +71,7 @@ hipError_t launch_bwd_part_sum(const Shape& s, bool query_side, const float* par
   g.one = (long long)s.B * s.H * g.rows * s.D;
   g.parts = parts;
   g.tensors = tensors;
+  g.scaled = scaled;
   g.sb = query_side ? s.qsb : s.sb;
   g.sh = query_side ? s.qsh : s.sh;
   g.sn = query_side ? s.qsn : s.sn;

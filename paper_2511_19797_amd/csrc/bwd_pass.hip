@@ -31,6 +31,10 @@
 // themselves): the products with G vanish (E phase: two per 16 head dims, DF = tG tV^T, in pass Q DF = tV gTO^T; OV:
 // two per 32, dV += tG^T Pd, dtV += tG^T P), and the G tile is neither fetched nor read (pass Q: no fragments of gO).
 //
+// With few fixed rows the streamed side of a pass is cut into parts (SPLIT; bwd_splits in tvm_common.h says when): a pass
+// bound by the length of its walk on a mostly idle chip.  Whole backward at d = 128 (us, whole / in parts, sums included): one
+// head of 1024 132 / 76, eight 135 / 108; one head of 4096 435 / 146; four of 4096, d = 104, 425 / 328.
+//
 // The translation unit is built with the machine scheduler off: source order is issue order.
 #include "pipe_ops.h"
 
@@ -58,14 +62,15 @@ __device__ __forceinline__ void landed1(f32x16& a) { asm volatile("" : "+v"(a));
 //   dsig, sig1: passes V, K: read (negated sums);  pass Q: written, with lse in log2 units to lse2w, for the key side:
 //   negated and in log2 units if pipe_ws, else plain (the generic-order key-side kernel follows) and lse2w untouched
 //   o, to: pass Q only (Step 1)
-template <int DK, int DV, int PASS, bool HAS_G>
+//   SPLIT: the streamed side in `parts` parts (bwd_splits); each leaves its float32 sums in `part` instead
+template <int DK, int DV, int PASS, bool HAS_G, bool SPLIT>
 __global__ __launch_bounds__(kNT, 1) void bwd_pass_kernel(
     Shape s, const bf16* __restrict__ f0, const bf16* __restrict__ f1, const bf16* __restrict__ f2,
     const bf16* __restrict__ f3, const bf16* __restrict__ t0, const bf16* __restrict__ t1,
     const bf16* __restrict__ t2, const bf16* __restrict__ t3, const float* __restrict__ lse_in,
     const float* __restrict__ stats, float* __restrict__ dsig, float* __restrict__ sig1, float* __restrict__ lse2w,
     int pipe_ws, const bf16* __restrict__ o, const bf16* __restrict__ to, bf16* __restrict__ out0,
-    bf16* __restrict__ out1) {
+    bf16* __restrict__ out1, float* __restrict__ part, int parts) {
   static_assert(PASS >= 1 && PASS <= 3, "pass V, K or Q");
   constexpr bool PV = PASS == 1, PQ = PASS == 3;
   using TX = Tile<32, DV / 8, kNT / 64>;  // Q, tQ, G, tG: read both ways
@@ -115,16 +120,25 @@ __global__ __launch_bounds__(kNT, 1) void bwd_pass_kernel(
   constexpr int NDMA_PRE = NS * NDMA / NQB;   // wave-loads issued before the barrier (behind the products of S)
   const int tid = threadIdx.x, lane = tid & 63, ic = lane & 31, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: what depends on it alone stays out of the VALU
-  const int nfix = PQ ? s.M : s.N, nstr = PQ ? s.N : s.M;  // rows of the fixed side, of the streamed side
+  const int nfix = PQ ? s.M : s.N;  // rows of the fixed side
   const int nfb = (nfix + kFix - 1) / kFix;
-  const int wg = xcd_remap(blockIdx.x, gridDim.x);
+  int nstr = PQ ? s.N : s.M;        // rows of the streamed side
+  int wg = xcd_remap(blockIdx.x, gridDim.x), z = 0, first = 0;
+  if (SPLIT) {  // part z of the streamed side: from here on a call with fewer rows there that start further on
+    const int wgs = nfb * s.B * s.H, n64 = (nstr + 63) >> 6;
+    z = wg / wgs;
+    wg -= z * wgs;
+    const int u0 = z * n64 / parts, u1 = (z + 1) * n64 / parts;
+    first = u0 * 64;
+    nstr = min(nstr, u1 * 64) - first;
+  }
   const int bh = wg / nfb, fb = wg - bh * nfb;
   const int b = bh / s.H, h = bh - b * s.H;
   const long long kbase = b * s.sb + h * s.sh, qbase = b * s.qsb + h * s.qsh;  // key side, query side
   const long long base = PQ ? qbase : kbase;    // fixed side
-  const long long tbase = PQ ? kbase : qbase;   // streamed side
   const long long fsn = PQ ? s.qsn : s.sn, tsn = PQ ? s.sn : s.qsn;
-  const long long rbase = (long long)bh * s.M;
+  const long long tbase = (PQ ? kbase : qbase) + first * tsn;   // streamed side
+  const long long rbase = (long long)bh * s.M + (PQ ? 0 : first);
   const int j = fb * kFix + wave * 32 + ic;  // this lane's row of the fixed side (a key; pass Q: a query)
 
   const unsigned pitch = (unsigned)(tsn * 2);  // row pitch of the streamed tensors in bytes
@@ -197,7 +211,7 @@ __global__ __launch_bounds__(kNT, 1) void bwd_pass_kernel(
     mub = iok ? stats[r] : 0.f;
     nds = -ds;
     ns1 = -s1;
-    if (iok && hh == 0) {
+    if (iok && hh == 0 && z == 0) {
       if (pipe_ws) {
         lse2w[r] = lse2;
         dsig[r] = nds;
@@ -486,7 +500,13 @@ __global__ __launch_bounds__(kNT, 1) void bwd_pass_kernel(
     landed_acc(a0[db]);
     landed_acc(a1[db]);
   }
-  {
+  if (SPLIT) {
+    const int row0 = fb * kFix + wave * 32;
+    const long long one = (long long)s.B * s.H * nfix * s.D;
+    float* const dst = part + z * 2 * one + ((long long)bh * nfix + row0) * s.D;
+    store_tile_f32<NDB>(dst, nfix - row0, s.D, a0, lane);
+    store_tile_f32<NDB>(dst + one, nfix - row0, s.D, a1, lane);
+  } else {
     // nobody reads the tile buffers any more and no tile load is in flight: each wave stages its two output
     // tiles through a region of its own
     constexpr unsigned REG = 32 * (64 * NDB + 16);
@@ -499,32 +519,39 @@ __global__ __launch_bounds__(kNT, 1) void bwd_pass_kernel(
   }
 }
 
+// One pass, whole or (a.part) with its streamed side in parts and their sum behind it.
+template <int DK, int DV, int PASS, bool HAS_G>
+hipError_t launch_pass(const Shape& s, const BwdArgs& a, hipStream_t st, bool pipe_ws) {
+  constexpr bool PQ = PASS == 3;
+  const int nfix = PQ ? s.M : s.N, nfb = (nfix + kFix - 1) / kFix;
+  const int parts = a.part != nullptr ? bwd_splits((long long)s.B * s.H, nfix, PQ ? s.N : s.M, 2) : 1;
+  const bf16* const qs[] = {(const bf16*)a.q, (const bf16*)a.tq, (const bf16*)a.gTO, (const bf16*)a.gO};
+  const bf16* const ks[] = {(const bf16*)a.k, (const bf16*)a.tk, (const bf16*)a.v, (const bf16*)a.tv};
+  const bf16* const* const f = PQ ? qs : ks;
+  const bf16* const* const t = PQ ? ks : qs;
+  void* const out[] = {PASS == 1 ? a.dv : PASS == 2 ? a.dk : a.dq, PASS == 1 ? a.dtv : PASS == 2 ? a.dtk : a.dtq};
+  auto go = [&](auto split) {
+    hipLaunchKernelGGL((bwd_pass_kernel<DK, DV, PASS, HAS_G, decltype(split)::value>), dim3(nfb * s.B * s.H * parts), dim3(kNT), 0, st,
+                       s, f[0], f[1], f[2], f[3], t[0], t[1], t[2], t[3], PQ ? a.lse : a.lse2, a.stats, a.dsig, a.sig1,
+                       PQ ? a.lse2 : nullptr, pipe_ws ? 1 : 0, PQ ? (const bf16*)a.o : nullptr, PQ ? (const bf16*)a.to : nullptr,
+                       (bf16*)out[0], (bf16*)out[1], a.part, parts);
+    return hipGetLastError();
+  };
+  if (parts == 1) return go(std::false_type{});
+  const hipError_t e = go(std::true_type{});
+  return e != hipSuccess ? e : launch_bwd_part_sum(s, PQ, a.part, parts, 2, PASS == 1 ? 0 : 2, out, st);
+}
+
 template <int DK, int DV, bool HAS_G>
 hipError_t launch_col(const Shape& s, const BwdArgs& a, hipStream_t st) {
-  const int nfb = (s.N + kFix - 1) / kFix;
-  const dim3 grid(nfb * s.B * s.H), block(kNT);
   // pass K first: it is the longer one
-  hipLaunchKernelGGL((bwd_pass_kernel<DK, DV, 2, HAS_G>), grid, block, 0, st, s, (const bf16*)a.k, (const bf16*)a.tk,
-                     (const bf16*)a.v, (const bf16*)a.tv, (const bf16*)a.q, (const bf16*)a.tq, (const bf16*)a.gTO,
-                     (const bf16*)a.gO, a.lse2, a.stats, a.dsig, a.sig1, nullptr, 1, nullptr, nullptr, (bf16*)a.dk,
-                     (bf16*)a.dtk);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((bwd_pass_kernel<DK, DV, 1, HAS_G>), grid, block, 0, st, s, (const bf16*)a.k, (const bf16*)a.tk,
-                     (const bf16*)a.v, (const bf16*)a.tv, (const bf16*)a.q, (const bf16*)a.tq, (const bf16*)a.gTO,
-                     (const bf16*)a.gO, a.lse2, a.stats, a.dsig, a.sig1, nullptr, 1, nullptr, nullptr, (bf16*)a.dv,
-                     (bf16*)a.dtv);
-  return hipGetLastError();
+  const hipError_t e = launch_pass<DK, DV, 2, HAS_G>(s, a, st, true);
+  return e != hipSuccess ? e : launch_pass<DK, DV, 1, HAS_G>(s, a, st, true);
 }
 
 template <int DK, int DV, bool HAS_G>
 hipError_t launch_row(const Shape& s, const BwdArgs& a, hipStream_t st, bool pipe_ws) {
-  const int nfb = (s.M + kFix - 1) / kFix;
-  hipLaunchKernelGGL((bwd_pass_kernel<DK, DV, 3, HAS_G>), dim3(nfb * s.B * s.H), dim3(kNT), 0, st, s, (const bf16*)a.q,
-                     (const bf16*)a.tq, (const bf16*)a.gTO, (const bf16*)a.gO, (const bf16*)a.k, (const bf16*)a.tk,
-                     (const bf16*)a.v, (const bf16*)a.tv, a.lse, a.stats, a.dsig, a.sig1, a.lse2, pipe_ws ? 1 : 0,
-                     (const bf16*)a.o, (const bf16*)a.to, (bf16*)a.dq, (bf16*)a.dtq);
-  return hipGetLastError();
+  return launch_pass<DK, DV, 3, HAS_G>(s, a, st, pipe_ws);
 }
 
 }  // namespace

@@ -526,7 +526,7 @@ hipError_t launch(const Shape& s, const BwdArgs& a, hipStream_t st) {
     if (parts > 1) {
       const hipError_t e = go(std::true_type{});
       void* const out[] = {a.dq, a.dtq};
-      return e != hipSuccess ? e : launch_bwd_part_sum(s, true, a.part, parts, 2, out, st);
+      return e != hipSuccess ? e : launch_bwd_part_sum(s, true, a.part, parts, 2, 2, out, st);
     }
   }
   return go(std::false_type{});

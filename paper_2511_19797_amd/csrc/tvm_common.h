@@ -88,13 +88,14 @@ inline int bwd_splits(long long heads, int fixed, int streamed, int tensors) {
   return best;
 }
 // Bytes of the partial gradients of the larger of the two backward kernels (0: neither is cut).  At most
-// 256 workgroups x 128 rows x 96 columns x 4 tensors of float32 = 48 MiB.
+// 256 workgroups x 128 rows x 96 columns x 4 tensors of float32 = 48 MiB (128 columns x 2 tensors: 32 MiB).
 inline size_t bwd_part_bytes(const Shape& s, int dtype) {
-  if (dtype != 1 || s.D > 96 || s.D % 8 != 0) return 0;
+  if (dtype != 1 || s.D > 128 || s.D % 8 != 0) return 0;
   const long long heads = (long long)s.B * s.H;
-  const int rs = bwd_splits(heads, s.M, s.N, 2), cs = bwd_splits(heads, s.N, s.M, 4);
+  const int ct = s.D > 96 ? 2 : 4;  // tensors of a key-side kernel: above 96 it runs as two passes, one after the other
+  const int rs = bwd_splits(heads, s.M, s.N, 2), cs = bwd_splits(heads, s.N, s.M, ct);
   const size_t row = rs > 1 ? (size_t)rs * 2 * heads * s.M * s.D * sizeof(float) : 0;
-  const size_t col = cs > 1 ? (size_t)cs * 4 * heads * s.N * s.D * sizeof(float) : 0;
+  const size_t col = cs > 1 ? (size_t)cs * ct * heads * s.N * s.D * sizeof(float) : 0;
   return row > col ? row : col;
 }
 constexpr size_t kBwdPartMax = (size_t)kBwdCUs * kBwdFix * 96 * 4 * sizeof(float);
@@ -117,9 +118,9 @@ hipError_t launch_bwd_col_pipe(const Shape& s, const BwdArgs& a, hipStream_t st)
 hipError_t launch_bwd_row_pipe_qknorm(const Shape& s, const BwdArgs& a, hipStream_t st);  // the same two with the QK-norm's
 hipError_t launch_bwd_col_pipe_qknorm(const Shape& s, const BwdArgs& a, hipStream_t st);  // backward in their epilogues
 // Adds the partial gradients of `parts` parts in order, scales and rounds them: `tensors` outputs [B,H,rows,D] (query-side or
-// key-side strides), the first two scaled by alpha, the others by one (bwd_part_sum.hip).
-hipError_t launch_bwd_part_sum(const Shape& s, bool query_side, const float* part, int parts, int tensors, void* const* out,
-                               hipStream_t st);
+// key-side strides), the first `scaled` of them times alpha (bwd_part_sum.hip).
+hipError_t launch_bwd_part_sum(const Shape& s, bool query_side, const float* part, int parts, int tensors, int scaled,
+                               void* const* out, hipStream_t st);
 hipError_t launch_gain_grad_sum(const float* part_q, int rows_q, float* gg_q, const float* part_k, int rows_k, float* gg_k,
                                 int D, hipStream_t st);  // adds partial gain-gradient rows in order (qknorm.hip)
 
