@@ -227,7 +227,7 @@ def tvmattn_jvp_bwd(q, k, v, tq, tk, tv, o, to, lse, stats, gO, gTO, scale=0.0, 
 
 
 def tvmattn_jvp_bwd_static(q, k, v, tq, tk, tv, o, to, lse, stats, gO, gTO, scale=0.0, out=None, flags=0):
-    """tvmattn_jvp_bwd without a workspace: the library's static device scratch holds the row vectors (at most
+    """tvmattn_jvp_bwd without a workspace: the library's static device scratch holds its place (at most
     TVMATTN_STATIC_MAX_ROWS query rows B*H*M).  The entry point itself allocates nothing; pass `out` to keep this
     wrapper from allocating the six gradients."""
     desc, out, ptrs = _bwd_args(q, k, v, tq, tk, tv, o, to, lse, stats, gO, gTO, scale, out, flags)

@@ -31,7 +31,15 @@
 // attention backward, where E = gZt = 0, the tangent inputs drop out and only dQ, dK, dV are
 // produced); 2 gTO only (the tangent path by itself, the paper's own split: the two products with
 // gO drop out).  The one-sided modes serve every head dim; mode 0 only those above 96.
+//
+// With few fixed rows and gO alone the streamed side is cut into parts (SPLIT; bwd_splits in tvm_common.h).  Results leave
+// through LDS as whole rows: stored straight from the accumulators, 8 bytes per
+// lane and row, they took 6 and 3 us more at B32 H18 N256 d64 with gO alone (key side 41 / 35 us, query side 33 / 30).  Parts
+// (whole backward with gO alone, us, whole / in parts): one head of 1024, d = 64, 46 / 27; one head of 4096 156 / 50, d = 128
+// 266 / 73; eight heads of 1024 47 / 44.
 #pragma once
+#include <type_traits>
+
 #include "mfma_tiles.h"
 
 namespace tvm {
@@ -50,13 +58,14 @@ __device__ __forceinline__ void zero_acc(f32x16 (&a)[NDB]) {
 // ------------------------------------------------------------------------------------------
 // Key side.
 // ------------------------------------------------------------------------------------------
-template <int DK, int DV, int kTS, int MODE>
+template <int DK, int DV, int kTS, int MODE, bool SPLIT>
 __global__ __launch_bounds__(kNT, MODE == 1 ? 2 : 1) void bwd_col_mfma_kernel(
     Shape s, const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v,
     const bf16* __restrict__ tq, const bf16* __restrict__ tk, const bf16* __restrict__ tv,
     const float* __restrict__ lse, const float* __restrict__ stats, const bf16* __restrict__ gO,
     const bf16* __restrict__ gTO, const float* __restrict__ dsig, const float* __restrict__ sig1,
-    bf16* __restrict__ dk, bf16* __restrict__ dtk, bf16* __restrict__ dv, bf16* __restrict__ dtv) {
+    bf16* __restrict__ dk, bf16* __restrict__ dtk, bf16* __restrict__ dv, bf16* __restrict__ dtv,
+    float* __restrict__ part, int parts) {
   using TX = Tile<kTS, DV / 8, kNT / 64>;  // read both ways: columns up to DV
   constexpr int ROWV = 4 * 256;                       // four float32 row vectors per stage (64 slots each)
   // one stage: Q, tQ, G, tG, row vectors; without gTO only Q and G (half the LDS: two workgroups per CU)
@@ -67,14 +76,22 @@ __global__ __launch_bounds__(kNT, MODE == 1 ? 2 : 1) void bwd_col_mfma_kernel(
   constexpr int NKS = DK / 16, NDB = DV / 32;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, ic = lane & 31, hh = lane >> 5;
   const int nfb = (s.N + kFix - 1) / kFix;
-  const int wg = xcd_remap(blockIdx.x, gridDim.x);
+  int wg = xcd_remap(blockIdx.x, gridDim.x), z = 0, i_first = 0;
+  const int rows = s.M;
+  if (SPLIT) {  // part z of the queries: from here on a call with fewer queries that start further on
+    const int wgs = nfb * s.B * s.H, ntiles = (s.M + 63) >> 6;
+    z = wg / wgs;
+    wg -= z * wgs;
+    const int t0 = z * ntiles / parts, t1 = (z + 1) * ntiles / parts;
+    i_first = t0 * 64;
+    s.M = min(s.M, t1 * 64) - i_first;
+  }
   const int bh = wg / nfb, fb = wg - bh * nfb;
   const int b = bh / s.H, h = bh - b * s.H;
   const long long base = b * s.sb + h * s.sh;     // key side (fixed)
-  const long long qbase = b * s.qsb + h * s.qsh;  // query side (streamed)
-  const long long rbase = (long long)bh * s.M;
+  const long long qbase = b * s.qsb + h * s.qsh + (long long)i_first * s.qsn;  // query side (streamed)
+  const long long rbase = (long long)bh * rows + i_first;
   const int j = fb * kFix + wave * 32 + ic;  // this lane's key
-  const bool jok = j < s.N;
 
   const typename TX::Lane lx = TX::lane_setup(s.D, wave, lane);
   const unsigned pitch = (unsigned)(s.qsn * 2);  // row pitch of the streamed (query-side) tensors in bytes
@@ -214,27 +231,37 @@ __global__ __launch_bounds__(kNT, MODE == 1 ? 2 : 1) void bwd_col_mfma_kernel(
     dma_wait();
     __syncthreads();  // next tile landed; everyone is done with this one
   }
-  if (!jok) return;
-  const long long ro = base + (long long)j * s.sn;
-  store_acc<NDB>(dk + ro, aK, s.alpha, s.D, hh);
-  store_acc<NDB>(dv + ro, aV, 1.f, s.D, hh);
+  const int row0 = fb * kFix + wave * 32;
+  if (SPLIT) {
+    const long long one = (long long)s.B * s.H * s.N * s.D;
+    float* const dst = part + z * 2 * one + ((long long)bh * s.N + row0) * s.D;
+    store_tile_f32<NDB>(dst, s.N - row0, s.D, aK, lane);
+    store_tile_f32<NDB>(dst + one, s.N - row0, s.D, aV, lane);
+    return;
+  }
+  // the loop ended with a barrier and no tile load is in flight: each wave stages its tiles through a region of its own
+  constexpr unsigned REG = 32 * (64 * NDB + 16);
+  static_assert(4 * REG <= 2 * BUF, "the output staging fits the stages");
+  const unsigned lw = lds0 + wave * REG;
+  store_tile_coalesced<NDB>(lw, dk + base, s.sn, row0, s.N, s.D, aK, s.alpha, lane);
+  store_tile_coalesced<NDB>(lw, dv + base, s.sn, row0, s.N, s.D, aV, 1.f, lane);
   if (MODE != 1) {
-    store_acc<NDB>(dtk + ro, aTK, s.alpha, s.D, hh);
-    store_acc<NDB>(dtv + ro, aTV, 1.f, s.D, hh);
+    store_tile_coalesced<NDB>(lw, dtk + base, s.sn, row0, s.N, s.D, aTK, s.alpha, lane);
+    store_tile_coalesced<NDB>(lw, dtv + base, s.sn, row0, s.N, s.D, aTV, 1.f, lane);
   }
 }
 
 // ------------------------------------------------------------------------------------------
 // Query side.
 // ------------------------------------------------------------------------------------------
-template <int DK, int DV, int kTS, int MODE>
+template <int DK, int DV, int kTS, int MODE, bool SPLIT>
 __global__ __launch_bounds__(kNT, MODE == 1 ? 2 : 1) void bwd_row_mfma_kernel(
     Shape s, const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v,
     const bf16* __restrict__ tq, const bf16* __restrict__ tk, const bf16* __restrict__ tv,
     const bf16* __restrict__ o, const bf16* __restrict__ to, const float* __restrict__ lse,
     const float* __restrict__ stats, const bf16* __restrict__ gO, const bf16* __restrict__ gTO,
     float* __restrict__ dsig, float* __restrict__ sig1, bf16* __restrict__ dq, bf16* __restrict__ dtq,
-    float* __restrict__ lse2w) {
+    float* __restrict__ lse2w, float* __restrict__ part, int parts) {
   using TK = Tile<kTS, DV / 8, kNT / 64>;  // K, tK: read both ways
   using TV = Tile<kTS, DK / 8, kNT / 64>;  // V, tV: score products only
   // one stage: K, tK, V, tV; without gTO only K and V (half the LDS: two workgroups per CU)
@@ -244,10 +271,19 @@ __global__ __launch_bounds__(kNT, MODE == 1 ? 2 : 1) void bwd_row_mfma_kernel(
   constexpr int NKS = DK / 16, NDB = DV / 32;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, ic = lane & 31, hh = lane >> 5;
   const int nfb = (s.M + kFix - 1) / kFix;
-  const int wg = xcd_remap(blockIdx.x, gridDim.x);
+  int wg = xcd_remap(blockIdx.x, gridDim.x), z = 0;
+  long long zoff = 0;
+  if (SPLIT) {  // part z of the keys: from here on a call with fewer keys that start further on
+    const int wgs = nfb * s.B * s.H, ntiles = (s.N + 63) >> 6;
+    z = wg / wgs;
+    wg -= z * wgs;
+    const int t0 = z * ntiles / parts, t1 = (z + 1) * ntiles / parts;
+    zoff = (long long)t0 * 64 * s.sn;
+    s.N = min(s.N, t1 * 64) - t0 * 64;
+  }
   const int bh = wg / nfb, fb = wg - bh * nfb;
   const int b = bh / s.H, h = bh - b * s.H;
-  const long long base = b * s.sb + h * s.sh;     // key side (streamed)
+  const long long base = b * s.sb + h * s.sh + zoff;  // key side (streamed)
   const long long qbase = b * s.qsb + h * s.qsh;  // query side (fixed)
   const int i = fb * kFix + wave * 32 + ic;  // this lane's query
   const bool iok = i < s.M;
@@ -303,7 +339,7 @@ __global__ __launch_bounds__(kNT, MODE == 1 ? 2 : 1) void bwd_row_mfma_kernel(
   const long long r = (long long)bh * s.M + (iok ? i : 0);
   const float lse2 = iok ? lse[r] * kLog2e : 0.f;
   const float mub = (MODE != 1 && iok) ? stats[r] : 0.f;
-  if (iok && hh == 0) {
+  if (iok && hh == 0 && z == 0) {
     if (lse2w != nullptr) {
       // for the hand-scheduled key-side passes (bwd_pass.hip): lse in log2 units, the two sums negated
       lse2w[r] = lse2;
@@ -417,31 +453,62 @@ __global__ __launch_bounds__(kNT, MODE == 1 ? 2 : 1) void bwd_row_mfma_kernel(
     dma_wait();
     __syncthreads();  // next tile landed; everyone is done with this one
   }
-  if (!iok) return;
-  const long long ro = qbase + (long long)i * s.qsn;
-  store_acc<NDB>(dq + ro, aQ, s.alpha, s.D, hh);
-  if (MODE != 1) store_acc<NDB>(dtq + ro, aTQ, s.alpha, s.D, hh);
+  const int row0 = fb * kFix + wave * 32;
+  if (SPLIT) {
+    store_tile_f32<NDB>(part + (((long long)z * s.B * s.H + bh) * s.M + row0) * s.D, s.M - row0, s.D, aQ, lane);
+    return;
+  }
+  // the loop ended with a barrier and no tile load is in flight: each wave stages its tiles through a region of its own
+  constexpr unsigned REG = 32 * (64 * NDB + 16);
+  static_assert(4 * REG <= 2 * BUF, "the output staging fits the stages");
+  const unsigned lw = lds0 + wave * REG;
+  store_tile_coalesced<NDB>(lw, dq + qbase, s.qsn, row0, s.M, s.D, aQ, s.alpha, lane);
+  if (MODE != 1) store_tile_coalesced<NDB>(lw, dtq + qbase, s.qsn, row0, s.M, s.D, aTQ, s.alpha, lane);
 }
 
+// (the parts of bwd_splits are those of a call with both gradients: their place is sized for it)
 template <int DK, int DV, int MODE>
 hipError_t launch_col(const Shape& s, const BwdArgs& a, hipStream_t st) {
   const int nfb = (s.N + kFix - 1) / kFix;
-  hipLaunchKernelGGL((bwd_col_mfma_kernel<DK, DV, (DV > 96 ? 32 : 64), MODE>), dim3(nfb * s.B * s.H), dim3(kNT), 0, st, s,
-                     (const bf16*)a.q, (const bf16*)a.k, (const bf16*)a.v, (const bf16*)a.tq, (const bf16*)a.tk,
-                     (const bf16*)a.tv, a.lse, a.stats, (const bf16*)a.gO, (const bf16*)a.gTO, a.dsig, a.sig1,
-                     (bf16*)a.dk, (bf16*)a.dtk, (bf16*)a.dv, (bf16*)a.dtv);
-  return hipGetLastError();
+  const int parts = MODE == 1 && a.part != nullptr ? bwd_splits((long long)s.B * s.H, s.N, s.M, s.D > 96 ? 2 : 4) : 1;
+  auto go = [&](auto split) {
+    hipLaunchKernelGGL((bwd_col_mfma_kernel<DK, DV, (DV > 96 ? 32 : 64), MODE, decltype(split)::value>),
+                       dim3(nfb * s.B * s.H * parts), dim3(kNT), 0, st, s, (const bf16*)a.q, (const bf16*)a.k, (const bf16*)a.v,
+                       (const bf16*)a.tq, (const bf16*)a.tk, (const bf16*)a.tv, a.lse, a.stats, (const bf16*)a.gO,
+                       (const bf16*)a.gTO, a.dsig, a.sig1, (bf16*)a.dk, (bf16*)a.dtk, (bf16*)a.dv, (bf16*)a.dtv, a.part, parts);
+    return hipGetLastError();
+  };
+  if constexpr (MODE == 1) {
+    if (parts > 1) {
+      const hipError_t e = go(std::true_type{});
+      void* const out[] = {a.dk, a.dv};
+      return e != hipSuccess ? e : launch_bwd_part_sum(s, false, a.part, parts, 2, 1, out, st);
+    }
+  }
+  return go(std::false_type{});
 }
 
 // pipe_ws: leave the row vectors in the workspace in the convention of the hand-scheduled key-side kernels
 template <int DK, int DV, int MODE>
 hipError_t launch_row(const Shape& s, const BwdArgs& a, hipStream_t st, bool pipe_ws = false) {
   const int nfb = (s.M + kFix - 1) / kFix;
-  hipLaunchKernelGGL((bwd_row_mfma_kernel<DK, DV, (DV > 96 ? 32 : 64), MODE>), dim3(nfb * s.B * s.H), dim3(kNT), 0, st, s,
-                     (const bf16*)a.q, (const bf16*)a.k, (const bf16*)a.v, (const bf16*)a.tq, (const bf16*)a.tk,
-                     (const bf16*)a.tv, (const bf16*)a.o, (const bf16*)a.to, a.lse, a.stats, (const bf16*)a.gO,
-                     (const bf16*)a.gTO, a.dsig, a.sig1, (bf16*)a.dq, (bf16*)a.dtq, pipe_ws ? a.lse2 : nullptr);
-  return hipGetLastError();
+  const int parts = MODE == 1 && a.part != nullptr ? bwd_splits((long long)s.B * s.H, s.M, s.N, 2) : 1;
+  auto go = [&](auto split) {
+    hipLaunchKernelGGL((bwd_row_mfma_kernel<DK, DV, (DV > 96 ? 32 : 64), MODE, decltype(split)::value>),
+                       dim3(nfb * s.B * s.H * parts), dim3(kNT), 0, st, s, (const bf16*)a.q, (const bf16*)a.k, (const bf16*)a.v,
+                       (const bf16*)a.tq, (const bf16*)a.tk, (const bf16*)a.tv, (const bf16*)a.o, (const bf16*)a.to, a.lse,
+                       a.stats, (const bf16*)a.gO, (const bf16*)a.gTO, a.dsig, a.sig1, (bf16*)a.dq, (bf16*)a.dtq,
+                       pipe_ws ? a.lse2 : nullptr, a.part, parts);
+    return hipGetLastError();
+  };
+  if constexpr (MODE == 1) {
+    if (parts > 1) {
+      const hipError_t e = go(std::true_type{});
+      void* const out[] = {a.dq};
+      return e != hipSuccess ? e : launch_bwd_part_sum(s, true, a.part, parts, 1, 1, out, st);
+    }
+  }
+  return go(std::false_type{});
 }
 
 }  // namespace

@@ -323,23 +323,6 @@ __device__ __forceinline__ int xcd_remap(int wg, int nwg) {
   return (wg & 7) * per + (wg >> 3);
 }
 
-// Stores a transposed accumulator (rows = d, column = this lane's row of the output) as bf16, scaled.
-template <int NDB>
-__device__ __forceinline__ void store_acc(bf16* __restrict__ dst, const f32x16 (&a)[NDB], float scale, int D, int hh) {
-#pragma unroll
-  for (int db = 0; db < NDB; ++db)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int d0 = db * 32 + 8 * g + 4 * hh;
-      if (d0 < D) {
-        bf16x4 o;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) o[t] = (bf16)(a[db][4 * g + t] * scale);
-        *reinterpret_cast<bf16x4*>(dst + d0) = o;
-      }
-    }
-}
-
 // Coalesced store of one wave's [32 x D] output tile held as transposed accumulators (rows = d,
 // column = this lane's output row): the wave parks the tile in its own LDS region as bf16, row by
 // row, then writes it out in 16-byte chunks with consecutive lanes on consecutive chunks, so a

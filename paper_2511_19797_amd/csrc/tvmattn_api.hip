@@ -285,10 +285,9 @@ int tvmattn_jvp_bwd_timed(const tvmattn_desc* desc, const void* q, const void* k
   if (rc) return rc;
   const size_t one = row_vector_bytes(s);
   char* const ws = static_cast<char*>(workspace);  // (a null workspace fails the pointer checks in bwd_impl)
-  // (a workspace that only holds the row vectors serves too: the streamed side then stays whole.  With gO alone the
-  // partial gradients are not used.)
+  // (a workspace that only holds the row vectors serves too: the streamed side then stays whole)
   const size_t pb = part_bytes(desc, s);
-  const bool cut = ws && gTO && pb != 0 && workspace_bytes >= 3 * one + pb;
+  const bool cut = ws && pb != 0 && workspace_bytes >= 3 * one + pb;
   return bwd_impl(desc, s, q, k, v, tq, tk, tv, o, to, lse, stats, gO, gTO, dq, dk, dv, dtq, dtk, dtv,
                   reinterpret_cast<float*>(ws), reinterpret_cast<float*>(ws ? ws + one : nullptr),
                   reinterpret_cast<float*>(ws ? ws + 2 * one : nullptr), workspace_bytes >= 3 * one,
@@ -337,7 +336,7 @@ int tvmattn_jvp_bwd_static(const tvmattn_desc* desc, const void* q, const void* 
   // kernel, behind it on the same stream, reads them
   return bwd_impl(desc, s, q, k, v, tq, tk, tv, o, to, lse, stats, gO, gTO, dq, dk, dv, dtq, dtk, dtv, base,
                   base + kStaticMaxRows, base + 2 * kStaticMaxRows, true,
-                  gTO && part_bytes(desc, s) != 0 ? base + 3 * kStaticMaxRows : nullptr, nullptr, hip_stream);
+                  part_bytes(desc, s) != 0 ? base + 3 * kStaticMaxRows : nullptr, nullptr, hip_stream);
 }
 
 // ---- RMSNorm with gain as QK-norm, with tangent

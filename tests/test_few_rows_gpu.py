@@ -53,7 +53,7 @@ def test_strided_static_and_small_workspace(d):
         assert pu.rel_err(a.float().cpu(), e.float().cpu()) <= 2 ** -7, n  # one bf16 rounding either side, at the largest
 
 
-@pytest.mark.parametrize("d", [72, 104])
+@pytest.mark.parametrize("d", [8, 72, 104, 128])
 @pytest.mark.parametrize("which", ["gO", "gTO"])
 def test_one_upstream_gradient(which, d):
     w = dataclasses.replace(wl.custom(1, 1, 1500, d, "bf16"), M=1030)
