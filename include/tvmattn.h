@@ -131,6 +131,8 @@ size_t tvmattn_jvp_bwd_workspace_bytes(const tvmattn_desc* desc);
  * Launches on the stream: a query-side pass (dq,dtq; Steps 3,5) that also forms the row
  * scalars of Step 1 (delta = gO.O, Sigma_1 = gTO.O, Sigma_2 = gTO.tO per row; a separate
  * launch on the plain-ALU path), then a key-side pass (dk,dtk,dv,dtv; Steps 2,4,6).
+ * With few rows on a side, and a workspace of the size asked for, that side's pass runs in parts over the other side
+ * and a further launch adds their float32 sums in order.
  * No atomics: results are bitwise reproducible.
  *
  * One upstream gradient only (both NULL is TVMATTN_INVALID_ARG):
