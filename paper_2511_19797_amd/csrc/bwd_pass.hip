@@ -125,12 +125,12 @@ __global__ __launch_bounds__(kNT, 1) void bwd_pass_kernel(
   int nstr = PQ ? s.N : s.M;        // rows of the streamed side
   int wg = xcd_remap(blockIdx.x, gridDim.x), z = 0, first = 0;
   if (SPLIT) {  // part z of the streamed side: from here on a call with fewer rows there that start further on
-    const int wgs = nfb * s.B * s.H, n64 = (nstr + 63) >> 6;
+    const int wgs = nfb * s.B * s.H;
     z = wg / wgs;
     wg -= z * wgs;
-    const int u0 = z * n64 / parts, u1 = (z + 1) * n64 / parts;
-    first = u0 * 64;
-    nstr = min(nstr, u1 * 64) - first;
+    const PartRows p = part_rows(nstr, z, parts);
+    first = p.first;
+    nstr = p.end - p.first;
   }
   const int bh = wg / nfb, fb = wg - bh * nfb;
   const int b = bh / s.H, h = bh - b * s.H;

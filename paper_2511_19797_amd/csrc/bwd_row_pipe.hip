@@ -97,12 +97,12 @@ __global__ __launch_bounds__(kNT, 1) void bwd_row_pipe_kernel(
   int wg = xcd_remap(blockIdx.x, gridDim.x), z = 0;
   long long zoff = 0;
   if (SPLIT) {  // part z of the keys: from here on a call with fewer keys that start further on
-    const int wgs = nfb * s.B * s.H, ntiles = (s.N + 63) >> 6;
+    const int wgs = nfb * s.B * s.H;
     z = wg / wgs;
     wg -= z * wgs;
-    const int t0 = z * ntiles / parts, t1 = (z + 1) * ntiles / parts;
-    zoff = (long long)t0 * 64 * s.sn;
-    s.N = min(s.N, t1 * 64) - t0 * 64;
+    const PartRows p = part_rows(s.N, z, parts);
+    zoff = (long long)p.first * s.sn;
+    s.N = p.end - p.first;
   }
   const int bh = wg / nfb, fb = wg - bh * nfb;
   const int b = bh / s.H, h = bh - b * s.H;

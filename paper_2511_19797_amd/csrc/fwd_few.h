@@ -12,7 +12,7 @@ namespace tvm {
 //   4096 keys:   128: 136 / 32   256: 137 / 36   512: 137 / 69   768: 138 / 101  1024: 138 / 132  (d = 128: 768: 179 / 170)
 inline bool fwd_few_rows(const Shape& s) {
   if (s.N < 128) return false;
-  const long long blocks = (long long)s.B * s.H * ((s.M + 31) / 32);
+  const long long blocks = (long long)s.B * s.H * (((long long)s.M + 31) / 32);
   return blocks <= (s.N < 512 ? 256 : s.N < 2048 || s.D > 96 ? 512 : 768);
 }
 hipError_t launch_fwd_few(const Shape& s, const FwdArgs& a, hipStream_t st);

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(64 * kNW, 1) void fwd_few_kernel(Shape s, const bf1
   const unsigned pitch = (unsigned)(s.sn * 2);
   char* const mine = lds + wave * BUF;
   const unsigned lds0 = lds_addr_of(lds), st = lds0 + (unsigned)wave * BUF;
-  const int ntiles = (s.N + 31) >> 5, tlast = ntiles - 1;
+  const int ntiles = (int)(((unsigned)s.N + 31u) >> 5), tlast = ntiles - 1;
   // per-lane byte offsets of the loads within a tile: for whole tiles, and for the last one, where rows past the end
   // fetch its last row again (keys of probability 0)
   typename TK::Offs ok_full, ok_last;
@@ -131,10 +131,10 @@ __global__ __launch_bounds__(64 * kNW, 1) void fwd_few_kernel(Shape s, const bf1
         sT = mfma(kf[kk], tqf[kk], sT);
         sT = mfma(tkf[kk], qf[kk], sT);
       }
-      if (t * 32 + 32 > s.N) {  // uniform: ragged last tile, keys >= N get probability 0
+      if (s.N - t * 32 < 32) {  // uniform: ragged last tile, keys >= N get probability 0
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          if (t * 32 + drow(r, hh) >= s.N) sS[r] = -INFINITY;
+          if (drow(r, hh) >= s.N - t * 32) sS[r] = -INFINITY;
       }
       float mx = sS[0];
 #pragma unroll

@@ -70,12 +70,14 @@ struct BwdArgs {
 // part.  Of those the fewest tiles one after the other, what the sum costs counted in tiles (1.5 - 2 us each): a launch
 // and the first tiles' latency are worth four, the partial sums of 256 workgroups two for each tensor (both ways at 5 TB/s).
 // Below 1024 streamed rows there is less than that to be had.  Whole backward (us, whole / in parts): one head of 1024, d = 64
-// 62 / 38; one head of 4096 209 / 74; one of 8192 403 / 178; four of 4096 213 / 177; 16 heads of 1024, d = 72 in two parts 77 / 79
-// (whole by this rule).
+// 62 / 38; one head of 4096 207 / 71; one of 8192 402 / 172; four of 4096 210 / 169; 16 heads of 1024, d = 72 in two parts 77 / 79
+// (whole by this rule).  Calls with gO alone take the parts of the call with both gradients, by whose tensors the rule weighs
+// the sum and the workspace is sized: twice what they leave, so they are cut in fewer parts than would pay (eight heads of
+// 1024, d = 64: 46 / 45).
 constexpr int kBwdCUs = 256, kBwdFix = 128;
 inline int bwd_splits(long long heads, int fixed, int streamed, int tensors) {
-  const long long wgs = heads * ((fixed + kBwdFix - 1) / kBwdFix);
-  const int tiles = (streamed + 63) / 64;
+  const long long wgs = heads * (((long long)fixed + kBwdFix - 1) / kBwdFix);
+  const int tiles = (int)(((long long)streamed + 63) / 64);
   if (tiles < 16 || 2 * wgs > kBwdCUs) return 1;
   int best = 1, best_cost = tiles;
   for (int p = 2; p <= tiles / 4 && p * wgs <= kBwdCUs; ++p) {
@@ -86,6 +88,16 @@ inline int bwd_splits(long long heads, int fixed, int streamed, int tensors) {
     }
   }
   return best;
+}
+// Rows first .. end-1 of part z of `rows` rows cut into `parts` parts: whole tiles of 64, floor(z tiles / parts) of them
+// before part z.  The product z tiles does not fit 32 bits from 2^29 rows on, so the quotient is taken apart first.
+struct PartRows {
+  int first, end;
+};
+__host__ __device__ inline PartRows part_rows(int rows, int z, int parts) {
+  const unsigned tiles = ((unsigned)rows + 63u) >> 6, n = (unsigned)parts, q = tiles / n, r = tiles - q * n;
+  const unsigned t0 = (unsigned)z * q + (unsigned)z * r / n, t1 = ((unsigned)z + 1u) * q + ((unsigned)z + 1u) * r / n;
+  return PartRows{(int)(t0 * 64u), t1 == tiles ? rows : (int)(t1 * 64u)};
 }
 // Bytes of the partial gradients of the larger of the two backward kernels (0: neither is cut).  At most
 // 256 workgroups x 128 rows x 96 columns x 4 tensors of float32 = 48 MiB (128 columns x 2 tensors: 32 MiB).
