@@ -12,7 +12,7 @@
 // both sets.  Everything is computed transposed, D = Q-fragment x P-fragment, so that a lane owns one output ROW
 // (32 per 32x32 block) and 16 of its columns: results leave through LDS as whole rows (store_tile_coalesced).
 //
-// Four tile shapes (chosen by pick_shape and plan_dw below): 256 x 256 and 256 x 192 here, 128 x 128 and 64 x 64 in
+// Four tile shapes (chosen by pick_shape and plan_dw, linear_plan.h): 256 x 256 and 256 x 192 here, 128 x 128 and 64 x 64 in
 // gemm_small_kernel.  Workgroup: eight waves as 2 x 4 (two per SIMD), each with 4 x 2 blocks of 32 x 32 (128 accumulator
 // registers), or as 4 x 2 with 2 x 3 blocks: a 256 x 256 or 256 x 192 output tile (128 flop per byte staged: smaller tiles are bound by L2->LDS traffic), contraction in
 // tiles of 64 through two LDS stages filled by asynchronous global->LDS loads (mfma_tiles.h: the same swizzled
@@ -29,6 +29,7 @@
 // row ranges, then one kernel that adds those.
 #include <type_traits>
 
+#include "linear_plan.h"
 #include "mfma_tiles.h"
 
 namespace tvm {
@@ -42,7 +43,6 @@ struct Cfg {
   static constexpr int TI = NWI_ * WI_ * 32;  // output rows per workgroup
   static constexpr int TJ = NWJ_ * WJ_ * 32;  // output columns per workgroup
 };
-constexpr int kBK = 64;                      // contraction per LDS tile
 constexpr int kGI = 8;                       // tile rows per group in the order the tiles are handed out
 
 // Transposed fragment with the contraction index in natural order: lane (ic, hh) gets, of column 32*db + ic of the
@@ -650,25 +650,11 @@ using Cfg256 = Cfg<2, 4, 4, 2, 2, 1>;  // 256 x 256, eight waves
 using Cfg192 = Cfg<4, 2, 2, 3, 2, 1>;  // 256 x 192, eight waves
 using Cfg128 = Cfg<2, 2, 2, 2, 3, 1>;  // 128 x 128, four waves
 using Cfg64 = Cfg<2, 2, 1, 1, 4, 2>;   // 64 x 64, four waves
+template <class C>
+constexpr bool shape_is(int c) { return C::TI == kTileI[c] && C::TJ == kTileJ[c]; }
+static_assert(shape_is<Cfg256>(k256) && shape_is<Cfg192>(k192) && shape_is<Cfg128>(k128) && shape_is<Cfg64>(k64), "the plan's tiles");
+static_assert(Cfg128::NT == kSmallThreads && Cfg64::NT == kSmallThreads, "the plan's limit");
 
-int dw_splits(int F, int K, int R) {
-  const int tiles = ((F + Cfg256::TI - 1) / Cfg256::TI) * ((K + Cfg256::TJ - 1) / Cfg256::TJ);
-  const int ntot = 2 * ((R + kBK - 1) / kBK);
-  // (the most splits any tile shape uses, and what the workspace is sized for)
-  // The fewest rounds of workgroups over the chip's 256 CUs (one workgroup each), each round costing its share of
-  // the contraction plus a fixed part (start-up, the float32 partial tile); ties go to fewer splits.
-  int best = 1;
-  long long best_cost = -1;
-  for (int s = 1; s <= 32 && s <= ntot; ++s) {
-    const long long rounds = ((long long)s * tiles + 255) / 256;
-    const long long cost = rounds * ((ntot + s - 1) / s + 64);
-    if (best_cost < 0 || cost < best_cost) {
-      best_cost = cost;
-      best = s;
-    }
-  }
-  return best;
-}
 // Persistent workgroups: 8 XCDs x at most 32 CUs, fewer where an XCD's share of the tiles is smaller.
 int persistent_grid(int tiles) {
   const int per = (tiles + 7) / 8;
@@ -679,67 +665,10 @@ int bias_chunks(int R) {
   return c > 256 ? 256 : c;
 }
 
-
-// ---- Which tile shape serves a product
-enum { k256, k192, k128, k64, kShapes };
-constexpr int kTileI[kShapes] = {Cfg256::TI, Cfg192::TI, Cfg128::TI, Cfg64::TI};
-constexpr int kTileJ[kShapes] = {Cfg256::TJ, Cfg192::TJ, Cfg128::TJ, Cfg64::TJ};
-int tiles_of(int c, int I, int J) { return (I + kTileI[c] - 1) / kTileI[c] * ((J + kTileJ[c] - 1) / kTileJ[c]); }
-
-// Time of `tiles` output tiles of shape c over `steps` contraction tiles each, in units of a hundredth of a contraction
-// tile of the 256 x 256 shape (1.5 us on an idle chip, 2 us on a full one): rounds of workgroups over the chip's 256
-// CUs times steps and a fixed part.  The weights are fits to measured times, R = 64 ... 16384 rows, widths 384, 768,
-// 1152 and their multiples by 3 and 4: they put the fastest shape first, or one within 3 % of it.  Some of both sides
-// (us; 256 | 192 | 128 | 64):
-//   forward, 256 x 4608 -> 1152:    104 |  99 |  52 |  32     few tiles: small ones fill the chip
-//   forward, 1024 x 4608 -> 1152:   101 |  94 |  53 |  60
-//   forward, 2048 x 1152 -> 3456:    40 |  58 |  63 |  75     224 tiles of 256 are one round, 288 of 192 are two
-//   forward, 16384 x 4608 -> 1152:  395 | 384 | 455 | 636     1152 = 6 x 192: no padded columns
-//   forward, 16384 x 1152 -> 4608:  321 | 355 | 524 | 690
-// The layers of a whole block with tangent, forward and backward (us, before / with this choice): B1 T256 C1152 forward 232 /
-// 198, B2 T250 C768 626 / 529 (both then bound by the host's calls), B32 T256 C1152 2727 / 2684, B16 T1024 5434 / 5359.
-long long tile_cost(int c, long long tiles, int steps) {
-  constexpr int kStep[kShapes] = {100, 88, 45, 28}, kFixed[kShapes] = {150, 130, 70, 50}, kSlots[kShapes] = {256, 256, 256, 512};
-  return (tiles + kSlots[c] - 1) / kSlots[c] * ((long long)steps * kStep[c] + kFixed[c]);
-}
-int pick_shape(int sets, int I, int J, int C) {
-  int best = k256;
-  for (int c = k192; c < kShapes; ++c) {
-    const int steps = (C + kBK - 1) / kBK;
-    if (tile_cost(c, (long long)sets * tiles_of(c, I, J), steps) < tile_cost(best, (long long)sets * tiles_of(best, I, J), steps)) best = c;
-  }
-  return best;
-}
-// Shape and number of contraction splits of grad W: what the partial tiles cost on top is two passes over them at
-// 5 TB/s and a launch (3 us).  The 128 and 64 shapes write bf16 directly when there is one split.  Never more splits
-// than dw_splits: the workspace is sized for those.
-// (us of the whole backward, R 500 768 -> 768: 53 with 16 splits of 256 x 256 tiles, 35 with one of 64 x 64; R 16384
-// 1152 -> 3456: 597 with 3 splits of 256 x 256, 581 with 3 of 256 x 192.)
-struct DwPlan {
-  int shape, splits;
-};
-DwPlan plan_dw(int F, int K, int R, int max_splits) {
-  const int ntot = 2 * ((R + kBK - 1) / kBK);
-  DwPlan best{k256, max_splits};
-  long long best_cost = -1;
-  for (int c = 0; c < kShapes; ++c)
-    for (int s = 1; s <= max_splits; ++s) {
-      const long long tiles = (long long)s * tiles_of(c, F, K);
-      // (grad W's 64 x 64 tiles fit one workgroup per CU: half as many at once)
-      long long cost = tile_cost(c, c == k64 ? 2 * tiles : tiles, (ntot + s - 1) / s);
-      if (s > 1 || c < k128) cost += 180 + (long long)s * F * K / 10000;  // 8 bytes per partial sum, 60 units per us
-      if (best_cost < 0 || cost < best_cost) {
-        best_cost = cost;
-        best = DwPlan{c, s};
-      }
-    }
-  return best;
-}
-
 // Launches a product with tile shape c.  (DIRECT: the 256-row shapes are left out, see plan_dw.)
 template <bool PTR, bool QTR, bool PARTIAL, bool DIRECT = false>
 hipError_t launch_gemm(int c, const GemmArgs& g, hipStream_t st) {
-  const int tiles = g.nz * tiles_of(c, g.I, g.J), small_grid = 8 * ((tiles + 7) / 8);
+  const int tiles = (int)(g.nz * tiles_of(c, g.I, g.J)), small_grid = (int)small_workgroups(tiles);
   if (c == k64) {
     hipLaunchKernelGGL((gemm_small_kernel<PTR, QTR, PARTIAL, Cfg64>), dim3(small_grid), dim3(Cfg64::NT), 0, st, g);
   } else if (DIRECT || c == k128) {

@@ -3,6 +3,7 @@
 #include <cstring>
 
 #include "../../paper_2511_19797_amd/csrc/fwd_few.h"
+#include "../../paper_2511_19797_amd/csrc/linear_plan.h"
 #include "../../paper_2511_19797_amd/csrc/tvm_common.h"
 
 using namespace tvm;
@@ -27,6 +28,10 @@ int main() {
       s.N = (int)a[2];
       s.D = (int)a[3];
       std::printf("%d\n", fwd_few_rows(s) ? 1 : 0);
+    } else if (!std::strcmp(what, "linear") && n == 3) {  // R K F: tile shapes of y, grad x, grad W (0 .. 3), splits of grad W
+      const int R = (int)a[0], K = (int)a[1], F = (int)a[2];
+      const DwPlan w = plan_dw(F, K, R, dw_splits(F, K, R));
+      std::printf("%d %d %d %d\n", pick_shape(2, R, F, K), pick_shape(2, R, K, F), w.shape, w.splits);
     } else {
       std::printf("? %s", line);
     }

@@ -34,3 +34,16 @@ def test_parts_fit_the_chip_and_their_place():
     cases = [(rng.randint(1, 300), rng.randint(1, 20000), rng.randint(1, 20000), rng.choice([2, 4])) for _ in range(400)]
     for (heads, fixed, streamed, _), (p,) in zip(cases, ask([("bwd_splits", *c) for c in cases])):
         assert p == 1 or (p * heads * -(-fixed // 128) <= 256 and 4 * p <= -(-streamed // 64))
+
+
+@pytest.mark.parametrize("R", [2 ** 28, 2 ** 29 - 1, 2 ** 29, 2 ** 30, MAX_ROWS - 255])
+def test_linear_tiles_fit_one_launch(R):
+    """The 128 and 64 tiles take a workgroup of 256 threads each, and a launch has at most 2^32 - 1 threads: calls with more
+    small tiles than that go to the persistent 256-row shapes (y: 2 x R x F, grad x: 2 x R x K)."""
+    for K, F in ((32, 32), (32, 96), (64, 32), (96, 64), (192, 32)):
+        (y, gx, _, _), = ask([("linear", R, K, F)])
+        for shape, width in ((y, F), (gx, K)):
+            if shape >= 2:
+                tile = 128 if shape == 2 else 64
+                tiles = 2 * -(-R // tile) * -(-width // tile)
+                assert -(-tiles // 8) * 8 * 256 < 2 ** 32, (R, K, F, shape)
