@@ -713,7 +713,7 @@ hipError_t launch_linear_fwd(int R, int K, int F, long long ldx, long long ldy, 
   g.ldo = ldy;
   g.bias = (const bf16*)bias;
   g.nz = 2;
-  return launch_gemm<false, false, false>(pick_shape(2, R, F, K), g, st);
+  return launch_gemm<false, false, false>(pick_shape(false, 2, R, F, K), g, st);
 }
 
 hipError_t launch_linear_bwd(int R, int K, int F, long long ldx, long long ldy, const void* x, const void* tx,
@@ -734,7 +734,7 @@ hipError_t launch_linear_bwd(int R, int K, int F, long long ldx, long long ldy, 
     g.out[1] = (bf16*)gtx;
     g.ldo = ldx;
     g.nz = 2;
-    const hipError_t e = launch_gemm<false, true, false>(pick_shape(2, R, K, F), g, st);
+    const hipError_t e = launch_gemm<false, true, false>(pick_shape(true, 2, R, K, F), g, st);
     if (e != hipSuccess) return e;
   }
   const int max_splits = dw_splits(F, K, R);

@@ -31,7 +31,7 @@ int main() {
     } else if (!std::strcmp(what, "linear") && n == 3) {  // R K F: tile shapes of y, grad x, grad W (0 .. 3), splits of grad W
       const int R = (int)a[0], K = (int)a[1], F = (int)a[2];
       const DwPlan w = plan_dw(F, K, R, dw_splits(F, K, R));
-      std::printf("%d %d %d %d\n", pick_shape(2, R, F, K), pick_shape(2, R, K, F), w.shape, w.splits);
+      std::printf("%d %d %d %d\n", pick_shape(false, 2, R, F, K), pick_shape(true, 2, R, K, F), w.shape, w.splits);
     } else {
       std::printf("? %s", line);
     }

@@ -47,3 +47,28 @@ def test_linear_tiles_fit_one_launch(R):
                 tile = 128 if shape == 2 else 64
                 tiles = 2 * -(-R // tile) * -(-width // tile)
                 assert -(-tiles // 8) * 8 * 256 < 2 ** 32, (R, K, F, shape)
+
+
+# R, K, F and the measured times (us) of the 256, 192, 128 and 64 tiles: the forward, and a whole backward without bias whose
+# grad x takes the shape
+MEASURED_FORWARD = [
+    (2048, 768, 1536, (26.1, 25.2, 28.4, 31.1)), (4096, 1152, 768, (33.6, 32.9, 36.4, 40.3)),
+    (4096, 768, 768, (26.0, 25.2, 28.6, 30.3)), (2048, 384, 1536, (17.5, 17.4, 20.5, 21.2)),
+    (8192, 384, 384, (17.7, 17.2, 20.7, 21.3)), (256, 4608, 1152, (101.7, 97.7, 51.0, 30.6)),
+    (1024, 1536, 1152, (40.3, 38.2, 23.9, 27.1)), (2048, 1152, 3456, (37.9, 60.7, 66.5, 81.4)),
+    (16384, 384, 1152, (45.8, 47.5, 79.3, 101.5)), (500, 768, 768, (23.5, 22.0, 15.2, 10.3)),
+    (64, 768, 768, (22.6, 21.4, 14.7, 9.6)), (65536, 32, 128, (19.2, 21.6, 26.9, 32.7)),
+    (8192, 256, 32, (11.9, 11.4, 8.9, 6.7)), (16384, 64, 1152, (25.9, 29.7, 53.7, 66.8)),
+]
+MEASURED_BACKWARD = [
+    (4096, 768, 384, (38.1, 37.2, 40.8, 42.5)), (16384, 1152, 1152, (211.5, 201.6, 249.7, 304.3)),
+    (8192, 96, 1536, (61.6, 56.8, 44.5, 40.5)), (500, 768, 768, (32.5, 30.2, 23.5, 19.0)),
+    (2048, 768, 768, (43.5, 41.4, 35.7, 37.7)), (1024, 768, 1152, (47.3, 44.4, 34.5, 31.0)),
+]
+
+
+@pytest.mark.parametrize("R,K,F,times,which", [(*m, 0) for m in MEASURED_FORWARD] + [(*m, 1) for m in MEASURED_BACKWARD])
+def test_linear_tiles_against_measured_times(R, K, F, times, which):
+    """The chosen shape is the fastest measured one, or within 4 % of it."""
+    shape = ask([("linear", R, K, F)])[0][which]
+    assert times[shape] <= 1.04 * min(times), (shape, times)
