@@ -554,14 +554,6 @@ hipError_t bwd_col_f32_m(const Shape& s, const BwdArgs& a, hipStream_t st) {
 
 }  // namespace
 
-// The rule of the dispatch.  Where these kernels take a call they are ahead at every size (both ends measured above), so
-// the line is drawn by what they can read.  Rows are addressed by 32-bit byte offsets within a head (a ragged last tile included), and 16-byte loads take whole
-// groups of four columns (pitches and bases are 16-byte multiples for every call).
-bool f32_mfma_supported(const Shape& s, int dtype) {
-  constexpr long long kMax = (1ll << 31) - 1;
-  const auto fits = [](int rows, long long pitch) { return pitch <= kMax / 4 / ((long long)rows + kR); };
-  return dtype == 0 && s.D % 4 == 0 && s.D <= 128 && fits(s.N, s.sn) && fits(s.M, s.qsn);
-}
 hipError_t launch_fwd_f32(const Shape& s, const FwdArgs& a, hipStream_t st) {
   return s.D <= 32 ? fwd_f32_t<32>(s, a, st) : s.D <= 64 ? fwd_f32_t<64>(s, a, st) : s.D <= 96 ? fwd_f32_t<96>(s, a, st) : fwd_f32_t<128>(s, a, st);
 }

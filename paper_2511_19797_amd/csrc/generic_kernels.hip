@@ -1,8 +1,8 @@
 // Plain-ALU kernels: one wavefront per query row (or per key row), float32
 // arithmetic throughout.  They serve what the matrix-core kernels do not take:
 // bf16 head dims that are not a multiple of 8, float32 ones that are not a
-// multiple of 4, head dims above 128.  Formulas: App. C of the paper -- the equations under "Step 1"
-// for S, Sdot, P, N; Steps 2-6 for the six gradients, with the row sums
+// multiple of 4, head dims above 128, and float32 calls of a handful of rows
+// (f32_mfma.h).  Formulas: App. C of the paper -- the equations under "Step 1" for S, Sdot, P, N; Steps 2-6 for the six gradients, with the row sums
 // Sigma_1, Sigma_2 collapsed to row dot products (Sigma_1 = gTO.O,
 // Sigma_2 = gTO.tO, since O = P V and tO = (P o N) V + P tV).
 #include "f32_mfma.h"
@@ -362,19 +362,19 @@ hipError_t bwd_row_generic_t(const Shape& s, const BwdArgs& a, hipStream_t st) {
 }  // namespace
 
 hipError_t launch_fwd_generic(const Shape& s, int dtype, const FwdArgs& a, hipStream_t st) {
-  if (f32_mfma_supported(s, dtype)) return launch_fwd_f32(s, a, st);
+  if (f32_mfma_fwd(s, dtype)) return launch_fwd_f32(s, a, st);
   return (dtype & ~kPlainAlu) == 0 ? fwd_generic_t<float>(s, a, st) : fwd_generic_t<bf16>(s, a, st);
 }
 hipError_t launch_bwd_pre(const Shape& s, int dtype, const BwdArgs& a, hipStream_t st) {
-  if (f32_mfma_supported(s, dtype)) return hipSuccess;  // the query-side kernel does Step 1 itself
+  if (f32_mfma_bwd(s, dtype, a.mode)) return hipSuccess;  // the query-side kernel does Step 1 itself
   return (dtype & ~kPlainAlu) == 0 ? bwd_pre_t<float>(s, a, st) : bwd_pre_t<bf16>(s, a, st);
 }
 hipError_t launch_bwd_col_generic(const Shape& s, int dtype, const BwdArgs& a, hipStream_t st) {
-  if (f32_mfma_supported(s, dtype)) return launch_bwd_col_f32(s, a, st);
+  if (f32_mfma_bwd(s, dtype, a.mode)) return launch_bwd_col_f32(s, a, st);
   return (dtype & ~kPlainAlu) == 0 ? bwd_col_generic_t<float>(s, a, st) : bwd_col_generic_t<bf16>(s, a, st);
 }
 hipError_t launch_bwd_row_generic(const Shape& s, int dtype, const BwdArgs& a, hipStream_t st) {
-  if (f32_mfma_supported(s, dtype)) return launch_bwd_row_f32(s, a, st);
+  if (f32_mfma_bwd(s, dtype, a.mode)) return launch_bwd_row_f32(s, a, st);
   return (dtype & ~kPlainAlu) == 0 ? bwd_row_generic_t<float>(s, a, st) : bwd_row_generic_t<bf16>(s, a, st);
 }
 

@@ -23,7 +23,7 @@ inline bool grid_fits(int c, long long tiles) { return c < k128 || small_workgro
 // its steps and a fixed part (first operands, results), behind a start-up.  The weights are fits to times of all four shapes at
 // 1177 forward shapes and 556 of grad x (whose second operand is read transposed: other weights), R = 64 ... 65536 rows, widths
 // 32 ... 4608 either way: the choice is within 1 % of the 256 x 256 shape or faster at all but 9 of them (at most 4 %, one
-// round's noise), and 1.1 % behind the fastest shape on average.  Some of them (us; 256 | 192 | 128 | 64):
+// round's noise), and 0.1 % behind the fastest shape on average.  Some of them (us; 256 | 192 | 128 | 64):
 //   forward, 256 x 4608 -> 1152:    102 |  98 |  51 |  31     few tiles: small ones fill the chip
 //   forward, 1024 x 1536 -> 1152:    40 |  38 |  24 |  27
 //   forward, 2048 x 768 -> 1536:     26 |  25 |  28 |  31     the small shapes' fixed part, round after round

@@ -2,6 +2,7 @@
 #include <cstdio>
 #include <cstring>
 
+#include "../../paper_2511_19797_amd/csrc/f32_mfma.h"
 #include "../../paper_2511_19797_amd/csrc/fwd_few.h"
 #include "../../paper_2511_19797_amd/csrc/linear_plan.h"
 #include "../../paper_2511_19797_amd/csrc/tvm_common.h"
@@ -32,6 +33,15 @@ int main() {
       const int R = (int)a[0], K = (int)a[1], F = (int)a[2];
       const DwPlan w = plan_dw(F, K, R, dw_splits(F, K, R));
       std::printf("%d %d %d %d\n", pick_shape(false, 2, R, F, K), pick_shape(true, 2, R, K, F), w.shape, w.splits);
+    } else if (!std::strcmp(what, "f32") && n == 4) {  // heads M N D: matrix cores in the forward, the backward, with gO alone
+      Shape s{};
+      s.B = 1;
+      s.H = (int)a[0];
+      s.M = (int)a[1];
+      s.N = (int)a[2];
+      s.D = (int)a[3];
+      s.sn = s.qsn = s.D;
+      std::printf("%d %d %d\n", f32_mfma_fwd(s, 0) ? 1 : 0, f32_mfma_bwd(s, 0, 0) ? 1 : 0, f32_mfma_bwd(s, 0, 1) ? 1 : 0);
     } else {
       std::printf("? %s", line);
     }

@@ -72,3 +72,32 @@ def test_linear_tiles_against_measured_times(R, K, F, times, which):
     """The chosen shape is the fastest measured one, or within 4 % of it."""
     shape = ask([("linear", R, K, F)])[0][which]
     assert times[shape] <= 1.04 * min(times), (shape, times)
+
+
+# float32: heads, M, N, d and the measured times (us) of the plain-ALU and of the matrix-core kernels, forward and backward
+MEASURED_F32 = [
+    (1, 1, 1, 4, (3.9, 4.7), (8.6, 10.9)), (1, 1, 1, 64, (5.1, 5.5), (20.9, 13.3)), (1, 4, 4, 16, (4.5, 4.6), (12.4, 10.9)),
+    (16384, 1, 1, 16, (28.4, 44.1), (99.4, 161.2)), (16384, 1, 1, 64, (62.7, 85.6), (298.0, 428.6)),
+    (16384, 1, 1, 128, (119.9, 293.4), (582.4, 1475.0)), (16384, 4, 4, 128, (156.8, 316.9), (1013.9, 1820.4)),
+    (16384, 4, 4, 32, (59.9, 60.6), (269.3, 215.0)), (2048, 4, 4, 64, (15.5, 13.5), (65.4, 47.1)),
+    (2048, 1, 16, 128, (52.1, 41.8), (321.6, 200.1)), (2048, 16, 1, 64, (37.5, 15.3), (156.5, 59.7)),
+    (1, 16, 1, 128, (7.6, 8.3), (45.5, 23.2)), (2048, 8, 8, 64, (33.9, 14.0), None), (2048, 64, 4, 32, (107.6, 35.4), None),
+]
+
+
+@pytest.mark.parametrize("heads,M,N,d,fwd,bwd", MEASURED_F32)
+def test_f32_kernels_against_measured_times(heads, M, N, d, fwd, bwd):
+    """The kernel family a float32 call takes is the faster measured one, or within 5 % of it; with gO alone always the matrix
+    cores."""
+    mfma_fwd, mfma_bwd, mfma_go = ask([("f32", heads, M, N, d)])[0]
+    assert fwd[mfma_fwd] <= 1.05 * min(fwd)
+    assert bwd is None or bwd[mfma_bwd] <= 1.05 * min(bwd)
+    assert mfma_go == 1
+
+
+def test_f32_kernels_of_ordinary_sizes():
+    """More than eight rows on both sides: the matrix cores, for every head dim that they read and no other."""
+    rng = random.Random(3)
+    cases = [(rng.choice([1, 48, 5000, 20000]), rng.randint(9, 5000), rng.randint(17, 5000), rng.randint(1, 256)) for _ in range(200)]
+    for (_, _, _, d), got in zip(cases, ask([("f32", *c) for c in cases])):
+        assert got == ((1, 1, 1) if d % 4 == 0 and d <= 128 else (0, 0, 0))

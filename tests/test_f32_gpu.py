@@ -29,6 +29,33 @@ def test_tile_edges(d):
         pu.check_heads(w, inp, fwd, grads, pu.all_heads(w))
 
 
+@pytest.mark.parametrize("H,M,N,d", [(4096, 4, 4, 16), (4096, 5, 4, 16), (4095, 1, 1, 64), (4096, 1, 1, 64), (1024, 4, 4, 128),
+                                     (64, 16, 1, 128), (65, 16, 1, 128), (4096, 1, 16, 100), (4096, 1, 17, 100), (4096, 8, 8, 104),
+                                     (3, 1, 1, 4), (3, 2, 2, 40), (3, 1, 2, 24)])
+def test_few_rows_on_both_sides_of_the_lines(H, M, N, d):
+    """Around the row and head counts where the kernel family changes, for the forward, the backward and the backward with gO
+    alone: sampled heads against the oracle, and every element against the plain-ALU kernels."""
+    w = dataclasses.replace(wl.custom(1, H, N, d, "f32"), M=M)
+    print(f"[case] {w}", flush=True)
+    inp = wl.make_inputs(w, 3 + d)
+    fwd, grads = pu.run_gpu(inp)
+    pu.check_heads(w, inp, fwd, grads, [(0, 0), (0, H // 2), (0, H - 1)])
+    # Against the plain-ALU kernels an error counts relative to the tensor's largest entry, or absolutely where that is below
+    # one: with a single key the gradients of q and k are exactly zero (P = 1), and what either family leaves of them is the
+    # difference of two d-term sums of O(1) products, at most d 2^-24 of the sum of their sizes (d^2 2^-24 x O(1) < 1e-3, in
+    # practice 1e-6).
+    near = lambda a, b: float((a - b).abs().max()) <= pu.TOL["f32"] * max(1.0, float(b.abs().max()))
+    pfwd, pgrads = pu.run_gpu(inp, flags=tvm.TVMATTN_FLAG_PLAIN_ALU)
+    for n, a, b in zip(pu.FWD_NAMES + pu.BWD_NAMES, fwd + tuple(grads), pfwd + tuple(pgrads)):
+        assert near(a, b), n
+    dev = {n: t.cuda() for n, t in inp.items()}
+    six = [dev[n] for n in ("q", "k", "v", "tq", "tk", "tv")]
+    alone, plain = (tvm.tvmattn_jvp_bwd(*six, *f, dev["gO"], None, flags=fl)
+                    for f, fl in ((fwd, 0), (pfwd, tvm.TVMATTN_FLAG_PLAIN_ALU)))
+    for a, b in zip(alone[:3], plain[:3]):
+        assert near(a, b)
+
+
 @pytest.mark.parametrize("d", [32, 72, 128])
 @pytest.mark.parametrize("which", ["gO", "gTO"])
 def test_one_upstream_gradient(d, which):
