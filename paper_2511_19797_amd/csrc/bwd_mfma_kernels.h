@@ -32,11 +32,10 @@
 // produced); 2 gTO only (the tangent path by itself, the paper's own split: the two products with
 // gO drop out).  The one-sided modes serve every head dim; mode 0 only those above 96.
 //
-// With few fixed rows and gO alone the streamed side is cut into parts (SPLIT; bwd_splits in tvm_common.h).  Results leave
-// through LDS as whole rows: stored straight from the accumulators, 8 bytes per
-// lane and row, they took 6 and 3 us more at B32 H18 N256 d64 with gO alone (key side 41 / 35 us, query side 33 / 30).  Parts
-// (whole backward with gO alone, us, whole / in parts): one head of 1024, d = 64, 46 / 27; one head of 4096 156 / 50, d = 128
-// 266 / 73; eight heads of 1024 47 / 44.
+// How results leave (LEAVE): straight from the accumulators, 8 bytes per lane and row; through LDS as whole rows (gO alone,
+// leave_as_rows below says when); or, with few fixed rows and gO alone, as float32 sums of one of the parts that the streamed
+// side is cut into (bwd_splits in tvm_common.h).  Parts (whole backward with gO alone, us, whole / in parts): one head of 1024,
+// d = 64, 46 / 27; one head of 4096 158 / 52, d = 128 270 / 74; four heads of 4096 157 / 106; eight heads of 1024 46 / 45.
 #pragma once
 #include <type_traits>
 
@@ -55,10 +54,29 @@ __device__ __forceinline__ void zero_acc(f32x16 (&a)[NDB]) {
   for (int db = 0; db < NDB; ++db) a[db] = zero16();
 }
 
+enum { kStraight, kRows, kParts };  // LEAVE
+
+// Stores a transposed accumulator (rows = d, column = this lane's row of the output) as bf16, scaled.
+template <int NDB>
+__device__ __forceinline__ void store_acc(bf16* __restrict__ dst, const f32x16 (&a)[NDB], float scale, int D, int hh) {
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int d0 = db * 32 + 8 * g + 4 * hh;
+      if (d0 < D) {
+        bf16x4 o;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) o[t] = (bf16)(a[db][4 * g + t] * scale);
+        *reinterpret_cast<bf16x4*>(dst + d0) = o;
+      }
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // Key side.
 // ------------------------------------------------------------------------------------------
-template <int DK, int DV, int kTS, int MODE, bool SPLIT>
+template <int DK, int DV, int kTS, int MODE, int LEAVE>
 __global__ __launch_bounds__(kNT, MODE == 1 ? 2 : 1) void bwd_col_mfma_kernel(
     Shape s, const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v,
     const bf16* __restrict__ tq, const bf16* __restrict__ tk, const bf16* __restrict__ tv,
@@ -78,7 +96,7 @@ __global__ __launch_bounds__(kNT, MODE == 1 ? 2 : 1) void bwd_col_mfma_kernel(
   const int nfb = (s.N + kFix - 1) / kFix;
   int wg = xcd_remap(blockIdx.x, gridDim.x), z = 0, i_first = 0;
   const int rows = s.M;
-  if (SPLIT) {  // part z of the queries: from here on a call with fewer queries that start further on
+  if (LEAVE == kParts) {  // part z of the queries: from here on a call with fewer queries that start further on
     const int wgs = nfb * s.B * s.H;
     z = wg / wgs;
     wg -= z * wgs;
@@ -231,8 +249,19 @@ __global__ __launch_bounds__(kNT, MODE == 1 ? 2 : 1) void bwd_col_mfma_kernel(
     dma_wait();
     __syncthreads();  // next tile landed; everyone is done with this one
   }
+  if (LEAVE == kStraight) {
+    if (j >= s.N) return;
+    const long long ro = base + (long long)j * s.sn;
+    store_acc<NDB>(dk + ro, aK, s.alpha, s.D, hh);
+    store_acc<NDB>(dv + ro, aV, 1.f, s.D, hh);
+    if (MODE != 1) {
+      store_acc<NDB>(dtk + ro, aTK, s.alpha, s.D, hh);
+      store_acc<NDB>(dtv + ro, aTV, 1.f, s.D, hh);
+    }
+    return;
+  }
   const int row0 = fb * kFix + wave * 32;
-  if (SPLIT) {
+  if (LEAVE == kParts) {
     const long long one = (long long)s.B * s.H * s.N * s.D;
     float* const dst = part + z * 2 * one + ((long long)bh * s.N + row0) * s.D;
     store_tile_f32<NDB>(dst, s.N - row0, s.D, aK, lane);
@@ -245,16 +274,12 @@ __global__ __launch_bounds__(kNT, MODE == 1 ? 2 : 1) void bwd_col_mfma_kernel(
   const unsigned lw = lds0 + wave * REG;
   store_tile_coalesced<NDB>(lw, dk + base, s.sn, row0, s.N, s.D, aK, s.alpha, lane);
   store_tile_coalesced<NDB>(lw, dv + base, s.sn, row0, s.N, s.D, aV, 1.f, lane);
-  if (MODE != 1) {
-    store_tile_coalesced<NDB>(lw, dtk + base, s.sn, row0, s.N, s.D, aTK, s.alpha, lane);
-    store_tile_coalesced<NDB>(lw, dtv + base, s.sn, row0, s.N, s.D, aTV, 1.f, lane);
-  }
 }
 
 // ------------------------------------------------------------------------------------------
 // Query side.
 // ------------------------------------------------------------------------------------------
-template <int DK, int DV, int kTS, int MODE, bool SPLIT>
+template <int DK, int DV, int kTS, int MODE, int LEAVE>
 __global__ __launch_bounds__(kNT, MODE == 1 ? 2 : 1) void bwd_row_mfma_kernel(
     Shape s, const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v,
     const bf16* __restrict__ tq, const bf16* __restrict__ tk, const bf16* __restrict__ tv,
@@ -273,7 +298,7 @@ __global__ __launch_bounds__(kNT, MODE == 1 ? 2 : 1) void bwd_row_mfma_kernel(
   const int nfb = (s.M + kFix - 1) / kFix;
   int wg = xcd_remap(blockIdx.x, gridDim.x), z = 0;
   long long zoff = 0;
-  if (SPLIT) {  // part z of the keys: from here on a call with fewer keys that start further on
+  if (LEAVE == kParts) {  // part z of the keys: from here on a call with fewer keys that start further on
     const int wgs = nfb * s.B * s.H;
     z = wg / wgs;
     wg -= z * wgs;
@@ -453,8 +478,15 @@ __global__ __launch_bounds__(kNT, MODE == 1 ? 2 : 1) void bwd_row_mfma_kernel(
     dma_wait();
     __syncthreads();  // next tile landed; everyone is done with this one
   }
+  if (LEAVE == kStraight) {
+    if (!iok) return;
+    const long long ro = qbase + (long long)i * s.qsn;
+    store_acc<NDB>(dq + ro, aQ, s.alpha, s.D, hh);
+    if (MODE != 1) store_acc<NDB>(dtq + ro, aTQ, s.alpha, s.D, hh);
+    return;
+  }
   const int row0 = fb * kFix + wave * 32;
-  if (SPLIT) {
+  if (LEAVE == kParts) {
     store_tile_f32<NDB>(part + (((long long)z * s.B * s.H + bh) * s.M + row0) * s.D, s.M - row0, s.D, aQ, lane);
     return;
   }
@@ -463,7 +495,6 @@ __global__ __launch_bounds__(kNT, MODE == 1 ? 2 : 1) void bwd_row_mfma_kernel(
   static_assert(4 * REG <= 2 * BUF, "the output staging fits the stages");
   const unsigned lw = lds0 + wave * REG;
   store_tile_coalesced<NDB>(lw, dq + qbase, s.qsn, row0, s.M, s.D, aQ, s.alpha, lane);
-  if (MODE != 1) store_tile_coalesced<NDB>(lw, dtq + qbase, s.qsn, row0, s.M, s.D, aTQ, s.alpha, lane);
 }
 
 // (the parts of bwd_splits are those of a call with both gradients: their place is sized for it)
@@ -471,8 +502,8 @@ template <int DK, int DV, int MODE>
 hipError_t launch_col(const Shape& s, const BwdArgs& a, hipStream_t st) {
   const int nfb = (s.N + kFix - 1) / kFix;
   const int parts = MODE == 1 && a.part != nullptr ? bwd_splits((long long)s.B * s.H, s.N, s.M, s.D > 96 ? 2 : 4) : 1;
-  auto go = [&](auto split) {
-    hipLaunchKernelGGL((bwd_col_mfma_kernel<DK, DV, (DV > 96 ? 32 : 64), MODE, decltype(split)::value>),
+  auto go = [&](auto leave) {
+    hipLaunchKernelGGL((bwd_col_mfma_kernel<DK, DV, (DV > 96 ? 32 : 64), MODE, decltype(leave)::value>),
                        dim3(nfb * s.B * s.H * parts), dim3(kNT), 0, st, s, (const bf16*)a.q, (const bf16*)a.k, (const bf16*)a.v,
                        (const bf16*)a.tq, (const bf16*)a.tk, (const bf16*)a.tv, a.lse, a.stats, (const bf16*)a.gO,
                        (const bf16*)a.gTO, a.dsig, a.sig1, (bf16*)a.dk, (bf16*)a.dtk, (bf16*)a.dv, (bf16*)a.dtv, a.part, parts);
@@ -480,12 +511,13 @@ hipError_t launch_col(const Shape& s, const BwdArgs& a, hipStream_t st) {
   };
   if constexpr (MODE == 1) {
     if (parts > 1) {
-      const hipError_t e = go(std::true_type{});
+      const hipError_t e = go(std::integral_constant<int, kParts>{});
       void* const out[] = {a.dk, a.dv};
       return e != hipSuccess ? e : launch_bwd_part_sum(s, false, a.part, parts, 2, 1, out, st);
     }
+    if (leave_as_rows((long long)nfb * s.B * s.H, s.N, s.D)) return go(std::integral_constant<int, kRows>{});
   }
-  return go(std::false_type{});
+  return go(std::integral_constant<int, kStraight>{});
 }
 
 // pipe_ws: leave the row vectors in the workspace in the convention of the hand-scheduled key-side kernels
@@ -493,8 +525,8 @@ template <int DK, int DV, int MODE>
 hipError_t launch_row(const Shape& s, const BwdArgs& a, hipStream_t st, bool pipe_ws = false) {
   const int nfb = (s.M + kFix - 1) / kFix;
   const int parts = MODE == 1 && a.part != nullptr ? bwd_splits((long long)s.B * s.H, s.M, s.N, 2) : 1;
-  auto go = [&](auto split) {
-    hipLaunchKernelGGL((bwd_row_mfma_kernel<DK, DV, (DV > 96 ? 32 : 64), MODE, decltype(split)::value>),
+  auto go = [&](auto leave) {
+    hipLaunchKernelGGL((bwd_row_mfma_kernel<DK, DV, (DV > 96 ? 32 : 64), MODE, decltype(leave)::value>),
                        dim3(nfb * s.B * s.H * parts), dim3(kNT), 0, st, s, (const bf16*)a.q, (const bf16*)a.k, (const bf16*)a.v,
                        (const bf16*)a.tq, (const bf16*)a.tk, (const bf16*)a.tv, (const bf16*)a.o, (const bf16*)a.to, a.lse,
                        a.stats, (const bf16*)a.gO, (const bf16*)a.gTO, a.dsig, a.sig1, (bf16*)a.dq, (bf16*)a.dtq,
@@ -503,12 +535,13 @@ hipError_t launch_row(const Shape& s, const BwdArgs& a, hipStream_t st, bool pip
   };
   if constexpr (MODE == 1) {
     if (parts > 1) {
-      const hipError_t e = go(std::true_type{});
+      const hipError_t e = go(std::integral_constant<int, kParts>{});
       void* const out[] = {a.dq};
       return e != hipSuccess ? e : launch_bwd_part_sum(s, true, a.part, parts, 1, 1, out, st);
     }
+    if (leave_as_rows((long long)nfb * s.B * s.H, s.M, s.D)) return go(std::integral_constant<int, kRows>{});
   }
-  return go(std::false_type{});
+  return go(std::integral_constant<int, kStraight>{});
 }
 
 }  // namespace

@@ -101,3 +101,19 @@ def test_f32_kernels_of_ordinary_sizes():
     cases = [(rng.choice([1, 48, 5000, 20000]), rng.randint(9, 5000), rng.randint(17, 5000), rng.randint(1, 256)) for _ in range(200)]
     for (_, _, _, d), got in zip(cases, ask([("f32", *c) for c in cases])):
         assert got == ((1, 1, 1) if d % 4 == 0 and d <= 128 else (0, 0, 0))
+
+
+# gO alone: heads, rows, d and the measured whole backward (us) with results straight from the accumulators and as whole rows
+MEASURED_STORES = [
+    (1, 33, 72, (9.4, 10.3)), (2048, 33, 72, (44.8, 47.9)), (64, 64, 72, (10.0, 10.8)), (1024, 64, 72, (31.9, 32.8)),
+    (1024, 64, 64, (28.0, 26.7)), (2048, 64, 128, (93.5, 84.2)), (2048, 128, 8, (26.4, 28.0)), (16, 128, 64, (14.5, 13.1)),
+    (16, 128, 72, (12.8, 13.1)), (256, 128, 72, (18.3, 16.8)), (2048, 128, 72, (102.8, 89.9)), (1, 128, 128, (22.0, 19.2)),
+    (256, 512, 104, (142.4, 129.0)), (1, 512, 64, (28.8, 27.2)), (512, 256, 32, (32.4, 31.9)), (64, 33, 104, (12.5, 13.4)),
+    (256, 96, 88, (16.3, 15.0)), (2048, 96, 48, (54.2, 50.6)), (1, 96, 56, (9.3, 9.7)),
+]
+
+
+@pytest.mark.parametrize("heads,rows,d,times", MEASURED_STORES)
+def test_stores_of_the_ordinary_backward_against_measured_times(heads, rows, d, times):
+    (whole,), = ask([("rows", heads, rows, d)])
+    assert times[whole] <= 1.02 * min(times)

@@ -84,3 +84,28 @@ def test_a_wave_without_finite_scores():
     ref = orc.attn_jvp_fwd_head(*[wl.to_f64(t.cpu()) for t in args], None)
     for g, r in zip((o, to, lse), ref):
         assert pu.rel_err(g[0, 0].double().cpu().numpy(), r) <= pu.TOL["bf16"]
+
+
+@pytest.mark.parametrize("d", [8, 24, 32, 40, 64, 72, 96, 104, 128])
+@pytest.mark.parametrize("H,M,N", [(2, 200, 130), (130, 130, 260), (520, 70, 33), (3, 50, 63)])
+def test_gO_alone_both_ways_to_store(H, M, N, d):
+    """The ordinary backward on few and on many workgroups, on rows that fill no workgroup and no wave: results straight from
+    the accumulators and as whole rows, ragged on both sides, sampled heads against the oracle; nothing is written beyond a
+    tensor's rows."""
+    w = dataclasses.replace(wl.custom(1, H, N, d, "bf16"), M=M)
+    print(f"[case] {w} gO alone", flush=True)
+    inp = wl.make_inputs(w, 17)
+    dev = {n: t.cuda() for n, t in inp.items()}
+    six = [dev[n] for n in ("q", "k", "v", "tq", "tk", "tv")]
+    fwd = tvm.tvmattn_jvp_fwd(*six)
+    room = [torch.full((H * rows * d + 4096,), float("nan"), dtype=torch.bfloat16, device="cuda") for rows in (M, N, N)]
+    out = [r[:H * rows * d].view(1, H, rows, d) for r, rows in zip(room, (M, N, N))]
+    tvm.tvmattn_jvp_bwd(*six, *fwd, dev["gO"], None, out=(*out, None, None, None))
+    torch.cuda.synchronize()
+    for r, o in zip(room, out):
+        assert bool(torch.isnan(r[o.numel():].float()).all()) and not bool(torch.isnan(o.float()).any())
+    for h in (0, H // 2, H - 1):
+        a = [wl.to_f64(inp[n][0, h]) for n in wl.NAMES]
+        a[wl.NAMES.index("gTO")] = np.zeros_like(a[wl.NAMES.index("gO")])
+        for n, g, r in zip(pu.BWD_NAMES, out, orc.attn_jvp_bwd_head(*a, None)):
+            assert pu.rel_err(g[0, h].float().cpu().numpy(), r) <= pu.TOL["bf16"], (h, n)
