@@ -32,8 +32,8 @@
 // produced); 2 gTO only (the tangent path by itself, the paper's own split: the two products with
 // gO drop out).  The one-sided modes serve every head dim; mode 0 only those above 96.
 //
-// How results leave (LEAVE): straight from the accumulators, 8 bytes per lane and row; through LDS as whole rows (gO alone,
-// leave_as_rows below says when); or, with few fixed rows and gO alone, as float32 sums of one of the parts that the streamed
+// How results leave (LEAVE): straight from the accumulators, 8 bytes per lane and row; through LDS as whole rows
+// (leave_as_rows in tvm_common.h says when); or, with few fixed rows and gO alone, as float32 sums of one of the parts that the streamed
 // side is cut into (bwd_splits in tvm_common.h).  Parts (whole backward with gO alone, us, whole / in parts): one head of 1024,
 // d = 64, 46 / 27; one head of 4096 158 / 52, d = 128 270 / 74; four heads of 4096 157 / 106; eight heads of 1024 46 / 45.
 #pragma once
@@ -274,6 +274,10 @@ __global__ __launch_bounds__(kNT, MODE == 1 ? 2 : 1) void bwd_col_mfma_kernel(
   const unsigned lw = lds0 + wave * REG;
   store_tile_coalesced<NDB>(lw, dk + base, s.sn, row0, s.N, s.D, aK, s.alpha, lane);
   store_tile_coalesced<NDB>(lw, dv + base, s.sn, row0, s.N, s.D, aV, 1.f, lane);
+  if (MODE != 1) {
+    store_tile_coalesced<NDB>(lw, dtk + base, s.sn, row0, s.N, s.D, aTK, s.alpha, lane);
+    store_tile_coalesced<NDB>(lw, dtv + base, s.sn, row0, s.N, s.D, aTV, 1.f, lane);
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -495,6 +499,7 @@ __global__ __launch_bounds__(kNT, MODE == 1 ? 2 : 1) void bwd_row_mfma_kernel(
   static_assert(4 * REG <= 2 * BUF, "the output staging fits the stages");
   const unsigned lw = lds0 + wave * REG;
   store_tile_coalesced<NDB>(lw, dq + qbase, s.qsn, row0, s.M, s.D, aQ, s.alpha, lane);
+  if (MODE != 1) store_tile_coalesced<NDB>(lw, dtq + qbase, s.qsn, row0, s.M, s.D, aTQ, s.alpha, lane);
 }
 
 // (the parts of bwd_splits are those of a call with both gradients: their place is sized for it)
@@ -515,8 +520,8 @@ hipError_t launch_col(const Shape& s, const BwdArgs& a, hipStream_t st) {
       void* const out[] = {a.dk, a.dv};
       return e != hipSuccess ? e : launch_bwd_part_sum(s, false, a.part, parts, 2, 1, out, st);
     }
-    if (leave_as_rows((long long)nfb * s.B * s.H, s.N, s.D)) return go(std::integral_constant<int, kRows>{});
   }
+  if (leave_as_rows(MODE != 1, (long long)nfb * s.B * s.H, s.N, s.D)) return go(std::integral_constant<int, kRows>{});
   return go(std::integral_constant<int, kStraight>{});
 }
 
@@ -539,8 +544,8 @@ hipError_t launch_row(const Shape& s, const BwdArgs& a, hipStream_t st, bool pip
       void* const out[] = {a.dq};
       return e != hipSuccess ? e : launch_bwd_part_sum(s, true, a.part, parts, 1, 1, out, st);
     }
-    if (leave_as_rows((long long)nfb * s.B * s.H, s.M, s.D)) return go(std::integral_constant<int, kRows>{});
   }
+  if (leave_as_rows(MODE != 1, (long long)nfb * s.B * s.H, s.M, s.D)) return go(std::integral_constant<int, kRows>{});
   return go(std::integral_constant<int, kStraight>{});
 }
 

@@ -99,7 +99,7 @@ __host__ __device__ inline PartRows part_rows(int rows, int z, int parts) {
   const unsigned t0 = (unsigned)z * q + (unsigned)z * r / n, t1 = ((unsigned)z + 1u) * q + ((unsigned)z + 1u) * r / n;
   return PartRows{(int)(t0 * 64u), t1 == tiles ? rows : (int)(t1 * 64u)};
 }
-// gO alone (the generic-order kernels): whether a kernel of `wgs` workgroups on `rows` fixed rows per head stores its results as
+// The generic-order kernels of the backward: whether one of `wgs` workgroups on `rows` fixed rows per head stores its results as
 // whole rows through LDS rather than straight from the accumulators, 8 bytes per lane and row.  Whole rows halve the store
 // instructions' cost, but every wave stages all its padded columns, also for rows and columns that do not exist: they pay where
 // the chip is full or nothing is padded (whole backward, us, straight / whole rows; one workgroup per 128 rows of a head):
@@ -108,8 +108,11 @@ __host__ __device__ inline PartRows part_rows(int rows, int z, int parts) {
 //   128 rows:  16 heads d = 40 +7 %, d = 72 12.8 / 13.1, d = 64 14.5 / 13.1;  256 heads d = 40 -3 %, d = 72 18.3 / 16.8;
 //              2048 heads d = 72 103 / 90, d = 64 87 / 74, d = 8 26.4 / 28.0
 //   512 rows:  1 head d = 48 +7 %, d = 72 27.3 / 27.5;  192 heads d = 48 -10 %;  512 heads d = 16 +2 %
-inline bool leave_as_rows(long long wgs, int rows, int D) {
-  if (rows < 64 || D <= 24) return false;
+// With the tangent (head dims above 96, 64 rows or fewer on the other side) from 96 rows on: one other-side row, d = 104, 256
+// heads of 96 rows -6 %, of 65 the same; 64 other-side rows, d = 128, any number of heads of 128 rows -7 %.
+inline bool leave_as_rows(bool tangent, long long wgs, int rows, int D) {
+  if (rows < (tangent ? 96 : 64) || D <= 24) return false;
+  if (D > 120) return true;
   if (rows < 96) return wgs >= (D >= 112 ? 256 : 512) && (D == 64 || D >= 80);
   if (D % 32 == 0 || D >= 112) return rows >= 128 || wgs >= 192;
   return wgs >= (D < 56 ? 256 : rows < 128 ? 192 : 128);

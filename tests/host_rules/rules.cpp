@@ -42,8 +42,8 @@ int main() {
       s.D = (int)a[3];
       s.sn = s.qsn = s.D;
       std::printf("%d %d %d\n", f32_mfma_fwd(s, 0) ? 1 : 0, f32_mfma_bwd(s, 0, 0) ? 1 : 0, f32_mfma_bwd(s, 0, 1) ? 1 : 0);
-    } else if (!std::strcmp(what, "rows") && n == 3) {  // heads rows D
-      std::printf("%d\n", leave_as_rows(a[0] * ((a[1] + 127) / 128), (int)a[1], (int)a[2]) ? 1 : 0);
+    } else if (!std::strcmp(what, "rows") && n == 4) {  // tangent heads rows D
+      std::printf("%d\n", leave_as_rows(a[0] != 0, a[1] * ((a[2] + 127) / 128), (int)a[2], (int)a[3]) ? 1 : 0);
     } else {
       std::printf("? %s", line);
     }

@@ -103,7 +103,8 @@ def test_f32_kernels_of_ordinary_sizes():
         assert got == ((1, 1, 1) if d % 4 == 0 and d <= 128 else (0, 0, 0))
 
 
-# gO alone: heads, rows, d and the measured whole backward (us) with results straight from the accumulators and as whole rows
+# heads, rows, d and the measured whole backward (us) with results straight from the accumulators and as whole rows: gO alone;
+# with the tangent and at most 64 rows on the other side
 MEASURED_STORES = [
     (1, 33, 72, (9.4, 10.3)), (2048, 33, 72, (44.8, 47.9)), (64, 64, 72, (10.0, 10.8)), (1024, 64, 72, (31.9, 32.8)),
     (1024, 64, 64, (28.0, 26.7)), (2048, 64, 128, (93.5, 84.2)), (2048, 128, 8, (26.4, 28.0)), (16, 128, 64, (14.5, 13.1)),
@@ -113,7 +114,12 @@ MEASURED_STORES = [
 ]
 
 
-@pytest.mark.parametrize("heads,rows,d,times", MEASURED_STORES)
-def test_stores_of_the_ordinary_backward_against_measured_times(heads, rows, d, times):
-    (whole,), = ask([("rows", heads, rows, d)])
+MEASURED_STORES_TANGENT = [
+    (64, 33, 104, (22.5, 25.7)), (1024, 64, 104, (116.8, 123.4)), (166, 976, 128, (179.4, 162.7)), (64, 64, 128, (30.6, 30.8)),
+]
+
+
+@pytest.mark.parametrize("tangent,heads,rows,d,times", [(0, *m) for m in MEASURED_STORES] + [(1, *m) for m in MEASURED_STORES_TANGENT])
+def test_stores_of_the_generic_backward_against_measured_times(tangent, heads, rows, d, times):
+    (whole,), = ask([("rows", tangent, heads, rows, d)])
     assert times[whole] <= 1.02 * min(times)

@@ -109,3 +109,22 @@ def test_gO_alone_both_ways_to_store(H, M, N, d):
         a[wl.NAMES.index("gTO")] = np.zeros_like(a[wl.NAMES.index("gO")])
         for n, g, r in zip(pu.BWD_NAMES, out, orc.attn_jvp_bwd_head(*a, None)):
             assert pu.rel_err(g[0, h].float().cpu().numpy(), r) <= pu.TOL["bf16"], (h, n)
+
+
+@pytest.mark.parametrize("d", [104, 128])
+@pytest.mark.parametrize("H,M,N", [(2, 300, 40), (2, 40, 300), (130, 97, 33), (200, 33, 96), (3, 95, 64)])
+def test_tangent_and_a_short_other_side_both_ways_to_store(H, M, N, d):
+    """Head dims above 96 with 64 rows or fewer on one side: the generic-order kernel of the other side stores straight from the
+    accumulators or whole rows; both gradients and gTO alone, sampled heads against the oracle."""
+    w = dataclasses.replace(wl.custom(1, H, N, d, "bf16"), M=M)
+    print(f"[case] {w}", flush=True)
+    inp = wl.make_inputs(w, 19)
+    fwd, grads = pu.run_gpu(inp)
+    pu.check_heads(w, inp, fwd, grads, [(0, 0), (0, H - 1)])
+    dev = {n: t.cuda() for n, t in inp.items()}
+    alone = tvm.tvmattn_jvp_bwd(*[dev[n] for n in ("q", "k", "v", "tq", "tk", "tv")], *fwd, None, dev["gTO"])
+    for h in (0, H - 1):
+        a = [wl.to_f64(inp[n][0, h]) for n in wl.NAMES]
+        a[wl.NAMES.index("gO")] = np.zeros_like(a[wl.NAMES.index("gO")])
+        for n, g, r in zip(pu.BWD_NAMES, alone, orc.attn_jvp_bwd_head(*a, None)):
+            assert pu.rel_err(g[0, h].float().cpu().numpy(), r) <= pu.TOL["bf16"], (h, n)
