@@ -277,7 +277,11 @@ int tvmattn_jvp_fwd_qknorm(const tvmattn_desc* desc,
  * TVMATTN_UNSUPPORTED (and the size query 0): call tvmattn_jvp_bwd and tvmattn_qknorm_jvp_bwd one after the other
  * there.  Three launches (query side, key side, the ordered sum of per-workgroup gain-gradient rows); no atomics.
  * The gradients with respect to the normalised rows are rounded to dtype between the two steps, as they are when
- * the two calls are made separately.
+ * the two calls are made separately: the six tensors are bit for bit those of the two calls.
+ * With few rows, where tvmattn_jvp_bwd runs in parts (a workspace of the size asked for provided), this call does too, and
+ * the norm's backward follows as launches of its own.  A workspace of the three row vectors (12 bytes per query row) and one
+ * float32 row of D per 128 rows of a head on each side, every one of the five padded to 256 bytes, is accepted as well: the
+ * call then stays whole, and equals the two calls made with a workspace of the row vectors alone.
  */
 size_t tvmattn_jvp_bwd_qknorm_workspace_bytes(const tvmattn_desc* desc);
 int tvmattn_jvp_bwd_qknorm(const tvmattn_desc* desc,

@@ -444,6 +444,36 @@ size_t tvmattn_qknorm_jvp_bwd_workspace_bytes(const tvmattn_desc* desc) {
   return norm_part_bytes(a, 0) + norm_part_bytes(a, 1);  // one partial gain-gradient row per workgroup and side
 }
 
+namespace {
+// The norm's backward with checked arguments; partial gain gradients at `ws`
+hipError_t norm_bwd(const tvmattn_desc* desc, const tvm::Shape& s, float eps, const void* q, const void* tq, const void* k,
+                    const void* tk, const float* gain_q, const float* gain_k, const void* gqn, const void* gtqn, const void* gkn,
+                    const void* gtkn, void* dq, void* dtq, void* dk, void* dtk, float* dgain_q, float* dgain_k, char* ws,
+                    hipStream_t st) {
+  tvm::NormArgs a{};
+  norm_sides(s, &a, eps);
+  a.side[0].x = q;
+  a.side[0].tx = tq;
+  a.side[0].g = gain_q;
+  a.side[0].gy = gqn;
+  a.side[0].gty = gtqn;
+  a.side[0].y = dq;
+  a.side[0].ty = dtq;
+  a.side[0].gg = dgain_q;
+  a.side[0].part = reinterpret_cast<float*>(ws);
+  a.side[1].x = k;
+  a.side[1].tx = tk;
+  a.side[1].g = gain_k;
+  a.side[1].gy = gkn;
+  a.side[1].gty = gtkn;
+  a.side[1].y = dk;
+  a.side[1].ty = dtk;
+  a.side[1].gg = dgain_k;
+  a.side[1].part = reinterpret_cast<float*>(ws + norm_part_bytes(a, 0));
+  return tvm::launch_qknorm_bwd(a, desc->dtype, st);
+}
+}  // namespace
+
 int tvmattn_qknorm_jvp_bwd(const tvmattn_desc* desc, const void* q, const void* tq, const void* k, const void* tk,
                            const float* gain_q, const float* gain_k, float eps, const void* gqn, const void* gtqn,
                            const void* gkn, const void* gtkn, void* dq, void* dtq, void* dk, void* dtk,
@@ -462,27 +492,8 @@ int tvmattn_qknorm_jvp_bwd(const tvmattn_desc* desc, const void* q, const void* 
   rc = check_bufs(in, out);
   if (rc) return rc;
   if (workspace_bytes < need) return TVMATTN_WORKSPACE_TOO_SMALL;
-  tvm::NormArgs a{};
-  norm_sides(s, &a, eps);
-  a.side[0].x = q;
-  a.side[0].tx = tq;
-  a.side[0].g = gain_q;
-  a.side[0].gy = gqn;
-  a.side[0].gty = gtqn;
-  a.side[0].y = dq;
-  a.side[0].ty = dtq;
-  a.side[0].gg = dgain_q;
-  a.side[0].part = static_cast<float*>(workspace);
-  a.side[1].x = k;
-  a.side[1].tx = tk;
-  a.side[1].g = gain_k;
-  a.side[1].gy = gkn;
-  a.side[1].gty = gtkn;
-  a.side[1].y = dk;
-  a.side[1].ty = dtk;
-  a.side[1].gg = dgain_k;
-  a.side[1].part = reinterpret_cast<float*>(static_cast<char*>(workspace) + norm_part_bytes(a, 0));
-  const hipError_t e = tvm::launch_qknorm_bwd(a, desc->dtype, static_cast<hipStream_t>(hip_stream));
+  const hipError_t e = norm_bwd(desc, s, eps, q, tq, k, tk, gain_q, gain_k, gqn, gtqn, gkn, gtkn, dq, dtq, dk, dtk, dgain_q, dgain_k,
+                                static_cast<char*>(workspace), static_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? TVMATTN_OK : TVMATTN_LAUNCH_FAILED;
 }
 
@@ -496,12 +507,26 @@ size_t fused_part_bytes(const tvm::Shape& s, bool query_side) {  // one float32 
 bool fused_supported(const tvmattn_desc* d, const tvm::Shape& s) {
   return !plain_alu(d) && tvm::mfma_supported(s, d->dtype) && s.D <= 96;
 }
+// Workspace with the norm's backward in the epilogues: the row vectors, and the two sides' partial gain gradients
+size_t fused_bytes(const tvm::Shape& s) {
+  return 3 * row_vector_bytes(s) + fused_part_bytes(s, true) + fused_part_bytes(s, false);
+}
+// ... and where tvmattn_jvp_bwd cuts a streamed side into parts (0: it does not).  This call then does what the two calls do,
+// one after the other, with the gradients of the normalised rows in the outputs' place; the partial gain gradients take the
+// place of the partial gradients, which are added up by then.  Bit for bit the two calls' results, as everywhere, and
+// the parts are ahead of the epilogues that they give up (us, whole with epilogues / in parts): one head of 1024, d = 64
+// 75 / 44, eight 77 / 70, twelve 81 / 81; one head of 4096 215 / 78, four 221 / 185; eight heads of 2048, d = 96 156 / 158.
+size_t fused_cut_bytes(const tvmattn_desc* desc, const tvm::Shape& s) {
+  const size_t part = part_bytes(desc, s), gain = tvmattn_qknorm_jvp_bwd_workspace_bytes(desc);
+  return part == 0 ? 0 : 3 * row_vector_bytes(s) + (part > gain ? part : gain);
+}
 }  // namespace
 
 size_t tvmattn_jvp_bwd_qknorm_workspace_bytes(const tvmattn_desc* desc) {
   tvm::Shape s;
   if (resolve(desc, &s) || !fused_supported(desc, s)) return 0;
-  return 3 * row_vector_bytes(s) + fused_part_bytes(s, true) + fused_part_bytes(s, false);
+  const size_t whole = fused_bytes(s), cut = fused_cut_bytes(desc, s);
+  return whole > cut ? whole : cut;
 }
 
 int tvmattn_jvp_bwd_qknorm(const tvmattn_desc* desc, const void* q, const void* tq, const void* k, const void* tk,
@@ -516,7 +541,10 @@ int tvmattn_jvp_bwd_qknorm(const tvmattn_desc* desc, const void* q, const void* 
   if (!(eps >= 0.f) || isinf(eps)) return TVMATTN_INVALID_ARG;
   if (!fused_supported(desc, s)) return TVMATTN_UNSUPPORTED;
   const long long esz = esz_of(desc->dtype), gb = (long long)s.D * 4, rvb = (long long)s.B * s.H * s.M * 4;
-  const size_t need = tvmattn_jvp_bwd_qknorm_workspace_bytes(desc);
+  // (a workspace that holds the row vectors and the gain gradients alone serves too: the streamed sides then stay whole)
+  const size_t cut_bytes = fused_cut_bytes(desc, s);
+  const bool cut = cut_bytes != 0 && workspace_bytes >= cut_bytes;
+  const size_t need = cut ? cut_bytes : fused_bytes(s);
   auto qs = [&](const void* p) { return side_buf(p, s, true, esz); };
   auto ks = [&](const void* p) { return side_buf(p, s, false, esz); };
   const Buf in[] = {qs(q),  qs(tq), ks(k), ks(tk), plain(gain_q, gb), plain(gain_k, gb), qs(qn),  qs(tqn),          ks(kn),
@@ -531,6 +559,16 @@ int tvmattn_jvp_bwd_qknorm(const tvmattn_desc* desc, const void* q, const void* 
   tvm::BwdArgs a{qn, kn, v, tqn, tkn, tv, o, to, lse, stats, gO, gTO, dq, dk, dv, dtq, dtk, dtv,
                  reinterpret_cast<float*>(ws), reinterpret_cast<float*>(ws + need0 / 3),
                  reinterpret_cast<float*>(ws + 2 * (need0 / 3)), 0};
+  hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  if (cut) {
+    a.part = reinterpret_cast<float*>(ws + need0);
+    if (tvm::launch_bwd_row_mfma(s, a, st) != hipSuccess) return TVMATTN_LAUNCH_FAILED;
+    if (tvm::launch_bwd_col_mfma(s, a, st) != hipSuccess) return TVMATTN_LAUNCH_FAILED;
+    // in place: a thread reads its 16 bytes of a row before it writes the same 16 bytes, and nobody else touches them
+    const hipError_t e = norm_bwd(desc, s, eps, q, tq, k, tk, gain_q, gain_k, dq, dtq, dk, dtk, dq, dtq, dk, dtk, dgain_q, dgain_k,
+                                  ws + need0, st);
+    return e == hipSuccess ? TVMATTN_OK : TVMATTN_LAUNCH_FAILED;
+  }
   a.nq = q;
   a.ntq = tq;
   a.nk = k;
@@ -540,7 +578,6 @@ int tvmattn_jvp_bwd_qknorm(const tvmattn_desc* desc, const void* q, const void* 
   a.neps = eps;
   a.npart_q = reinterpret_cast<float*>(ws + need0);
   a.npart_k = reinterpret_cast<float*>(ws + need0 + fused_part_bytes(s, true));
-  hipStream_t st = static_cast<hipStream_t>(hip_stream);
   if (tvm::launch_bwd_row_pipe_qknorm(s, a, st) != hipSuccess) return TVMATTN_LAUNCH_FAILED;
   if (tvm::launch_bwd_col_pipe_qknorm(s, a, st) != hipSuccess) return TVMATTN_LAUNCH_FAILED;
   const int rows_q = ((s.M + 127) / 128) * s.B * s.H, rows_k = ((s.N + 127) / 128) * s.B * s.H;

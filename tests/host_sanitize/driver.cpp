@@ -153,6 +153,25 @@ int main() {
                                 P(9 * G), P(10 * G), P(11 * G), P(12 * G), (float*)P(13 * G), (float*)P(14 * G), P(15 * G),
                                 P(16 * G), P(17 * G), P(18 * G), P(19 * G), P(22 * G), P(23 * G), P(24 * G), (float*)P(25 * G),
                                 (float*)P(26 * G), P(27 * G), nf, nullptr) == TVMATTN_OK);
+  // few rows: the attention's backward in parts, then the norm's; a workspace of the epilogues' size is served too
+  {
+    tvmattn_desc few = mk(1, 2, 2048, 72);
+    const size_t rows = 3u * 2 * 2048 * 4, whole = rows + 2u * 2 * 16 * 72 * 4;
+    const size_t asked = tvmattn_jvp_bwd_qknorm_workspace_bytes(&few);
+    EXPECT(asked > whole && asked >= tvmattn_jvp_bwd_workspace_bytes(&few) && tvmattn_jvp_bwd_workspace_bytes(&few) > rows);
+    auto call = [&](uint64_t ws, size_t bytes) {
+      return tvmattn_jvp_bwd_qknorm(&few, P(G), P(2 * G), P(3 * G), P(4 * G), gq, gk, 1e-6f, P(5 * G), P(6 * G), P(7 * G), P(8 * G),
+                                    P(9 * G), P(10 * G), P(11 * G), P(12 * G), (float*)P(13 * G), (float*)P(14 * G), P(15 * G),
+                                    P(16 * G), P(17 * G), P(18 * G), P(19 * G), P(22 * G), P(23 * G), P(24 * G), (float*)P(25 * G),
+                                    (float*)P(26 * G), P(ws), bytes, nullptr);
+    };
+    EXPECT(call(27 * G, asked) == TVMATTN_OK);
+    EXPECT(call(27 * G, asked - 1) == TVMATTN_OK);   // whole
+    EXPECT(call(27 * G, whole) == TVMATTN_OK);
+    EXPECT(call(27 * G, whole - 1) == TVMATTN_WORKSPACE_TOO_SMALL);
+    EXPECT(call(17 * G - whole, whole) == TVMATTN_OK);          // right in front of dq ...
+    EXPECT(call(17 * G - whole, asked) == TVMATTN_INVALID_ARG); // ... where a workspace of the asked size would reach into it
+  }
   tvmattn_desc wide = mk(1, 1, 64, 128);
   EXPECT(tvmattn_jvp_bwd_qknorm_workspace_bytes(&wide) == 0);
   const int B = 4, T = 100, C = 1152;

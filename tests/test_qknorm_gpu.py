@@ -222,6 +222,70 @@ def test_fused_backward_against_the_oracle_chain_and_the_two_calls(B, H, M, N, d
         assert pu.rel_err(got.cpu().numpy(), r) <= pu.TOL["bf16"], name
 
 
+@pytest.mark.parametrize("B,H,M,N,d", [
+    (1, 1, 1024, 1024, 64), (1, 2, 1100, 1300, 72), (1, 3, 40, 1100, 32), (2, 1, 1537, 33, 96), (1, 2, 2049, 64, 8),
+    (1, 8, 1024, 1024, 72),
+])
+def test_fused_backward_in_parts_is_the_two_calls(B, H, M, N, d):
+    """Few rows, where the attention's backward runs in parts over one side or both: the fused call's eight results are bit for
+    bit those of the two calls (strided outputs too), and with a workspace of the epilogues' size alone its six tensors those
+    of the two calls that stay whole; against the oracle chain either way."""
+    announce(f"fused attention + qknorm backward in parts B{B} H{H} M{M} N{N} d{d}")
+    inp, gains, chained, fused = fused_and_chained(B, H, M, N, d, 75)
+    for name, a, b in zip(FUSED_NAMES, chained, fused):
+        assert torch.equal(a, b), name
+    dev = {n: t.cuda() for n, t in inp.items()}
+    gq, gk = gains[0].cuda(), gains[1].cuda()
+    raw = (dev["q"], dev["tq"], dev["k"], dev["tk"], gq, gk, EPS)
+    n4 = tvm.tvmattn_qknorm_jvp_fwd(*raw)
+    six = (n4[0], n4[2], dev["v"], n4[1], n4[3], dev["tv"])
+    f4 = tvm.tvmattn_jvp_fwd(*six)
+    args = (*raw, *n4, dev["v"], dev["tv"], *f4, dev["gO"], dev["gTO"])
+    pad = lambda n: (n + 255) // 256 * 256
+    rows = 3 * pad(B * H * M * 4)
+    assert tvm.tvmattn_jvp_bwd_workspace_bytes(dev["q"], k=dev["k"]) > rows   # the call is one that runs in parts
+    small = rows + sum(pad(-(-n // 128) * B * H * d * 4) for n in (M, N))
+    assert tvm.tvmattn_jvp_bwd_qknorm_workspace_bytes(dev["q"], dev["k"]) > small
+    ws = lambda n: torch.empty(n, dtype=torch.uint8, device="cuda")
+    whole = tvm.tvmattn_jvp_bwd_qknorm(*args, workspace=ws(small))
+    g = tvm.tvmattn_jvp_bwd(*six, *f4, dev["gO"], dev["gTO"], workspace=ws(rows))
+    r = tvm.tvmattn_qknorm_jvp_bwd(*raw, g[0], g[3], g[1], g[4])
+    for name, a, b in zip(FUSED_NAMES[:6], (r[0], r[2], g[2], r[1], r[3], g[5]), whole):
+        assert torch.equal(a, b), name
+    with pytest.raises(tvm.TvmattnError) as ei:
+        tvm.tvmattn_jvp_bwd_qknorm(*args, workspace=ws(small - 1))
+    assert ei.value.status == -3
+    # outputs in the slices of one [B,n,3,H,d] buffer (self-attention), inputs laid out the same
+    if M == N:
+        def sliced(*ts):
+            buf = torch.empty(B, M, 3, H, d, dtype=torch.bfloat16, device="cuda")
+            views = [buf[:, :, i].permute(0, 2, 1, 3) for i in range(3)]
+            for t, v in zip(ts, views):
+                v.copy_(t)
+            return views
+        e = torch.zeros_like(dev["q"])
+        (sq, sk, sv), (stq, stk, stv), (so, sto, _) = sliced(dev["q"], dev["k"], dev["v"]), sliced(dev["tq"], dev["tk"], dev["tv"]), sliced(f4[0], f4[1], e)
+        (sqn, skn, _), (stqn, stkn, _), (sgO, sgTO, _) = sliced(n4[0], n4[2], e), sliced(n4[1], n4[3], e), sliced(dev["gO"], dev["gTO"], e)
+        o1, o2 = sliced(e, e, e), sliced(e, e, e)
+        got = tvm.tvmattn_jvp_bwd_qknorm(sq, stq, sk, stk, gq, gk, EPS, sqn, stqn, skn, stkn, sv, stv, so, sto, f4[2], f4[3], sgO, sgTO,
+                                         out=(o1[0], o1[1], o1[2], o2[0], o2[1], o2[2], torch.empty_like(gq), torch.empty_like(gk)))
+        for name, a, b in zip(FUSED_NAMES, fused, got):
+            assert torch.equal(a, b), name
+    gsum = [np.zeros(d), np.zeros(d)]
+    for b in range(B):
+        for h in range(H):
+            ref, rg = oracle_chain(inp, gains, b, h)
+            for res in (fused, whole):
+                for name, got, t in zip(FUSED_NAMES[:6], res, ref):
+                    e = pu.rel_err(got[b, h].float().cpu().numpy(), t)
+                    assert e <= pu.TOL["bf16"], (name, b, h, e)
+            gsum[0] += rg[0]
+            gsum[1] += rg[1]
+    for res in (fused, whole):
+        for name, got, t in zip(FUSED_NAMES[6:], res[6:], gsum):
+            assert pu.rel_err(got.cpu().numpy(), t) <= pu.TOL["bf16"], name
+
+
 def test_fused_backward_full_size():
     """C4 in the launch configuration bench.py times: bitwise against the two separate calls for the tensors,
     sampled heads against the oracle chain."""
