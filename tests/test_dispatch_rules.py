@@ -1,8 +1,11 @@
 """The rules that choose kernels and cut work, evaluated on the host (tests/dispatch_rules.py)."""
+import os
 import random
 
 import pytest
 
+from paper_2511_19797_amd import binding, build as tvm_build
+from tests import dispatch_cases as dc
 from tests.dispatch_rules import ask
 
 MAX_ROWS = 2 ** 31 - 1   # the largest row count a descriptor may name
@@ -123,3 +126,38 @@ MEASURED_STORES_TANGENT = [
 def test_stores_of_the_generic_backward_against_measured_times(tangent, heads, rows, d, times):
     (whole,), = ask([("rows", tangent, heads, rows, d)])
     assert times[whole] <= 1.02 * min(times)
+
+
+# ---------------------------------------------------------------- the sizes of the GPU tests are where they claim to be
+@pytest.mark.parametrize("shape,tiles,parts", dc.LINEAR)
+def test_linear_cases(shape, tiles, parts):
+    R, K, F = shape
+    (y, gx, gw, splits), = ask([("linear", *shape)])
+    assert tuple((256, 192, 128, 64)[c] for c in (y, gx, gw)) == tiles
+    assert (splits > 1 or gw < 2) == parts   # (the 128 and 64 tiles of one split write gW themselves)
+
+
+def test_linear_cases_are_ragged_everywhere():
+    for product, contraction, column in (("y", 1, 2), ("gx", 2, 1), ("gw", 0, 1)):
+        for tile in (256, 192, 128, 64):
+            assert any(t[("y", "gx", "gw").index(product)] == tile and s[contraction] % 64 != 0 and s[column] % tile != 0 and s[column] > tile
+                       for s, t, _ in dc.LINEAR), (product, tile)
+
+
+def test_forward_cases():
+    eight = [(c, d) for c in dc.FORWARD_EIGHT_WAVES for d in dc.FORWARD_EIGHT_WAVES_DIMS]
+    four = [(c, d) for c in dc.FORWARD_FOUR_WAVES for d in dc.FORWARD_FOUR_WAVES_DIMS]
+    four += [(c, d) for c in dc.FORWARD_FOUR_WAVES_WIDE for d in (104, 128)]
+    for cases in (eight, four):
+        assert set(ask([("fwd_few", *c, d) for c, d in cases])) == {(0,)}
+    assert all(M > 128 and N >= 512 and d <= 96 for (_, M, N), d in eight)
+    assert all(N >= 128 and (N < 512 or M <= 128 or d > 96) for (_, M, N), d in four)
+    assert [bool(a) for a, in ask([("fwd_few", *c[:4]) for c in dc.FORWARD_LINES])] == [c[4] for c in dc.FORWARD_LINES]
+
+
+@pytest.mark.parametrize("B,T,C,dtype", dc.GATE_MANY_ROWS)
+def test_gate_cases(B, T, C, dtype):
+    if not os.path.exists(binding.LIB_PATH):
+        tvm_build.build()
+    need = binding.lib().tvmattn_gate_jvp_bwd_workspace_bytes(B, T, C, {"f32": binding.TVMATTN_F32, "bf16": binding.TVMATTN_BF16}[dtype])
+    assert need > 32 * B * 2 * C * 4 + 255

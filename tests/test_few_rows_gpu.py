@@ -11,6 +11,7 @@ import torch
 import paper_2511_19797_amd as tvm
 from oracle import tvmattn_oracle as orc
 from paper_2511_19797_amd import workloads as wl
+from tests import dispatch_cases as dc
 from tests import parity_util as pu
 
 pytestmark = pytest.mark.gpu
@@ -28,6 +29,19 @@ def test_against_oracle(M, N, d):
     inp = wl.make_inputs(w, 100 + d)
     fwd, grads = pu.run_gpu(inp)
     pu.check_heads(w, inp, fwd, grads, pu.all_heads(w))
+
+
+@pytest.mark.parametrize("H,M,N,d,few", dc.FORWARD_LINES)
+def test_forward_on_both_sides_of_the_lines(H, M, N, d, few):
+    """The last block count that the forward for few rows takes and the first that it leaves: sampled heads against the oracle."""
+    w = dataclasses.replace(wl.custom(1, H, N, d, "bf16"), M=M)
+    print(f"[case] {w} few={few}", flush=True)
+    inp = wl.make_inputs(w, 21)
+    fwd = tvm.tvmattn_jvp_fwd(*[inp[n].cuda() for n in ("q", "k", "v", "tq", "tk", "tv")])
+    for h in (0, H - 1):
+        ref = orc.attn_jvp_fwd_head(*[wl.to_f64(inp[n][0, h]) for n in wl.NAMES[:6]], None)
+        for n, g, r in zip(pu.FWD_NAMES, fwd, ref):
+            assert pu.rel_err(g[0, h].float().cpu().numpy(), r) <= pu.TOL["bf16"], (h, n)
 
 
 @pytest.mark.parametrize("d", [64, 72, 128])

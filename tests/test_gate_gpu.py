@@ -9,6 +9,7 @@ import torch
 import paper_2511_19797_amd as tvm
 from oracle import gate_oracle as orc
 from paper_2511_19797_amd import workloads as wl
+from tests import dispatch_cases as dc
 from tests import parity_util as pu
 
 pytestmark = pytest.mark.gpu
@@ -52,6 +53,19 @@ def test_every_element_against_the_oracle(B, T, C, dtype):
     fwd, grads = run(inp)
     worst = check(inp, fwd, grads, dtype)
     print("   worst rel err:", {k: f"{v:.2e}" for k, v in worst.items()}, flush=True)
+
+
+@pytest.mark.parametrize("B,T,C,dtype", dc.GATE_MANY_ROWS)
+def test_many_partial_rows_are_added_first(B, T, C, dtype):
+    """Small batches of many tokens: a kernel of its own adds each element's partial rows into the first of them.  Every
+    element against the oracle, and two runs agree bit for bit."""
+    announce(f"gate B{B} T{T} C{C} {dtype}")
+    inp = wl.make_gate_inputs(B, T, C, dtype, 96)
+    fwd, grads = run(inp)
+    check(inp, fwd, grads, dtype)
+    fwd2, grads2 = run(inp)
+    for a, b in zip(list(fwd) + list(grads), list(fwd2) + list(grads2)):
+        assert torch.equal(a, b)
 
 
 def test_full_size_and_reproducible():

@@ -9,6 +9,7 @@ import torch
 import paper_2511_19797_amd as tvm
 from oracle import linear_oracle as orc
 from paper_2511_19797_amd import workloads as wl
+from tests import dispatch_cases as dc
 from tests import parity_util as pu
 
 pytestmark = pytest.mark.gpu
@@ -131,14 +132,20 @@ def test_unsupported_shapes_are_refused():
 
 @pytest.mark.parametrize("R,K,F", [
     (64, 64, 64), (65, 96, 192), (1, 64, 2304),   # 64 x 64 tiles: one tile, one row over, contraction of 1.5 tiles
-    (127, 544, 160),      # ... with more contraction tiles than stages, ragged on every side
-    (160, 160, 4608), (1024, 3072, 768),          # 128 x 128 tiles: fewer contraction tiles than stages, many
-    (1000, 768, 3072), (1031, 1152, 1120),        # ... and a weight gradient of one split, of several
-    (2048, 1152, 1184), (4095, 4608, 384),        # 256 x 192 tiles: a ragged last column tile, a ragged last row
+    (127, 544, 160), (160, 160, 4608),            # ... with more contraction tiles than stages, ragged on every side
+    (1024, 3072, 768), (1000, 768, 3072),         # 64 and 256 x 192, and a weight gradient of 128 x 128 tiles in one split
+    (1031, 1152, 1120), (2048, 1152, 1184),       # 128 x 128, 256 x 192: ragged last rows and columns
+    (4095, 4608, 384),                            # 128 x 128 (y), 256 x 192 (grad x), 256 x 256 (grad W)
 ])
 def test_linear_tile_shapes(R, K, F):
     """Sizes at the edges of the tile shapes between which the layer's products choose."""
     run(R, K, F, seed=3 + R % 7)
+
+
+@pytest.mark.parametrize("shape", [c[0] for c in dc.LINEAR])
+def test_linear_every_tile_of_every_product(shape):
+    """Every tile shape of y, grad x and grad W, ragged in rows, columns and contraction."""
+    run(*shape, seed=5 + shape[0] % 7)
 
 
 @pytest.mark.parametrize("R", [1, 127, 128, 129, 511, 513, 2048, 2049])

@@ -1,5 +1,6 @@
 """GPU-vs-oracle parity through the C-ABI (ctypes binding).  Every case prints its name
 before touching the GPU so a failing run names its case."""
+import dataclasses
 import sys
 
 import numpy as np
@@ -8,6 +9,7 @@ import torch
 
 import paper_2511_19797_amd as tvm
 from paper_2511_19797_amd import workloads as wl
+from tests import dispatch_cases as dc
 from tests import parity_util as pu
 
 pytestmark = pytest.mark.gpu
@@ -27,7 +29,7 @@ def run_case(w, seed, heads=None, scale=0.0, force_generic=False):
     return inp, fwd, grads
 
 
-# ---------------------------------------------------------------- float32 (plain-ALU kernels)
+# ---------------------------------------------------------------- float32 (matrix cores: d a multiple of 4 up to 128)
 def test_c1_f32_tiny():
     run_case(wl.CONFIGS["C1"], seed=1)
 
@@ -35,6 +37,31 @@ def test_c1_f32_tiny():
 @pytest.mark.parametrize("B,H,N,d", [(2, 3, 77, 40), (1, 2, 1, 8), (1, 1, 130, 256), (1, 2, 64, 4), (2, 1, 200, 72)])
 def test_f32_ragged_shapes(B, H, N, d):
     run_case(wl.custom(B, H, N, d, "f32"), seed=2)
+
+
+@pytest.mark.parametrize("B,H,N,d", [(2, 3, 77, 40), (1, 2, 130, 64), (1, 1, 1, 8), (1, 2, 65, 128), (1, 1, 33, 4)])
+def test_f32_plain_kernels(B, H, N, d):
+    """The plain-ALU kernels on head dims that the matrix cores take."""
+    run_case(wl.custom(B, H, N, d, "f32"), seed=2, force_generic=True)
+
+
+@pytest.mark.parametrize("d,width", [(26, 28), (3, 4), (30, 64), (127, 128)])
+def test_f32_head_dims_that_are_no_multiple_of_four(d, width):
+    """Rows of d columns inside rows of `width` (row pitches are 16-byte multiples): the plain-ALU kernels, which leave the
+    columns between alone."""
+    w = dataclasses.replace(wl.custom(2, 2, 90, d, "f32"), M=70)
+    announce(f"f32 d={d} in rows of {width}")
+    inp = wl.make_inputs(w, 16)
+    wide = {n: torch.full((*t.shape[:3], width), float("nan"), device="cuda") for n, t in inp.items()}
+    dev = {n: t[..., :d] for n, t in wide.items()}
+    for n, t in inp.items():
+        dev[n].copy_(t)
+    o, to, lse, stats = tvm.tvmattn_jvp_fwd(*(dev[n] for n in wl.NAMES[:6]))
+    room = [torch.full((2, 2, 70 if q else 90, width), float("nan"), device="cuda") for q in (1, 0, 0, 1, 0, 0)]
+    grads = tvm.tvmattn_jvp_bwd(*(dev[n] for n in wl.NAMES[:6]), o, to, lse, stats, dev["gO"], dev["gTO"], out=tuple(r[..., :d] for r in room))
+    torch.cuda.synchronize()
+    assert all(bool(torch.isnan(r[..., d:]).all()) for r in room)
+    pu.check_heads(w, inp, (o, to, lse, stats), grads, pu.all_heads(w))
 
 
 def test_f32_explicit_scale():
@@ -92,15 +119,30 @@ def test_bf16_hand_scheduled_passes_tile_boundaries(d):
 @pytest.mark.parametrize("d", [8, 24, 40, 64, 72, 96])
 def test_bf16_wide_forward_workgroups(d):
     """From 512 keys on (head dims up to 96, more than 128 queries) the forward runs eight-wave workgroups of 256
-    query rows.  Every instantiation of it (one per padded head dim), with a whole and a ragged last key block,
-    with workgroups whose upper waves hold no query row (M = 257, 300), and with M != N either way round: every
-    element of all ten outputs against the oracle."""
+    query rows, unless there are few blocks of rows: with one or two heads these lengths go to the forward for few
+    rows (fwd_few.hip), here with a whole and a ragged last key tile and M != N either way round, every element of
+    all ten outputs against the oracle.  The eight-wave workgroups themselves: the next test."""
     import dataclasses
     for N in (512, 513, 543, 1000):
         run_case(wl.custom(1, 2 if N == 512 else 1, N, d, "bf16"), seed=60 + N % 11)
     for M, N in ((257, 512), (300, 543), (700, 600), (600, 700)):
         w = dataclasses.replace(wl.custom(1, 1, N, d, "bf16"), M=M)
         run_case(w, seed=70 + M % 13)
+
+
+@pytest.mark.parametrize("d", dc.FORWARD_EIGHT_WAVES_DIMS)
+@pytest.mark.parametrize("H,M,N", dc.FORWARD_EIGHT_WAVES)
+def test_bf16_forward_eight_wave_workgroups(H, M, N, d):
+    """Every instantiation of the eight-wave forward (one per padded head dim), ragged in rows and keys: enough heads that no
+    call is one of few rows; sampled heads of all ten outputs against the oracle."""
+    run_case(dataclasses.replace(wl.custom(1, H, N, d, "bf16"), M=M), seed=80 + N % 11, heads=[(0, 0), (0, H - 1)])
+
+
+@pytest.mark.parametrize("H,M,N,d", [(*c, d) for c in dc.FORWARD_FOUR_WAVES for d in dc.FORWARD_FOUR_WAVES_DIMS] +
+                         [(*c, d) for c in dc.FORWARD_FOUR_WAVES_WIDE for d in (104, 128)])
+def test_bf16_forward_four_wave_workgroups(H, M, N, d):
+    """The same for the four-wave workgroups of 128 rows from 128 keys on."""
+    run_case(dataclasses.replace(wl.custom(1, H, N, d, "bf16"), M=M), seed=90 + N % 11, heads=[(0, 0), (0, H // 2), (0, H - 1)])
 
 
 def test_inputs_sliced_from_a_fused_projection():
