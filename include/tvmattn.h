@@ -72,7 +72,8 @@ typedef enum {
 /* Per-call switches, OR-ed into tvmattn_desc.flags.  Unknown bits are TVMATTN_INVALID_ARG. */
 enum {
   /* Diagnostic: serve this call with the plain-ALU kernels even where the matrix-core kernels would take it
-   * (bf16 with D a multiple of 8, float32 with D a multiple of 4, D <= 128).  Both families compute the operation stated above. */
+   * (bf16 with D a multiple of 8, float32 with D a multiple of 4 and more than a handful of rows, D <= 128).  Both families
+   * compute the operation stated above. */
   TVMATTN_FLAG_PLAIN_ALU = 1
 };
 
@@ -116,7 +117,8 @@ int tvmattn_jvp_fwd(const tvmattn_desc* desc,
 
 /* Bytes of device scratch tvmattn_jvp_bwd needs for this descriptor (0 on a bad descriptor).  Three float32 row vectors
  * (12 bytes per query row) and, for bf16 calls with few rows and a long other side, float32 partial gradients (48 MiB at
- * most).  A workspace that holds the row vectors alone is accepted too: such calls then leave most of the GPU idle. */
+ * most).  A workspace that holds the row vectors alone, each padded to 256 bytes, is accepted too: such calls then leave most of
+ * the GPU idle. */
 size_t tvmattn_jvp_bwd_workspace_bytes(const tvmattn_desc* desc);
 
 /*
@@ -173,8 +175,8 @@ int tvmattn_jvp_bwd_timed(const tvmattn_desc* desc,
  * tvmattn_jvp_bwd for callers that cannot allocate device memory or carry a workspace (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): same arguments without the workspace, same
  * kernels, same results bit for bit.  What the workspace otherwise holds, the three float32 row vectors and the
- * partial gradients, lives in a static device array of 3 * TVMATTN_STATIC_MAX_ROWS floats and 48 MiB (60 MiB on every
- * GPU the library runs on, held until the process ends).  The call allocates nothing and frees nothing.
+ * partial gradients, lives in a static device array of 3 * TVMATTN_STATIC_MAX_ROWS floats and 48 MiB (60 MiB on each
+ * GPU this function is called on, from the first call until the process ends).  The call allocates nothing and frees nothing.
  *   - B*H*M (query rows) above TVMATTN_STATIC_MAX_ROWS: TVMATTN_SCRATCH_TOO_SMALL, nothing enqueued.
  *   - The device that is current at the call must be the one hip_stream belongs to; each GPU has its own array.
  *   - Every call on a GPU shares that GPU's array: calls that may overlap in time on one GPU (different streams,
@@ -323,7 +325,7 @@ int tvmattn_adaln_jvp_fwd(int B, int T, int C, int dtype,
  *   out: gx, gtx [B,T,C] dtype; ga, gta, gb, gtb [B,C] float32 (summed over the T tokens of their batch element)
  *   workspace: device memory, 16-byte aligned, at least tvmattn_adaln_jvp_bwd_workspace_bytes(...) bytes
  *              (0 = unsupported shape).
- * Two launches; the sums over tokens use no atomics and are bitwise reproducible.
+ * Two launches, three with many tokens per batch element; the sums over tokens use no atomics and are bitwise reproducible.
  */
 size_t tvmattn_adaln_jvp_bwd_workspace_bytes(int B, int T, int C, int dtype);
 int tvmattn_adaln_jvp_bwd(int B, int T, int C, int dtype,
@@ -372,7 +374,7 @@ int tvmattn_gate_jvp_fwd(int B, int T, int C, int dtype,
  *   out: gh, gth [B,T,C] dtype; gc, gtc [B,C] float32 (summed over the T tokens of their batch element)
  *   workspace: device memory, 16-byte aligned, at least tvmattn_gate_jvp_bwd_workspace_bytes(...) bytes
  *              (0 = unsupported shape).
- * Two launches; the sums over tokens use no atomics and are bitwise reproducible.
+ * Two launches, three with many tokens and a small batch; the sums over tokens use no atomics and are bitwise reproducible.
  */
 size_t tvmattn_gate_jvp_bwd_workspace_bytes(int B, int T, int C, int dtype);
 int tvmattn_gate_jvp_bwd(int B, int T, int C, int dtype,
@@ -431,7 +433,7 @@ int tvmattn_linear_jvp_fwd(int R, int K, int F, int dtype,
  *   workspace: device memory, 16-byte aligned, at least tvmattn_linear_jvp_bwd_workspace_bytes(...) bytes (0 =
  *              unsupported shape): float32 partial sums of gw over ranges of tokens, and of gbias.
  * Launches: gx and gtx in one; gw as partial sums over token ranges and their sum in a fixed order (no atomics,
- * bitwise reproducible); gbias likewise.
+ * bitwise reproducible), or in one launch where one range fills the chip; gbias likewise, in one launch up to 2048 tokens.
  */
 size_t tvmattn_linear_jvp_bwd_workspace_bytes(int R, int K, int F, int dtype);
 int tvmattn_linear_jvp_bwd(int R, int K, int F, int dtype,

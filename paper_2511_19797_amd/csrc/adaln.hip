@@ -617,8 +617,8 @@ int adaln_wgs(int B, int T, bool backward, bool gate) {
   const int total = !backward ? ADALN_TF : gate ? GATE_TB : ADALN_TB;
   const int groups = (T + R - 1) / R, cap = total / B > 1 ? total / B : 1;
   int passes = (groups + cap - 1) / cap;
-  // Small batches: up to four passes per workgroup of the gate's backward where that still leaves 32 workgroups per
-  // element.  The tail kernel walks the partial rows with one workgroup per batch element (a fifth of a microsecond per
+  // Small batches: up to four passes per workgroup of the gate's backward, as many as it takes to come down to 32 workgroups
+  // per element (17 to 32 of them up to 128 groups of rows, a quarter of the groups beyond).  The tail kernel walks the partial rows with one workgroup per batch element (a fifth of a microsecond per
   // row, against a microsecond per pass here): 2 x 250 tokens x 768, 4.5 + 22 us with 125 rows each, 6.4 + 8.6 us with 32.
   if (backward && gate) passes = std::max(passes, std::min(4, (groups + kGateRowsDirect - 1) / kGateRowsDirect));
   return (groups + passes - 1) / passes;

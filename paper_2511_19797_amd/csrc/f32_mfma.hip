@@ -1,6 +1,6 @@
 // float32 attention with tangent on the float32 matrix cores (v_mfma_f32_16x16x4_f32: full float32 operands, products
-// and sums).  Head dims that are multiples of 4 up to 128, both sequence lengths arbitrary; what it does not take runs
-// on the plain-ALU kernels (generic_kernels.hip), whose formulas these kernels share.
+// and sums).  Head dims that are multiples of 4 up to 128, but for calls of a handful of rows (f32_mfma.h says which); what it
+// does not take runs on the plain-ALU kernels (generic_kernels.hip), whose formulas these kernels share.
 //
 // What bounds it: the float32 matrix rate (157 TFLOP/s, a sixteenth of the bf16 one), so operand traffic is cheap by
 // comparison and nothing of the streamed side goes through LDS.  A workgroup owns 16 rows of the fixed side (queries

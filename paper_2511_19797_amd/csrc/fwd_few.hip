@@ -8,8 +8,8 @@
 // per 256.  A wave fetches its own tiles (no barrier in the loop) into one stage: the fragments of K, tK are read to
 // registers first and the next tile's K, tK requested behind them, those of V, tV likewise, so that each half of the stage
 // has the other half's work to land behind.
-// Bound by the products and the softmax of one wave per SIMD.  One head of 4096, d = 64 (128 workgroups): 135 us on 16 workgroups
-// of fwd_mfma.hip, 31 us here (210 TFLOP/s on half of the CUs).
+// Bound by the products and the softmax of one wave per SIMD.  One head of 4096, d = 64 (128 workgroups): 136 us on 16 workgroups
+// of fwd_mfma.hip, 32 us here (200 TFLOP/s on half of the CUs).
 #include "fwd_few.h"
 #include "mfma_tiles.h"
 

@@ -305,8 +305,10 @@ int tvmattn_jvp_bwd(const tvmattn_desc* desc, const void* q, const void* k, cons
 // ---- the same backward for callers that cannot allocate: the row vectors live in a static device array
 namespace {
 constexpr long long kStaticMaxRows = TVMATTN_STATIC_MAX_ROWS;  // query rows B*H*M served by the static scratch
-// Three row vectors of kStaticMaxRows floats each (60 MiB in all per GPU the library runs on, held until the process ends).
-// Behind them the partial gradients of a cut streamed side (48 MiB at most, bwd_part_bytes).
+// Three row vectors of kStaticMaxRows floats each, and behind them the partial gradients of a cut streamed side (48 MiB at
+// most, bwd_part_bytes): 60 MiB on each GPU this entry point is called on, from the first call until the process ends.  (The
+// array is in this translation unit's code object, which holds no kernel: hipGetSymbolAddress below loads it.  Free memory
+// before and after: 62 MiB go with the first call; forward, backward and a linear layer before it took 8, code and tensors.)
 static __device__ __align__(256) float scratch[3 * kStaticMaxRows + tvm::kBwdPartMax / sizeof(float)];
 constexpr int kMaxDevices = 64;
 float* g_scratch_ptr[kMaxDevices];         // device address of `scratch` on each GPU (its name is no device address)
