@@ -12,16 +12,8 @@
 // both sets.  Everything is computed transposed, D = Q-fragment x P-fragment, so that a lane owns one output ROW
 // (32 per 32x32 block) and 16 of its columns: results leave through LDS as whole rows (store_tile_coalesced).
 //
-// Four tile shapes (chosen by pick_shape and plan_dw, linear_plan.h): 256 x 256 and 256 x 192 here, 128 x 128 and 64 x 64 in
-// gemm_small_kernel.  Workgroup: eight waves as 2 x 4 (two per SIMD), each with 4 x 2 blocks of 32 x 32 (128 accumulator
-// registers), or as 4 x 2 with 2 x 3 blocks: a 256 x 256 or 256 x 192 output tile (128 flop per byte staged: smaller tiles are bound by L2->LDS traffic), contraction in
-// tiles of 64 through two LDS stages filled by asynchronous global->LDS loads (mfma_tiles.h: the same swizzled
-// row-major tiles as the attention kernels; "row" fragments are 16-byte reads, "transposed" ones the transposing LDS
-// read, here with the contraction index in natural order so that both kinds pair up).  Per contraction step of 16
-// a wave reads 4 + 2 fragments for 8 products (2 + 3 for 6), a step ahead of the products that use them.  Workgroups are
-// persistent, one per CU: each walks a list of output tiles in an order that keeps an XCD's workgroups on one patch
-// of tiles, requests the next tile's first operands during the last contraction tile of the current one, and writes
-// a tile's results while those land.
+// Four tile shapes (chosen by pick_shape and plan_dw, linear_plan.h): 256 x 256 and 256 x 192 in linear_pipe.hip, 128 x 128 and
+// 64 x 64 here (gemm_small_kernel).
 //
 // grad W contracts over all tokens of both sets (32K rows at DiT-XL/2 512 px) for few output tiles, so the token
 // range is split over several workgroups per tile; each leaves a float32 partial tile in the workspace and a second
@@ -29,8 +21,7 @@
 // row ranges, then one kernel that adds those.
 #include <type_traits>
 
-#include "linear_plan.h"
-#include "mfma_tiles.h"
+#include "linear_gemm.h"
 
 namespace tvm {
 namespace {
@@ -43,7 +34,6 @@ struct Cfg {
   static constexpr int TI = NWI_ * WI_ * 32;  // output rows per workgroup
   static constexpr int TJ = NWJ_ * WJ_ * 32;  // output columns per workgroup
 };
-constexpr int kGI = 8;                       // tile rows per group in the order the tiles are handed out
 
 // Transposed fragment with the contraction index in natural order: lane (ic, hh) gets, of column 32*db + ic of the
 // tile, rows 16*cc + 8*hh + 0..7 (the first transposing read takes rows 8hh..8hh+3, the second 8hh+4..8hh+7;
@@ -65,20 +55,6 @@ struct TrNat {
     const bf16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lp)(p + hi + imm));
     return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
   }
-};
-
-struct GemmArgs {
-  const bf16* P[2];   // two row sets (forward, grad x) or two contraction sets (grad W)
-  const bf16* Q[2];
-  long long ldP, ldQ; // row pitch in elements of the matrices as stored
-  int I, J, C;        // output rows, output columns, contraction length per set
-  int csets;          // contraction sets (1, or 2 for grad W)
-  bf16* out[2];       // one per row set (forward, grad x); row pitch ldo
-  long long ldo;
-  const bf16* bias;   // added to out[0] only (the tangent has no bias), may be null
-  float* part;        // grad W: float32 partial tiles [splits][I][J]
-  int splits;
-  int nz;             // row sets (forward, grad x: 2) or splits (grad W)
 };
 
 // float32 partial tile of one wave (kWI x kWJ blocks from row i, column jw of split zz): lane = output row, four
@@ -105,270 +81,14 @@ __device__ __forceinline__ void store_partial(const GemmArgs& g, const f32x16 (&
   }
 }
 
-template <bool PTR, bool QTR, bool PARTIAL, class C>
-__global__ __launch_bounds__(C::NT, C::OCC) void gemm_kernel(GemmArgs g) {
-  constexpr int kNW = C::NW, kWI = C::WI, kWJ = C::WJ, kTI = C::TI, kTJ = C::TJ, NST = C::NST;
-  // tiles: "transposed" access [kBK][columns of the stored matrix]; "row" access [rows of the operand][32], two of
-  // them back to back for the kBK = 64 entries of a contraction tile (rows of 64 bytes are dense in LDS and free of
-  // bank conflicts; rows of 128 bytes would need padding)
-  static_assert(kBK == 64, "a row-access operand is staged as two tiles of 32");
-  using TP = typename std::conditional<PTR, Tile<kBK, kTI / 8, kNW>, Tile<kTI, 4, kNW>>::type;
-  using TQ = typename std::conditional<QTR, Tile<kBK, kTJ / 8, kNW>, Tile<kTJ, 4, kNW>>::type;
-  constexpr int P_BYTES = PTR ? TP::BYTES : 2 * TP::BYTES, Q_BYTES = QTR ? TQ::BYTES : 2 * TQ::BYTES;
-  constexpr int BUF = P_BYTES + Q_BYTES;
-  constexpr int STAGE_BYTES = NST * BUF;  // NST stages: tile t in use, tiles t+1 .. t+NST-2 landed or landing, one being refilled
-  constexpr int LOADS = (PTR ? 1 : 2) * TP::IPW + (QTR ? 1 : 2) * TQ::IPW;  // wave-loads per wave and tile
-  constexpr int OUT_REGION = 32 * (64 * kWJ + 16);  // per wave, for store_tile_coalesced
-  constexpr int LDS_BYTES = STAGE_BYTES > kNW * OUT_REGION ? STAGE_BYTES : kNW * OUT_REGION;
-  __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
-  const int tid = threadIdx.x, lane = tid & 63, ic = lane & 31, hh = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wi = wave % C::NWI, wj = wave / C::NWI;
-  const int nI = (g.I + kTI - 1) / kTI, nJ = (g.J + kTJ - 1) / kTJ;
-  const int nct = (g.C + kBK - 1) / kBK;  // contraction tiles per set
-  const int ntot = g.csets * nct;
-  const unsigned lds0 = lds_addr_of(lds);
-  const typename TP::RAddr rp = TP::raddr(ic, hh);
-  const typename TQ::RAddr rq = TQ::raddr(ic, hh);
-  const TrNat<TP> tp = TrNat<TP>::make(ic, hh);
-  const TrNat<TQ> tq = TrNat<TQ>::make(ic, hh);
-  f32x16 acc[kWI][kWJ];
-  bf16x8 pf[2][kWI], qf[2][kWJ];
-  static_assert(NST == 2, "two stages");
-  static_assert(kNW * OUT_REGION <= BUF, "the output staging fits in one stage");
-
-  // Writes out the accumulators of output tile (i0, j0) of row set / split zz.  Runs while the first loads of the
-  // workgroup's next tile are on their way into one stage: bf16 results are staged through the other one, `stage`.
-  auto write_out = [&](int i0, int j0, int zz, int stage) {
-    const int jw = j0 + wj * (kWJ * 32);  // first output column of this wave
-    if (PARTIAL) {
-      store_partial<kWI, kWJ>(g, acc, zz, i0 + wi * kWI * 32, jw, ic, hh);
-    } else {
-      const unsigned lw = lds0 + (unsigned)stage * BUF + (unsigned)wave * OUT_REGION;  // each wave stages its rows through a region of its own
-      if (jw < g.J) {
-#pragma unroll
-        for (int a = 0; a < kWI; ++a) {
-          const int row0 = i0 + (wi * kWI + a) * 32;
-          store_tile_coalesced<kWJ>(lw, g.out[zz] + jw, g.ldo, row0, g.I, g.J - jw, acc[a], 1.f, lane);
-        }
-      }
-    }
-  };
-
-  // Persistent workgroups, one per CU, each working through a list of output tiles: the next tile's first operands
-  // are requested during the last contraction tile of the current one, and a tile's results are written while they
-  // land (and drain to HBM while the next tile is computed).  Hardware
-  // workgroup ids go round-robin over the 8 XCDs, each with an L2 of its own: XCD x owns the x-th eighth of the
-  // logical tile ids, which its workgroups take in turn; logical ids walk the tiles of a row set (or split) in groups
-  // of kGI tile rows, down the group first.  The ~32 workgroups of an XCD are then on a patch of about 8 x 4 tiles at
-  // any one time and march through the contraction together: an operand panel comes from HBM once for the tiles of
-  // the patch that share it.
-  const bool late = !PARTIAL && wave >= kNW / 2;  // (uniform; waves w and w + 4 share a SIMD; grad W has no registers to spare for it)
-  const int total = g.nz * nI * nJ;
-  const int per_xcd = (total + 7) >> 3, wg_per_xcd = (int)(gridDim.x >> 3);
-  const int id_end = min(total, ((int)(blockIdx.x & 7) + 1) * per_xcd);
-
-  // An output tile: where it is, its range of contraction tiles, and the per-lane byte offsets of this wave's loads
-  // within an operand tile (whole tiles / a set's last tile)
-  struct Ctx {
-    int i0, j0, zz, t_begin, t_end, pset;
-    typename TP::Offs op_full, op_last;
-    typename TQ::Offs oq_full, oq_last;
-  };
-  auto locate = [&](int wg) {
-    Ctx c;
-    c.zz = wg / (nI * nJ);  // row set (forward, grad x) or split (grad W)
-    const int id = wg - c.zz * (nI * nJ);
-    const int grp = id / (kGI * nJ), it_first = grp * kGI, gs = min(nI - it_first, kGI);
-    const int rem = id - grp * (kGI * nJ);
-    const int jt = rem / gs, it = it_first + (rem - jt * gs);
-    c.i0 = it * kTI;
-    c.j0 = jt * kTJ;
-    c.t_begin = PARTIAL ? (int)((long long)c.zz * ntot / g.splits) : 0;
-    c.t_end = PARTIAL ? (int)((long long)(c.zz + 1) * ntot / g.splits) : ntot;
-    c.pset = PARTIAL ? 0 : c.zz;
-    const unsigned pitchP = (unsigned)(g.ldP * 2), pitchQ = (unsigned)(g.ldQ * 2);
-    const int clast = g.C - (nct - 1) * kBK;  // contraction entries in a set's last tile
-    if (PTR) {
-      const typename TP::Lane l = TP::lane_setup(min(g.I - c.i0, kTI), wave, lane);  // columns of the stored matrix = output rows
-      c.op_full = TP::offsets(l, pitchP, kBK);
-      c.op_last = TP::offsets(l, pitchP, clast);
-    } else {
-      c.op_full = c.op_last = TP::offsets(TP::lane_setup(32, wave, lane), pitchP, min(g.I - c.i0, kTI));
-    }
-    if (QTR) {
-      const typename TQ::Lane l = TQ::lane_setup(min(g.J - c.j0, kTJ), wave, lane);
-      c.oq_full = TQ::offsets(l, pitchQ, kBK);
-      c.oq_last = TQ::offsets(l, pitchQ, clast);
-    } else {
-      c.oq_full = c.oq_last = TQ::offsets(TQ::lane_setup(32, wave, lane), pitchQ, min(g.J - c.j0, kTJ));
-    }
-    return c;
-  };
-  // wave-load number x (compile-time, 0 .. LOADS-1) of contraction tile t of output tile c into the stage at `buf`
-  auto issue = [&](const Ctx& c, int t, unsigned buf, int x) {
-    const int set = t / nct, ct = t - set * nct;
-    const long long c0 = (long long)ct * kBK;
-    const bool last = ct == nct - 1;
-    const bf16* pb = g.P[PARTIAL ? set : c.pset] + (PTR ? c0 * g.ldP + c.i0 : (long long)c.i0 * g.ldP + c0);
-    const bf16* qb = g.Q[PARTIAL ? set : 0] + (QTR ? c0 * g.ldQ + c.j0 : (long long)c.j0 * g.ldQ + c0);
-    // (row access: the contraction length is a multiple of 32, so the second half of a set's last tile is either
-    // whole or absent; an absent half fetches the first half again, and its fragments are zeroed on the P side)
-    const int half2 = (last && g.C - (int)c0 <= 32) ? 0 : 32;
-    constexpr int NP = (PTR ? 1 : 2) * TP::IPW;
-    if (x < NP) {
-      if (PTR) TP::issue_at(last ? c.op_last.o[x] : c.op_full.o[x], x, pb, buf, wave);
-      else if (x < TP::IPW) TP::issue_at(c.op_full.o[x], x, pb, buf, wave);
-      else TP::issue_at(c.op_full.o[x - TP::IPW], x - TP::IPW, pb + half2, buf + TP::BYTES, wave);
-    } else {
-      const int y = x - NP;
-      if (QTR) TQ::issue_at(last ? c.oq_last.o[y] : c.oq_full.o[y], y, qb, buf + P_BYTES, wave);
-      else if (y < TQ::IPW) TQ::issue_at(c.oq_full.o[y], y, qb, buf + P_BYTES, wave);
-      else TQ::issue_at(c.oq_full.o[y - TQ::IPW], y - TQ::IPW, qb + half2, buf + P_BYTES + TQ::BYTES, wave);
-    }
-  };
-  // A ragged last contraction tile of a set: entries beyond the set's end were fetched as copies of valid ones (the
-  // set's last row, or the first half of the tile); on the P side each wave overwrites with zeros what it fetched of
-  // them (call this once its own loads have landed), so that those entries contribute nothing.
-  auto fix_ragged = [&](int t, int n) {
-    const int ct = t % nct;
-    const int cvalid = ct == nct - 1 ? g.C - ct * kBK : kBK;
-    if (cvalid < kBK) {
-      char* pt = lds + n * BUF;
-#pragma unroll
-      for (int x = 0; x < TP::IPW; ++x) {
-        const int pos = (wave + x * kNW) * 64 + lane;  // chunk of the tile this lane fetched with wave-load x
-        if (PTR) {
-          if (pos / TP::PCH >= cvalid) *reinterpret_cast<uint4*>(pt + pos * 16) = make_uint4(0u, 0u, 0u, 0u);
-        } else if (cvalid <= 32) {
-          *reinterpret_cast<uint4*>(pt + TP::BYTES + pos * 16) = make_uint4(0u, 0u, 0u, 0u);
-        }
-      }
-    }
-  };
-
-  int wg = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-  if (wg >= id_end) return;  // (the grid is never larger than the tiles need, but an XCD's share may be short)
-  Ctx cur = locate(wg);
-  int n0 = 0;  // the stage that holds (or is receiving) the first contraction tile of `cur`
-#pragma unroll
-  for (int x = 0; x < LOADS; ++x) issue(cur, cur.t_begin, lds0, x);
-  int prev_i0 = 0, prev_j0 = 0, prev_zz = -1;  // the tile whose results are still in the accumulators (zz < 0: none)
-  for (;;) {
-    // The first contraction tile of `cur` is on its way into stage n0 (requested during the last contraction tile of
-    // the output tile before, or just now for the workgroup's first one); the other stage is free.  In this order: the
-    // bias values are requested; the wait for the loads in flight; the results of the tile before leave through the
-    // free stage (their stores are not waited for here: the next wait comes a contraction tile later); the
-    // accumulators start from the bias (row set 0; the tangent has none) or from zero.
-    float bv[kWJ][16];
-    {
-      const bool with_bias = !PARTIAL && g.bias != nullptr && cur.pset == 0;
-      const int jw = cur.j0 + wj * (kWJ * 32);
-#pragma unroll
-      for (int b = 0; b < kWJ; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = jw + b * 32 + drow(r, hh);
-          bv[b][r] = with_bias && j < g.J ? (float)g.bias[j] : 0.f;
-        }
-    }
-    dma_wait();
-    fix_ragged(cur.t_begin, n0);
-    if (prev_zz >= 0) write_out(prev_i0, prev_j0, prev_zz, n0 ^ 1);
-    prev_i0 = cur.i0;
-    prev_j0 = cur.j0;
-    prev_zz = cur.zz;
-#pragma unroll
-    for (int b = 0; b < kWJ; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-#pragma unroll
-        for (int a = 0; a < kWI; ++a) acc[a][b][r] = bv[b][r];
-    __syncthreads();  // the first contraction tile is there for everyone; everyone's staging reads are over
-    const bool has_next = wg + wg_per_xcd < id_end;  // uniform
-    const int t_begin = cur.t_begin, t_end = cur.t_end;
-    int n = n0;
-    for (int t = t_begin; t < t_end; ++t, n ^= 1) {
-      // tile t is there for everyone and everyone is done with tile t-1, whose stage is refilled now
-      const bool more = t + 1 < t_end;  // uniform
-      const char* sp = lds + n * BUF;
-      const char* sq = sp + P_BYTES;
-      // fragments of contraction step kk into register set `set`
-      auto fetch = [&](int set, int kk) {
-#pragma unroll
-        for (int a = 0; a < kWI; ++a)
-          pf[set][a] = PTR ? tp.frag(sp, kk, wi * kWI + a) : TP::frag_row(sp + (kk >> 1) * TP::BYTES, rp, wi * kWI + a, kk & 1);
-#pragma unroll
-        for (int b = 0; b < kWJ; ++b)
-          qf[set][b] = QTR ? tq.frag(sq, kk, wj * kWJ + b) : TQ::frag_row(sq + (kk >> 1) * TQ::BYTES, rq, wj * kWJ + b, kk & 1);
-      };
-      auto products = [&](int set) {
-#pragma unroll
-        for (int a = 0; a < kWI; ++a)
-#pragma unroll
-          for (int b = 0; b < kWJ; ++b) acc[a][b] = mfma(qf[set][b], pf[set][a], acc[a][b]);
-      };
-      // Two register sets take turns: the LDS reads of step kk+1 are issued ahead of the products of step kk (the
-      // scheduling barriers keep the compiler from sinking them back to their first use), and the next tile's loads
-      // are issued while the first fragments are on their way from LDS.  The two waves that share a SIMD meet the
-      // per-tile barrier one contraction step apart: the second one (`late`) arrives before its last step, whose
-      // fragments it already holds, so that right behind the barrier the matrix pipe has that step's products to
-      // run while both waves wait for their first fragments of the new tile.
-      static_assert(kBK / 16 == 4, "four contraction steps per tile");
-      auto sync = [&]() {
-        if (more) {
-          dma_wait();  // the next tile has landed
-          fix_ragged(t + 1, n ^ 1);
-        }  // (behind an output tile's last contraction tile the loads in flight are the next output tile's: not waited for here)
-        __syncthreads();  // it is there for everyone, and nobody reads this tile from LDS any more
-      };
-      fetch(0, 0);
-      fetch(1, 1);
-      __builtin_amdgcn_sched_barrier(0);
-      if (more) {
-#pragma unroll
-        for (int x = 0; x < LOADS; ++x) issue(cur, t + 1, lds0 + (n ^ 1) * BUF, x);
-      } else if (has_next) {
-        // the workgroup's next output tile: its first operands are requested now, a contraction tile ahead of the
-        // results of this one, into the stage that this tile no longer uses
-        const Ctx nx = locate(wg + wg_per_xcd);
-#pragma unroll
-        for (int x = 0; x < LOADS; ++x) issue(nx, nx.t_begin, lds0 + (n ^ 1) * BUF, x);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      products(0);
-      __builtin_amdgcn_sched_barrier(0);
-      fetch(0, 2);
-      __builtin_amdgcn_sched_barrier(0);
-      products(1);
-      __builtin_amdgcn_sched_barrier(0);
-      fetch(1, 3);
-      __builtin_amdgcn_sched_barrier(0);
-      products(0);
-      __builtin_amdgcn_sched_barrier(0);
-      if (late) sync();
-      __builtin_amdgcn_sched_barrier(0);
-      products(1);
-      __builtin_amdgcn_sched_barrier(0);
-      if (!late) sync();
-    }
-    // n: the stage behind the one computed from last, i.e. where the next output tile's first operands are landing
-    if (!has_next) {
-      write_out(prev_i0, prev_j0, prev_zz, n ^ 1);
-      break;
-    }
-    wg += wg_per_xcd;
-    cur = locate(wg);  // (worked out again rather than kept in registers through the loop)
-    n0 = n;
-  }
-}
-
 // The same product for shapes with few 256-row tiles: workgroups of four waves on 64 x 64 or 128 x 128 output tiles, one
 // tile each, many workgroups in flight.  What bounds it is latency (a contraction tile is 128 or 512 cycles of matrix
 // work per wave against some 2000 from L2), so the contraction runs NST - 1 tiles ahead through NST LDS stages, with one
-// barrier per tile and the loads in flight counted rather than drained.  Contraction tiles are taken in the same order
-// and every output element is the same chain of products as in gemm_kernel: results are bit for bit the same (with
-// equal splits).
+// barrier per tile and the loads in flight counted rather than drained.  Tiles are filled and read as in the attention kernels
+// (mfma_tiles.h: swizzled row-major tiles; "row" fragments are 16-byte reads, "transposed" ones the transposing LDS read, here
+// with the contraction index in natural order so that both kinds pair up).  Contraction tiles are taken in the same order and
+// every output element is the same chain of products as in linear_pipe.hip: results are bit for bit the same (with equal
+// splits).
 template <bool PTR, bool QTR, bool PARTIAL, class C>
 __global__ __launch_bounds__(C::NT, C::OCC) void gemm_small_kernel(GemmArgs g) {
   constexpr int kNW = C::NW, kWI = C::WI, kWJ = C::WJ, kTI = C::TI, kTJ = C::TJ, NST = C::NST;
@@ -381,7 +101,7 @@ __global__ __launch_bounds__(C::NT, C::OCC) void gemm_small_kernel(GemmArgs g) {
   static_assert(NST >= 3 && (NST - 2) * LOADS < 64 && kNW * OUT_REGION <= NST * BUF, "stages");
   __shared__ __attribute__((aligned(16))) char lds[NST * BUF];
   const int nI = (g.I + kTI - 1) / kTI, nJ = (g.J + kTJ - 1) / kTJ, total = g.nz * nI * nJ;
-  // XCD x owns the x-th eighth of the tile list (as in gemm_kernel: groups of kGI tile rows, down the group first)
+  // XCD x owns the x-th eighth of the tile list (as in linear_pipe.hip: groups of kGI tile rows, down the group first)
   const int wg = (int)(blockIdx.x & 7) * ((total + 7) >> 3) + (int)(blockIdx.x >> 3);
   if (wg >= min(total, ((int)(blockIdx.x & 7) + 1) * ((total + 7) >> 3))) return;
   const int tid = threadIdx.x, lane = tid & 63, ic = lane & 31, hh = lane >> 5;
@@ -458,7 +178,7 @@ __global__ __launch_bounds__(C::NT, C::OCC) void gemm_small_kernel(GemmArgs g) {
   for (int t = t_begin; t < t_end; ++t) {
     dma_wait_keep<(NST - 2) * LOADS>();  // this wave's share of tile t has landed
     const int ct = two && t >= nct ? t - nct : t;
-    if (ct == nct - 1 && clast < kBK) {  // entries beyond the set's end weigh nothing (see fix_ragged in gemm_kernel)
+    if (ct == nct - 1 && clast < kBK) {  // entries beyond the set's end were fetched as copies: zeros instead
       char* pt = lds + n * BUF;
 #pragma unroll
       for (int x = 0; x < TP::IPW; ++x) {
@@ -646,39 +366,24 @@ __global__ __launch_bounds__(1024) void colsum_direct_kernel(const bf16* __restr
 constexpr int kDirectRows = 2048;  // up to this many rows the column sums take one launch
 
 // The tile shapes in use
-using Cfg256 = Cfg<2, 4, 4, 2, 2, 1>;  // 256 x 256, eight waves
-using Cfg192 = Cfg<4, 2, 2, 3, 2, 1>;  // 256 x 192, eight waves
 using Cfg128 = Cfg<2, 2, 2, 2, 3, 1>;  // 128 x 128, four waves
 using Cfg64 = Cfg<2, 2, 1, 1, 4, 2>;   // 64 x 64, four waves
 template <class C>
 constexpr bool shape_is(int c) { return C::TI == kTileI[c] && C::TJ == kTileJ[c]; }
-static_assert(shape_is<Cfg256>(k256) && shape_is<Cfg192>(k192) && shape_is<Cfg128>(k128) && shape_is<Cfg64>(k64), "the plan's tiles");
+static_assert(shape_is<Cfg128>(k128) && shape_is<Cfg64>(k64), "the plan's tiles");
 static_assert(Cfg128::NT == kSmallThreads && Cfg64::NT == kSmallThreads, "the plan's limit");
 
-// Persistent workgroups: 8 XCDs x at most 32 CUs, fewer where an XCD's share of the tiles is smaller.
-int persistent_grid(int tiles) {
-  const int per = (tiles + 7) / 8;
-  return 8 * (per < 32 ? per : 32);
-}
 int bias_chunks(int R) {
   const int c = (R + 63) / 64;
   return c > 256 ? 256 : c;
 }
 
-// Launches a product with tile shape c.  (DIRECT: the 256-row shapes are left out, see plan_dw.)
-template <bool PTR, bool QTR, bool PARTIAL, bool DIRECT = false>
-hipError_t launch_gemm(int c, const GemmArgs& g, hipStream_t st) {
-  const int tiles = (int)(g.nz * tiles_of(c, g.I, g.J)), small_grid = (int)small_workgroups(tiles);
-  if (c == k64) {
-    hipLaunchKernelGGL((gemm_small_kernel<PTR, QTR, PARTIAL, Cfg64>), dim3(small_grid), dim3(Cfg64::NT), 0, st, g);
-  } else if (DIRECT || c == k128) {
-    hipLaunchKernelGGL((gemm_small_kernel<PTR, QTR, PARTIAL, Cfg128>), dim3(small_grid), dim3(Cfg128::NT), 0, st, g);
-  } else if constexpr (!DIRECT) {
-    if (c == k192)
-      hipLaunchKernelGGL((gemm_kernel<PTR, QTR, PARTIAL, Cfg192>), dim3(persistent_grid(tiles)), dim3(Cfg192::NT), 0, st, g);
-    else
-      hipLaunchKernelGGL((gemm_kernel<PTR, QTR, PARTIAL, Cfg256>), dim3(persistent_grid(tiles)), dim3(Cfg256::NT), 0, st, g);
-  }
+// Launches a product with tile shape c (128 or 64).
+template <bool PTR, bool QTR, bool PARTIAL>
+hipError_t launch_small(int c, const GemmArgs& g, hipStream_t st) {
+  const dim3 grid((unsigned)small_workgroups(g.nz * tiles_of(c, g.I, g.J)));
+  if (c == k64) hipLaunchKernelGGL((gemm_small_kernel<PTR, QTR, PARTIAL, Cfg64>), grid, dim3(Cfg64::NT), 0, st, g);
+  else hipLaunchKernelGGL((gemm_small_kernel<PTR, QTR, PARTIAL, Cfg128>), grid, dim3(Cfg128::NT), 0, st, g);
   return hipGetLastError();
 }
 
@@ -713,7 +418,8 @@ hipError_t launch_linear_fwd(int R, int K, int F, long long ldx, long long ldy, 
   g.ldo = ldy;
   g.bias = (const bf16*)bias;
   g.nz = 2;
-  return launch_gemm<false, false, false>(pick_shape(false, 2, R, F, K), g, st);
+  const int shape = pick_shape(false, 2, R, F, K);
+  return shape < k128 ? launch_gemm_fwd(shape, g, st) : launch_small<false, false, false>(shape, g, st);
 }
 
 hipError_t launch_linear_bwd(int R, int K, int F, long long ldx, long long ldy, const void* x, const void* tx,
@@ -734,7 +440,8 @@ hipError_t launch_linear_bwd(int R, int K, int F, long long ldx, long long ldy, 
     g.out[1] = (bf16*)gtx;
     g.ldo = ldx;
     g.nz = 2;
-    const hipError_t e = launch_gemm<false, true, false>(pick_shape(true, 2, R, K, F), g, st);
+    const int shape = pick_shape(true, 2, R, K, F);
+    const hipError_t e = shape < k128 ? launch_gemm_gx(shape, g, st) : launch_small<false, true, false>(shape, g, st);
     if (e != hipSuccess) return e;
   }
   const int max_splits = dw_splits(F, K, R);
@@ -759,10 +466,10 @@ hipError_t launch_linear_bwd(int R, int K, int F, long long ldx, long long ldy, 
     g.out[0] = (bf16*)gw;
     g.ldo = K;
     if (splits == 1 && plan.shape >= k128) {
-      const hipError_t e = launch_gemm<true, true, false, true>(plan.shape, g, st);
+      const hipError_t e = launch_small<true, true, false>(plan.shape, g, st);
       if (e != hipSuccess) return e;
     } else {
-      hipError_t e = launch_gemm<true, true, true>(plan.shape, g, st);
+      hipError_t e = plan.shape < k128 ? launch_gemm_gw(plan.shape, g, st) : launch_small<true, true, true>(plan.shape, g, st);
       if (e != hipSuccess) return e;
       const long long n = (long long)F * K;
       hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)((n / 8 + 255) / 256)), dim3(256), 0, st, part, splits, n,

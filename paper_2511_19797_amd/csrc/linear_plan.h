@@ -20,25 +20,23 @@ inline long long small_workgroups(long long tiles) { return 8 * ((tiles + 7) / 8
 inline bool grid_fits(int c, long long tiles) { return c < k128 || small_workgroups(tiles) * kSmallThreads < (1ll << 32); }
 
 // Time of a product (ns): `tiles` output tiles of shape c over `steps` contraction tiles each are rounds of 256 workgroups, each
-// its steps and a fixed part (first operands, results), behind a start-up.  The weights are fits to times of all four shapes at
-// 1177 forward shapes and 556 of grad x (whose second operand is read transposed: other weights), R = 64 ... 65536 rows, widths
-// 32 ... 4608 either way: the choice is within 1 % of the 256 x 256 shape or faster at all but 9 of them (at most 4 %, one
-// round's noise), and 0.1 % behind the fastest shape on average.  Some of them (us; 256 | 192 | 128 | 64):
-//   forward, 256 x 4608 -> 1152:    102 |  98 |  51 |  31     few tiles: small ones fill the chip
-//   forward, 1024 x 1536 -> 1152:    40 |  38 |  24 |  27
-//   forward, 2048 x 768 -> 1536:     26 |  25 |  28 |  31     the small shapes' fixed part, round after round
-//   forward, 2048 x 1152 -> 3456:    38 |  61 |  67 |  81     224 tiles of 256 are one round, 288 of 192 are two
-//   forward, 16384 x 384 -> 1152:    46 |  48 |  79 | 102     short contraction: 192 has the larger fixed part
-//   forward, 16384 x 4608 -> 1152:  395 | 384 | 455 | 636     long contraction, and 1152 = 6 x 192: no padded columns
-//   forward, 16384 x 1152 -> 4608:  321 | 355 | 524 | 690
-// The layers of a whole block with tangent, forward and backward (us, with 256 x 256 tiles alone / with this choice): B1 T256
-// C1152 forward 232 / 198, B2 T250 C768 626 / 529 (both then bound by the host's calls), B32 T256 C1152 2727 / 2684, B16 T1024
-// 5434 / 5359.
+// its steps and a fixed part (first operands, results), behind a start-up.  The weights are fits to kernel times of all four
+// shapes at 378 products of the forward and 378 of grad x (whose second operand is read transposed: other weights), R = 64 ...
+// 65536 rows, widths 32 ... 4608 either way.  From a contraction of 288 on the choice is 0.2 % behind the fastest shape on
+// average (forward; at most 9 %), below, where nearly all of a product is start-up and stores, 4 %; grad x 0.2 and 0.3 %.
+// Some of the times (us; 256 | 192 | 128 | 64):
+//   forward, 500 x 768 -> 768:       18 |  15 |  12 |   8     few tiles: small ones fill the chip
+//   forward, 1024 x 1152 -> 1152:    24 |  20 |  16 |  18
+//   forward, 2048 x 768 -> 2304:     23 |  20 |  33 |  35     the small shapes' fixed part, round after round
+//   forward, 2048 x 512 -> 3072:     19 |  20 |  28 |  38
+//   forward, 16384 x 64 -> 1152:     20 |  18 |  39 |  48     short contraction: first operands and stores
+//   forward, 16384 x 768 -> 3072:   135 | 140 | 256 | 345
+//   forward, 8192 x 4608 -> 1152:   183 | 152 | 236 | 288     long contraction, and 1152 = 6 x 192: no padded columns
 struct ShapeCost {
   int start, fixed, step;
 };
-constexpr ShapeCost kCostRow[kShapes] = {{4323, 4654, 1625}, {2820, 8013, 1356}, {1500, 5408, 693}, {865, 2359, 265}};
-constexpr ShapeCost kCostTr[kShapes] = {{3060, 8558, 1427}, {2889, 8984, 1114}, {2938, 5155, 625}, {1628, 2537, 214}};
+constexpr ShapeCost kCostRow[kShapes] = {{0, 6943, 1600}, {1984, 6784, 1153}, {1762, 5408, 641}, {2165, 2397, 277}};
+constexpr ShapeCost kCostTr[kShapes] = {{4487, 11999, 1106}, {0, 10232, 804}, {3294, 4464, 598}, {3385, 2146, 198}};
 inline long long product_ns(const ShapeCost& c, long long tiles, int steps) {
   return c.start + (tiles + 255) / 256 * (c.fixed + (long long)steps * c.step);
 }
@@ -76,18 +74,18 @@ inline int dw_splits(int F, int K, int R) {
   }
   return best;
 }
-// grad W: time of `tiles` output tiles of shape c over `steps` contraction tiles each, in hundredths of a contraction tile of
-// the 256 x 256 shape (1.5 us on an idle chip, 2 us on a full one).
+// grad W: time of `tiles` output tiles of shape c over `steps` contraction tiles each, in units of about 17 ns (the 256 x 256
+// shape takes 1.2 us per contraction tile on an idle chip, 1.6 on a full one).
 inline long long dw_cost(int c, long long tiles, int steps) {
-  constexpr int kStep[kShapes] = {100, 88, 45, 28}, kFixed[kShapes] = {150, 130, 70, 50};
+  constexpr int kStep[kShapes] = {86, 72, 48, 28}, kFixed[kShapes] = {75, 100, 70, 66};
   return (tiles + 255) / 256 * ((long long)steps * kStep[c] + kFixed[c]);
 }
 // Shape and number of contraction splits of grad W: what the partial tiles cost on top is two passes over them at
 // 5 TB/s and a launch (3 us).  The 128 and 64 shapes write bf16 directly when there is one split.  Never more splits
 // than dw_splits: the workspace is sized for those.
-// (us of the whole backward, R 500 768 -> 768: 53 with 16 splits of 256 x 256 tiles, 35 with one of 64 x 64; R 16384
-// 1152 -> 3456: 597 with 3 splits of 256 x 256, 581 with 3 of 256 x 192.  Against every shape but 64 and every number of splits,
-// twelve layers of 384 ... 4608 and R = 2048 ... 65536: within 4 % of the fastest, never behind the 256 shape by more than 1.5 %.)
+// (us of grad W alone, 256 | 192 | 128 | 64: R 500 768 -> 768 19 | 17 | 16 | 10; R 4096 768 -> 3072 53 | 48 | 73 | 122; R 16384
+// 1152 -> 3456 252 | 220 | 352 | 685.  At 189 layers of 288 ... 4608 and R = 64 ... 16384 the choice is 2 % behind the fastest
+// shape on average.)
 struct DwPlan {
   int shape, splits;
 };

@@ -14,6 +14,21 @@ LINEAR = [
     ((3114, 4192, 288), (64, 256, 256), True),
 ]
 
+# The 256-row tiles: (R, K, F), the tiles of y, grad x and grad W.  One contraction tile and half of one, one and a half, two;
+# a last row tile of one row, of all but one; a last column tile of one block of 32; several output tiles per workgroup with
+# contractions shorter than the loads run ahead; grad W with the border between the two row sets inside a part.
+LINEAR_PIPE = [
+    ((4097, 32, 1184), (256, 64, 64)),
+    ((8191, 64, 416), (256, 64, 64)),
+    ((66000, 32, 32), (256, 64, 64)),
+    ((5000, 96, 800), (256, 64, 128)),
+    ((33025, 96, 96), (192, 128, 64)),
+    ((6145, 608, 352), (192, 192, 128)),
+    ((12289, 768, 800), (192, 192, 192)),
+    ((3001, 4640, 1184), (192, 256, 192)),
+    ((2049, 1184, 4640), (192, 192, 256)),
+]
+
 # Forward: heads, M, N.  Eight waves on 256 rows (512 keys and more, more than 128 queries, head dims up to 96), with a whole and
 # with a ragged last key tile, workgroups whose upper waves hold no row, M != N either way round
 FORWARD_EIGHT_WAVES = [(33, 512, 512), (33, 513, 513), (32, 543, 543), (17, 1000, 1000), (60, 257, 512), (52, 300, 543), (25, 700, 600),
