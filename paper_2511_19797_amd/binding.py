@@ -1,4 +1,4 @@
-"""ctypes binding of libtvmattn.so: argument marshalling only.
+"""Binding of libtvmattn.so: argument marshalling only (ctypes, and for ordinary calls the native module _fastcall).
 
 Same names as the C entry points (include/tvmattn.h).  torch supplies device
 memory and the current stream; every step of the computation runs in the
@@ -102,6 +102,31 @@ def lib():
     return _lib
 
 
+_fast = None
+
+
+def _load_fast():
+    """The module that takes the ordinary calls in native code (csrc/fastcall.cpp): each of its functions does what the
+    function here that calls it does, for plain tensors that pass the checks, and returns None for anything else, which
+    then goes through the Python below."""
+    global _fast
+    lib()
+    try:
+        from . import _fastcall
+    except ImportError as e:
+        raise ImportError(f"{os.path.join(_HERE, '_fastcall.so')} cannot be loaded ({e}): run `python -m "
+                          "paper_2511_19797_amd.build` (or __graft_entry__.build()) first") from e
+    _fast = _fastcall
+    return _fast
+
+
+def _taken(r):
+    """The outputs of a call that _fast has made, or the error that its status stands for."""
+    if r.__class__ is int:
+        _check(r)
+    return r
+
+
 def tvmattn_version():
     return lib().tvmattn_version()
 
@@ -166,6 +191,10 @@ def _ptr(t):
 def tvmattn_jvp_fwd(q, k, v, tq, tk, tv, scale=0.0, out=None, save=True, flags=0):
     """Returns (o, to, lse, stats).  `out`, if given, is that same tuple of preallocated tensors.
     save=False: nothing is kept for a backward (lse and stats are None)."""
+    if out is None:
+        r = (_fast or _load_fast()).jvp_fwd(q, k, v, tq, tk, tv, scale, save, flags)
+        if r is not None:
+            return _taken(r)
     _same_layout(q, tq)
     _same_layout(k, v, tk, tv)
     desc = make_desc(k, scale, q, flags)
@@ -213,6 +242,10 @@ def tvmattn_jvp_bwd(q, k, v, tq, tk, tv, o, to, lse, stats, gO, gTO, scale=0.0, 
     None and dtq, dtk, dtv come back as None.  gO=None: the gradient of <gTO, tO> alone.
     events: None, or four raw hipEvent_t handles (ints, created with timing enabled; None or 0 skips that
     record): the call goes through tvmattn_jvp_bwd_timed."""
+    if out is None and workspace is None and events is None:
+        r = (_fast or _load_fast()).jvp_bwd(q, k, v, tq, tk, tv, o, to, lse, stats, gO, gTO, scale, flags)
+        if r is not None:
+            return _taken(r)
     desc, out, ptrs = _bwd_args(q, k, v, tq, tk, tv, o, to, lse, stats, gO, gTO, scale, out, flags)
     need = int(lib().tvmattn_jvp_bwd_workspace_bytes(ctypes.byref(desc)))
     if workspace is None:
@@ -242,6 +275,10 @@ def _gain_ok(g, ref):
 
 def tvmattn_qknorm_jvp_fwd(q, tq, k, tk, gain_q, gain_k, eps, out=None):
     """Returns (qn, tqn, kn, tkn): RMSNorm with gain of the rows of q and k, and the tangents along tq, tk."""
+    if out is None:
+        r = (_fast or _load_fast()).qknorm_fwd(q, tq, k, tk, gain_q, gain_k, eps)
+        if r is not None:
+            return _taken(r)
     _same_layout(q, tq)
     _same_layout(k, tk)
     _gain_ok(gain_q, q)
@@ -321,6 +358,12 @@ def tvmattn_jvp_bwd_qknorm(q, tq, k, tk, gain_q, gain_k, eps, qn, tqn, kn, tkn, 
     """Attention backward and QK-norm backward in one call.  Returns (dq, dk, dv, dtq, dtk, dtv, dgain_q, dgain_k),
     the first six with respect to the tensors before the normalisation.  Raises TvmattnError (status -2) for
     shapes the fused kernels do not take."""
+    if out is not None and len(out) == 8 and workspace is None:
+        r = (_fast or _load_fast()).bwd_qknorm(q, tq, k, tk, gain_q, gain_k, eps, qn, tqn, kn, tkn, v, tv, o, to, lse, stats, gO,
+                                               gTO, scale, *out)
+        if r is not None:
+            _check(r)
+            return out
     _same_layout(q, tq, qn, tqn, o, to, gO, gTO)
     _same_layout(k, tk, kn, tkn, v, tv)
     _gain_ok(gain_q, q)
@@ -362,6 +405,10 @@ def _adaln_args(x, tx, mods):
 
 def tvmattn_adaln_jvp_fwd(x, tx, a, ta, b, tb, eps, out=None):
     """Returns (y, ty): RMSNorm^-(x) * RMSNorm^-(a) + RMSNorm^-(b) and its tangent along (tx, ta, tb)."""
+    if out is None:
+        r = (_fast or _load_fast()).adaln_fwd(x, tx, a, ta, b, tb, eps)
+        if r is not None:
+            return _taken(r)
     B, T, C, dt = _adaln_args(x, tx, (a, ta, b, tb))
     y, ty = out if out is not None else (torch.empty_like(x), torch.empty_like(x))
     _check(lib().tvmattn_adaln_jvp_fwd(B, T, C, dt, x.data_ptr(), tx.data_ptr(), a.data_ptr(), ta.data_ptr(), b.data_ptr(),
@@ -372,6 +419,10 @@ def tvmattn_adaln_jvp_fwd(x, tx, a, ta, b, tb, eps, out=None):
 def tvmattn_adaln_jvp_bwd(x, tx, a, ta, b, tb, eps, gy, gty, out=None, workspace=None, gres=None, gtres=None):
     """Returns (gx, gtx, ga, gta, gb, gtb).  gres, gtres (both or neither): gradients that reach x and tx along the
     residual connection, added to gx and gtx (tvmattn_adaln_jvp_bwd_residual)."""
+    if out is None and workspace is None:
+        r = (_fast or _load_fast()).adaln_bwd(x, tx, a, ta, b, tb, eps, gy, gty, gres, gtres)
+        if r is not None:
+            return _taken(r)
     B, T, C, dt = _adaln_args(x, tx, (a, ta, b, tb))
     _adaln_args(gy, gty, ())
     if gy.shape != x.shape or gy.dtype != x.dtype:
@@ -398,6 +449,10 @@ def tvmattn_adaln_jvp_bwd(x, tx, a, ta, b, tb, eps, gy, gty, out=None, workspace
 
 def tvmattn_gate_jvp_fwd(x, tx, h, th, c, tc, eps, out=None):
     """Returns (z, tz): x + RMSNorm^-(c) * h and its tangent along (tx, th, tc)."""
+    if out is None:
+        r = (_fast or _load_fast()).gate_fwd(x, tx, h, th, c, tc, eps)
+        if r is not None:
+            return _taken(r)
     B, T, C, dt = _adaln_args(x, tx, (c, tc))
     _adaln_args(h, th, ())
     if h.shape != x.shape or h.dtype != x.dtype:
@@ -410,6 +465,10 @@ def tvmattn_gate_jvp_fwd(x, tx, h, th, c, tc, eps, out=None):
 
 def tvmattn_gate_jvp_bwd(h, th, c, tc, eps, gz, gtz, out=None, workspace=None):
     """Returns (gh, gth, gc, gtc); the gradients with respect to x and tx are gz and gtz themselves."""
+    if out is None and workspace is None:
+        r = (_fast or _load_fast()).gate_bwd(h, th, c, tc, eps, gz, gtz)
+        if r is not None:
+            return _taken(r)
     B, T, C, dt = _adaln_args(h, th, (c, tc))
     _adaln_args(gz, gtz, ())
     if gz.shape != h.shape or gz.dtype != h.dtype:
@@ -439,6 +498,10 @@ def _pointwise_args(first, *rest):
 
 def tvmattn_gelu_jvp_fwd(u, tu, out=None):
     """Returns (a, ta): the tanh-form GELU of u and its tangent gelu'(u) * tu."""
+    if out is None:
+        r = (_fast or _load_fast()).gelu_fwd(u, tu)
+        if r is not None:
+            return _taken(r)
     a, ta = out if out is not None else (torch.empty_like(u), torch.empty_like(u))
     n, dt = _pointwise_args(u, tu, a, ta)
     _check(lib().tvmattn_gelu_jvp_fwd(n, dt, u.data_ptr(), tu.data_ptr(), a.data_ptr(), ta.data_ptr(), _stream()))
@@ -447,6 +510,10 @@ def tvmattn_gelu_jvp_fwd(u, tu, out=None):
 
 def tvmattn_gelu_jvp_bwd(u, tu, ga, gta, out=None):
     """Returns (gu, gtu), the gradient of <ga, a> + <gta, ta>."""
+    if out is None:
+        r = (_fast or _load_fast()).gelu_bwd(u, tu, ga, gta)
+        if r is not None:
+            return _taken(r)
     gu, gtu = out if out is not None else (torch.empty_like(u), torch.empty_like(u))
     n, dt = _pointwise_args(u, tu, ga, gta, gu, gtu)
     _check(lib().tvmattn_gelu_jvp_bwd(n, dt, u.data_ptr(), tu.data_ptr(), ga.data_ptr(), gta.data_ptr(), gu.data_ptr(),
@@ -485,6 +552,10 @@ def _linear_args(x, tx, w, bias):
 def tvmattn_linear_jvp_fwd(x, tx, w, bias=None, out=None):
     """Returns (y, ty): x W^T + b and tx W^T, for x, tx [..., K] (or 2-D [R, K] views with a row pitch) and w [F, K].
     `out`: preallocated (y, ty), contiguous [..., F] or 2-D [R, F] views with a row pitch."""
+    if out is None:
+        r = (_fast or _load_fast()).linear_fwd(x, tx, w, bias)
+        if r is not None:
+            return _taken(r)
     R, K, F, dt, ldx = _linear_args(x, tx, w, bias)
     if out is None:
         shape = x.shape[:-1] + (F,)
@@ -507,6 +578,10 @@ def tvmattn_linear_jvp_bwd_workspace_bytes(x, w):
 def tvmattn_linear_jvp_bwd(x, tx, w, gy, gty, bias_grad=True, out=None, workspace=None):
     """Returns (gx, gtx, gw, gbias), the gradient of <gy, y> + <gty, ty> (gbias None unless bias_grad).  `out`:
     preallocated (gx, gtx, gw, gbias or None); gx, gtx must be laid out like x."""
+    if out is None and workspace is None:
+        r = (_fast or _load_fast()).linear_bwd(x, tx, w, gy, gty, bias_grad)
+        if r is not None:
+            return _taken(r)
     R, K, F, dt, ldx = _linear_args(x, tx, w, None)
     Ry, ldy = _rows(gy, F, "gy")
     if Ry != R or gty.shape != gy.shape or gty.stride() != gy.stride() or gy.dtype != x.dtype or gty.dtype != x.dtype:

@@ -8,6 +8,7 @@ from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB = os.path.join(HERE, "libtvmattn.so")
+FASTCALL = os.path.join(HERE, "_fastcall.so")        # the binding's ordinary calls (csrc/fastcall.cpp), a CPython module
 PEAKS_LIB = os.path.join(HERE, "libtvmpeaks.so")  # bench.py's microbenchmarks of the card's ceilings, not part of the product
 
 COMMON = [
@@ -49,6 +50,20 @@ def _run(cmd, verbose):
         print(err)
 
 
+def build_fastcall(verbose=False):
+    """Host code only, against the torch that is installed and the library beside it."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    tlib = cpp_extension.library_paths()[0]
+    _run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-w", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+          "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-I{sysconfig.get_paths()['include']}", "-I/opt/rocm/include",
+          *[f"-I{d}" for d in cpp_extension.include_paths()], os.path.join(HERE, "csrc", "fastcall.cpp"), "-o", FASTCALL,
+          f"-L{tlib}", "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10", f"-L{HERE}", "-l:libtvmattn.so",
+          "-Wl,-rpath,$ORIGIN", f"-Wl,-rpath,{tlib}"], verbose)
+
+
 def build(verbose=False, extra=(), jobs=None):
     srcs = sorted(glob.glob(os.path.join(HERE, "csrc", "*.hip")))
     jobs = jobs or min(8, os.cpu_count() or 1, len(srcs))
@@ -62,6 +77,7 @@ def build(verbose=False, extra=(), jobs=None):
         with ThreadPoolExecutor(max_workers=jobs) as pool:  # one hipcc process per translation unit
             objs = list(pool.map(compile_one, srcs))
         _run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], verbose)
+    build_fastcall(verbose)
     _run(["hipcc", *COMMON, "-shared", os.path.join(HERE, "peaks", "peaks.hip"), "-o", PEAKS_LIB], verbose)
     return LIB
 
