@@ -26,36 +26,8 @@
 namespace tvm {
 namespace {
 
-// Shape of a workgroup: NWI x NWJ waves, each with WI x WJ blocks of 32 x 32; NST LDS stages; OCC workgroups per CU.
-template <int NWI_, int NWJ_, int WI_, int WJ_, int NST_, int OCC_>
-struct Cfg {
-  static constexpr int NWI = NWI_, NWJ = NWJ_, WI = WI_, WJ = WJ_, NST = NST_, OCC = OCC_;
-  static constexpr int NW = NWI_ * NWJ_, NT = 64 * NW;
-  static constexpr int TI = NWI_ * WI_ * 32;  // output rows per workgroup
-  static constexpr int TJ = NWJ_ * WJ_ * 32;  // output columns per workgroup
-};
-
-// Transposed fragment with the contraction index in natural order: lane (ic, hh) gets, of column 32*db + ic of the
-// tile, rows 16*cc + 8*hh + 0..7 (the first transposing read takes rows 8hh..8hh+3, the second 8hh+4..8hh+7;
-// four consecutive rows share one swizzle term, as in Tile::taddr).
-template <class T>
-struct TrNat {
-  int lo, hi;
-  __device__ __forceinline__ static TrNat make(int ic, int hh) {
-    const int i = ic & 15, bq = ic >> 4;
-    const int y = 2 * bq + ((i & 3) >> 1);
-    const int r0 = 8 * hh + (i >> 2), r1 = r0 + 4;
-    const int sub = (i & 1) * 8;
-    return TrNat{(r0 * T::PCH + (y ^ ((r0 >> 2) & 3))) * 16 + sub, (r1 * T::PCH + (y ^ ((r1 >> 2) & 3))) * 16 + sub};
-  }
-  __device__ __forceinline__ bf16x8 frag(const char* p, int cc, int db) const {
-    typedef bf16x4 __attribute__((address_space(3))) * lp;
-    const int imm = cc * 16 * T::PCH * 16 + db * 64;
-    const bf16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lp)(p + lo + imm));
-    const bf16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lp)(p + hi + imm));
-    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
-  }
-};
+// All waves of the workgroup.  (Not __syncthreads, which waits for every load in flight.)
+__device__ __forceinline__ void barrier() { asm volatile("s_barrier" ::: "memory"); }
 
 // float32 partial tile of one wave (kWI x kWJ blocks from row i, column jw of split zz): lane = output row, four
 // consecutive columns per register group.
@@ -81,139 +53,153 @@ __device__ __forceinline__ void store_partial(const GemmArgs& g, const f32x16 (&
   }
 }
 
-// The same product for shapes with few 256-row tiles: workgroups of four waves on 64 x 64 or 128 x 128 output tiles, one
-// tile each, many workgroups in flight.  What bounds it is latency (a contraction tile is 128 or 512 cycles of matrix
-// work per wave against some 2000 from L2), so the contraction runs NST - 1 tiles ahead through NST LDS stages, with one
-// barrier per tile and the loads in flight counted rather than drained.  Tiles are filled and read as in the attention kernels
-// (mfma_tiles.h: swizzled row-major tiles; "row" fragments are 16-byte reads, "transposed" ones the transposing LDS read, here
-// with the contraction index in natural order so that both kinds pair up).  Contraction tiles are taken in the same order and
-// every output element is the same chain of products as in linear_pipe.hip: results are bit for bit the same (with equal
-// splits).
-template <bool PTR, bool QTR, bool PARTIAL, class C>
-__global__ __launch_bounds__(C::NT, C::OCC) void gemm_small_kernel(GemmArgs g) {
-  constexpr int kNW = C::NW, kWI = C::WI, kWJ = C::WJ, kTI = C::TI, kTJ = C::TJ, NST = C::NST;
-  using TP = typename std::conditional<PTR, Tile<kBK, kTI / 8, kNW>, Tile<kTI, 4, kNW>>::type;
-  using TQ = typename std::conditional<QTR, Tile<kBK, kTJ / 8, kNW>, Tile<kTJ, 4, kNW>>::type;
-  constexpr int P_BYTES = PTR ? TP::BYTES : 2 * TP::BYTES, Q_BYTES = QTR ? TQ::BYTES : 2 * TQ::BYTES;
-  constexpr int BUF = P_BYTES + Q_BYTES;
-  constexpr int LOADS = (PTR ? 1 : 2) * TP::IPW + (QTR ? 1 : 2) * TQ::IPW;
-  constexpr int OUT_REGION = 32 * (64 * kWJ + 16);
-  static_assert(NST >= 3 && (NST - 2) * LOADS < 64 && kNW * OUT_REGION <= NST * BUF, "stages");
-  __shared__ __attribute__((aligned(16))) char lds[NST * BUF];
-  const int nI = (g.I + kTI - 1) / kTI, nJ = (g.J + kTJ - 1) / kTJ, total = g.nz * nI * nJ;
+// The products for shapes with few 256-row tiles: workgroups of four waves on 64 x 64 or 128 x 128 output tiles (N), one tile
+// each.  What bounds a contraction tile of 64 is LDS: at N = 64 32 KB of fragment reads and 16 KB that land there, 384 cycles at
+// 128 bytes a cycle, next to 128 cycles of products per wave (N = 128: 96 KB, 768 and 512).  So a wave reads the fragments of
+// the next tile between the products of this one, the loads run NST - 2 tiles ahead, counted rather than drained, and their
+// descriptors move by additions: a tile takes 430 cycles (900), against 740 (1500) with reads, then products, and descriptors
+// worked out anew for every tile.  us before / now: forward 256 x 1152 -> 1152 9.6 / 7.5, 256 x 4608 -> 1152 26.8 / 18.2, 500 x 3072
+// -> 768 19.1 / 13.6, 500 x 1152 -> 3456 (128) 17.8 / 15.0; grad x 256 x 1152 -> 4608 28.2 / 17.4; grad W 500 x 768 -> 3072 (128) 16.2 / 13.6.
+// Operand tiles as in linear_pipe.hip (Operand: whole cache lines, no padding, zeros beyond the edges).  Contraction tiles are
+// taken in the same order and every output element is the same chain of products as there: results are bit for bit the same
+// (with equal splits).
+template <bool PTR, bool QTR, bool PARTIAL, int N, int NST, int OCC>
+__global__ __launch_bounds__(kSmallThreads, OCC) void gemm_small_kernel(GemmArgs g) {
+  constexpr int W = N / 64;                              // blocks of 32 x 32 per wave, either way
+  using OP = Operand<PTR, N>;
+  using OQ = Operand<QTR, N>;
+  constexpr unsigned HALF = N * 128u, BUF = 2 * HALF;    // a stage: P tile, Q tile
+  constexpr int LOADS = OP::LOADS + OQ::LOADS;           // wave-loads per wave and tile
+  constexpr unsigned OUT_REGION = 32 * (64 * W + 16);    // per wave, for store_tile_coalesced
+  static_assert(NST >= 4 && (NST - 2) * LOADS < 64 && 4 * OUT_REGION <= NST * BUF && NST * BUF * OCC <= 160 * 1024, "stages");
+  __shared__ __attribute__((aligned(1024))) char lds[NST * BUF];
+  const int nI = (g.I + N - 1) / N, nJ = (g.J + N - 1) / N, total = g.nz * nI * nJ;
   // XCD x owns the x-th eighth of the tile list (as in linear_pipe.hip: groups of kGI tile rows, down the group first)
   const int wg = (int)(blockIdx.x & 7) * ((total + 7) >> 3) + (int)(blockIdx.x >> 3);
   if (wg >= min(total, ((int)(blockIdx.x & 7) + 1) * ((total + 7) >> 3))) return;
-  const int tid = threadIdx.x, lane = tid & 63, ic = lane & 31, hh = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wi = wave % C::NWI, wj = wave / C::NWI;
-  const int zz = wg / (nI * nJ), id = wg - zz * (nI * nJ);
-  const int grp = id / (kGI * nJ), it_first = grp * kGI, gs = min(nI - it_first, kGI);
-  const int rem = id - grp * (kGI * nJ), jt = rem / gs, it = it_first + (rem - jt * gs);
-  const int i0 = it * kTI, j0 = jt * kTJ;
+  const int lane = threadIdx.x & 63, ic = lane & 31, hh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wi = wave & 1, wj = wave >> 1;
+  const Quotient zq = divide((unsigned)wg, g.by_set), grp = divide(zq.r, g.by_group);
+  const int zz = (int)zq.q, it_first = (int)grp.q * kGI;
+  const Quotient jt = nI - it_first >= kGI ? Quotient{grp.r / kGI, grp.r % kGI} : divide(grp.r, g.by_rest);
+  const int i0 = (it_first + (int)jt.r) * N, j0 = (int)jt.q * N;
   const int nct = (g.C + kBK - 1) / kBK, ntot = g.csets * nct;
-  const int t_begin = PARTIAL ? (int)((long long)zz * ntot / g.splits) : 0;
-  const int t_end = PARTIAL ? (int)((long long)(zz + 1) * ntot / g.splits) : ntot;
+  const int t_begin = PARTIAL ? (int)divide((unsigned)zz * (unsigned)ntot, g.by_splits).q : 0;  // splits <= 32, ntot <= 2^26
+  const int t_end = PARTIAL ? (int)divide((unsigned)(zz + 1) * (unsigned)ntot, g.by_splits).q : ntot;
   const bool two = g.csets == 2;  // grad W: contraction over both row sets
   const int clast = g.C - (nct - 1) * kBK;
-  const unsigned lds0 = lds_addr_of(lds);
   const unsigned pitchP = (unsigned)(g.ldP * 2), pitchQ = (unsigned)(g.ldQ * 2);
-  typename TP::Offs op_full, op_last;
-  typename TQ::Offs oq_full, oq_last;
-  if (PTR) {
-    const typename TP::Lane l = TP::lane_setup(min(g.I - i0, kTI), wave, lane);
-    op_full = TP::offsets(l, pitchP, kBK);
-    op_last = TP::offsets(l, pitchP, clast);
-  } else {
-    op_full = op_last = TP::offsets(TP::lane_setup(32, wave, lane), pitchP, min(g.I - i0, kTI));
-  }
-  if (QTR) {
-    const typename TQ::Lane l = TQ::lane_setup(min(g.J - j0, kTJ), wave, lane);
-    oq_full = TQ::offsets(l, pitchQ, kBK);
-    oq_last = TQ::offsets(l, pitchQ, clast);
-  } else {
-    oq_full = oq_last = TQ::offsets(TQ::lane_setup(32, wave, lane), pitchQ, min(g.J - j0, kTJ));
-  }
-  const typename TP::RAddr rp = TP::raddr(ic, hh);
-  const typename TQ::RAddr rq = TQ::raddr(ic, hh);
-  const TrNat<TP> tp = TrNat<TP>::make(ic, hh);
-  const TrNat<TQ> tq = TrNat<TQ>::make(ic, hh);
-  f32x16 acc[kWI][kWJ];
+  const int validP = min(g.I - i0, N), validQ = min(g.J - j0, N);
+  const unsigned lds0 = lds_addr_of(lds);
+  OP op;
+  OQ oq;
+  op.setup(lds0, wi, wave, lane, pitchP);
+  oq.setup(lds0 + HALF, wj, wave, lane, pitchQ);
+  // accumulators start from bias x 1 as one more product, exactly the bias (row set 0 only): block b's column 32 b + ic
+  f32x16 acc[W][W];
+  unsigned bias_bits[W];
   {
-    const bool with_bias = !PARTIAL && g.bias != nullptr && zz == 0;
-    const int jw = j0 + wj * (kWJ * 32);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16*>(g.bias), 0, !PARTIAL && g.bias != nullptr && zz == 0 ? g.J * 2 : 0, 0x00027000);
 #pragma unroll
-    for (int b = 0; b < kWJ; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int j = jw + b * 32 + drow(r, hh);
-        const float v = with_bias && j < g.J ? (float)g.bias[j] : 0.f;
-#pragma unroll
-        for (int a = 0; a < kWI; ++a) acc[a][b][r] = v;
-      }
+    for (int b = 0; b < W; ++b) {
+      const unsigned off = (unsigned)(j0 + (wj * W + b) * 32 + ic) * 2u;
+      bias_bits[b] = PARTIAL ? 0u : (unsigned)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)(hh == 0 ? off : kNowhere), 0, 0);
+    }
   }
-  // all wave-loads of contraction tile t (beyond the end: the last one again, never used) into the stage at `buf`
-  auto issue = [&](int t, unsigned buf) {
-    t = min(t, t_end - 1);
+  // The loads' cursor: descriptors (first byte, size for the bounds check) and lane offsets of contraction tile c_t.  Within a
+  // set a move is three additions per operand; c_plain counts the moves left until something else is due.
+  u32x4 sp, sq;
+  unsigned vp = op.voff[0], vq = oq.voff[0];
+  int c_t, c_plain = 0;
+  auto place = [&](int t) {
+    c_t = t;
     const int set = two && t >= nct ? 1 : 0, ct = t - set * nct;
     const long long c0 = (long long)ct * kBK;
     const bool last = ct == nct - 1;
-    const bf16* pb = g.P[two ? set : PARTIAL ? 0 : zz] + (PTR ? c0 * g.ldP + i0 : (long long)i0 * g.ldP + c0);
-    const bf16* qb = g.Q[set] + (QTR ? c0 * g.ldQ + j0 : (long long)j0 * g.ldQ + c0);
-    const int half2 = (last && clast <= 32) ? 0 : 32;
-#pragma unroll
-    for (int x = 0; x < TP::IPW; ++x) {
-      TP::issue_at(PTR && last ? op_last.o[x] : op_full.o[x], x, pb, buf, wave);
-      if (!PTR) TP::issue_at(op_full.o[x], x, pb + half2, buf + TP::BYTES, wave);
-    }
-#pragma unroll
-    for (int x = 0; x < TQ::IPW; ++x) {
-      TQ::issue_at(QTR && last ? oq_last.o[x] : oq_full.o[x], x, qb, buf + P_BYTES, wave);
-      if (!QTR) TQ::issue_at(oq_full.o[x], x, qb + half2, buf + P_BYTES + TQ::BYTES, wave);
+    const bf16 *p = g.P[two ? set : PARTIAL ? 0 : zz], *q = g.Q[set];
+    const unsigned rows = (unsigned)((last ? clast : kBK) - 1);
+    if (PTR) sp = descriptor((unsigned long long)(uintptr_t)(p + c0 * g.ldP + i0), rows * pitchP + (unsigned)validP * 2u);
+    else sp = descriptor((unsigned long long)(uintptr_t)(p + (long long)i0 * g.ldP + c0), (unsigned)(validP - 1) * pitchP + (unsigned)(g.C - (int)c0) * 2u);
+    if (QTR) sq = descriptor((unsigned long long)(uintptr_t)(q + c0 * g.ldQ + j0), rows * pitchQ + (unsigned)validQ * 2u);
+    else sq = descriptor((unsigned long long)(uintptr_t)(q + (long long)j0 * g.ldQ + c0), (unsigned)(validQ - 1) * pitchQ + (unsigned)(g.C - (int)c0) * 2u);
+    const unsigned cut = last && clast <= 32 ? kNowhere : 0u;  // row access: the second half of a set's last tile is absent
+    if (!PTR) vp = op.voff[0] | (op.half & cut);
+    if (!QTR) vq = oq.voff[0] | (oq.half & cut);
+    if (t >= t_end) sp[2] = sq[2] = 0;  // beyond the end: loads that fetch nothing, so that the count of loads in flight stays the same
+    // plain moves: up to the tile before the set's last one, and before the end
+    c_plain = min(nct - 2 - ct, t_end - 1 - t);
+  };
+  auto move = [&]() {
+    if (c_plain > 0) {
+      --c_plain;
+      ++c_t;
+      sp = descriptor(((unsigned long long)sp[1] << 32 | sp[0]) + (PTR ? 64ull * pitchP : 128ull), PTR ? sp[2] : sp[2] - 128u);
+      sq = descriptor(((unsigned long long)sq[1] << 32 | sq[0]) + (QTR ? 64ull * pitchQ : 128ull), QTR ? sq[2] : sq[2] - 128u);
+    } else if (c_t < t_end) {
+      place(c_t + 1);
     }
   };
+  // wave-load x of the cursor's tile into the stage at `to`
+  auto issue = [&](unsigned to, int x) __attribute__((always_inline)) {
+    const unsigned l = lds0 + to + (unsigned)wave * 1024u;
+    if (x < OP::LOADS) load_lds(sp, vp, (unsigned)(x * OP::ROWS_STEP) * pitchP, l, x * 4096);
+    else load_lds(sq, vq, (unsigned)((x - OP::LOADS) * OQ::ROWS_STEP) * pitchQ, l, (int)HALF + (x - OP::LOADS) * 4096);
+  };
+  bf16x8 pf[2][kBK / 16][W], qf[2][kBK / 16][W];
+  auto fetch = [&](int set, int kk, unsigned at) {
 #pragma unroll
-  for (int x = 0; x < NST - 1; ++x) issue(t_begin + x, lds0 + x * BUF);
-  int n = 0;
-  for (int t = t_begin; t < t_end; ++t) {
-    dma_wait_keep<(NST - 2) * LOADS>();  // this wave's share of tile t has landed
-    const int ct = two && t >= nct ? t - nct : t;
-    if (ct == nct - 1 && clast < kBK) {  // entries beyond the set's end were fetched as copies: zeros instead
-      char* pt = lds + n * BUF;
+    for (int a = 0; a < W; ++a) pf[set][kk][a] = op.frag(a, kk, at);
 #pragma unroll
-      for (int x = 0; x < TP::IPW; ++x) {
-        const int pos = (wave + x * kNW) * 64 + lane;
-        if (PTR) {
-          if (pos / TP::PCH >= clast) *reinterpret_cast<uint4*>(pt + pos * 16) = make_uint4(0u, 0u, 0u, 0u);
-        } else if (clast <= 32) {
-          *reinterpret_cast<uint4*>(pt + TP::BYTES + pos * 16) = make_uint4(0u, 0u, 0u, 0u);
-        }
-      }
+    for (int b = 0; b < W; ++b) qf[set][kk][b] = oq.frag(b, kk, at);
+  };
+  place(t_begin);
+  for (unsigned x = 0; x < NST - 1; ++x) {
+#pragma unroll
+    for (int y = 0; y < LOADS; ++y) issue(x * BUF, y);
+    move();
+  }
+  {
+    const bf16x8 one = __builtin_bit_cast(bf16x8, u32x4{hh == 0 ? 0x3f80u : 0u, 0u, 0u, 0u});
+#pragma unroll
+    for (int b = 0; b < W; ++b) {
+      const bf16x8 bv = __builtin_bit_cast(bf16x8, u32x4{bias_bits[b], 0u, 0u, 0u});
+#pragma unroll
+      for (int a = 0; a < W; ++a) acc[a][b] = mfma(bv, one, zero16());
     }
-    __syncthreads();  // it is there for everyone, and everyone is done with tile t-1, whose stage is refilled now
-    const int nf = n == 0 ? NST - 1 : n - 1;
-    issue(t + NST - 1, lds0 + nf * BUF);
-    const char* sp = lds + n * BUF;
-    const char* sq = sp + P_BYTES;
+  }
+  dma_wait_keep<(NST - 2) * LOADS>();
+  barrier();
+#pragma unroll
+  for (int kk = 0; kk < kBK / 16; ++kk) fetch(0, kk, 0);
+  unsigned at = 0;  // tile t's stage
+  auto turn = [&](int t, int set) {
+    const unsigned next = at + BUF == NST * BUF ? 0 : at + BUF, before = at == 0 ? (NST - 1) * BUF : at - BUF;
+    dma_wait_keep<(NST - 3) * LOADS>();
+    barrier();  // tile t + 1 is there for everyone, and everyone has tile t - 1 in registers: its stage is refilled now
 #pragma unroll
     for (int kk = 0; kk < kBK / 16; ++kk) {
-      bf16x8 pf[kWI], qf[kWJ];
+      fetch(set ^ 1, kk, next);
 #pragma unroll
-      for (int a = 0; a < kWI; ++a)
-        pf[a] = PTR ? tp.frag(sp, kk, wi * kWI + a) : TP::frag_row(sp + (kk >> 1) * TP::BYTES, rp, wi * kWI + a, kk & 1);
+      for (int x = kk * LOADS / 4; x < (kk + 1) * LOADS / 4; ++x) issue(before, x);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int b = 0; b < kWJ; ++b)
-        qf[b] = QTR ? tq.frag(sq, kk, wj * kWJ + b) : TQ::frag_row(sq + (kk >> 1) * TQ::BYTES, rq, wj * kWJ + b, kk & 1);
+      for (int a = 0; a < W; ++a)
 #pragma unroll
-      for (int a = 0; a < kWI; ++a)
-#pragma unroll
-        for (int b = 0; b < kWJ; ++b) acc[a][b] = mfma(qf[b], pf[a], acc[a][b]);
+        for (int b = 0; b < W; ++b) acc[a][b] = mfma(qf[set][kk][b], pf[set][kk][a], acc[a][b]);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    n = n + 1 == NST ? 0 : n + 1;
+    move();
+    at = next;
+  };
+  for (int t = t_begin; t < t_end; t += 2) {
+    turn(t, 0);
+    if (t + 1 < t_end) turn(t + 1, 1);
   }
-  const int jw = j0 + wj * (kWJ * 32);
+  const int jw = j0 + wj * (W * 32);
   if (PARTIAL) {
-    store_partial<kWI, kWJ>(g, acc, zz, i0 + wi * kWI * 32, jw, ic, hh);
+    store_partial<W, W>(g, acc, zz, i0 + wi * W * 32, jw, ic, hh);
     dma_wait();  // (no load may land in LDS that the next workgroup owns)
     return;
   }
@@ -222,8 +208,8 @@ __global__ __launch_bounds__(C::NT, C::OCC) void gemm_small_kernel(GemmArgs g) {
   if (jw < g.J) {
     const unsigned lw = lds0 + (unsigned)wave * OUT_REGION;
 #pragma unroll
-    for (int a = 0; a < kWI; ++a)
-      store_tile_coalesced<kWJ>(lw, g.out[zz] + jw, g.ldo, i0 + (wi * kWI + a) * 32, g.I, g.J - jw, acc[a], 1.f, lane);
+    for (int a = 0; a < W; ++a)
+      store_tile_coalesced<W>(lw, g.out[zz] + jw, g.ldo, i0 + (wi * W + a) * 32, g.I, g.J - jw, acc[a], 1.f, lane);
   }
 }
 
@@ -365,25 +351,21 @@ __global__ __launch_bounds__(1024) void colsum_direct_kernel(const bf16* __restr
 }
 constexpr int kDirectRows = 2048;  // up to this many rows the column sums take one launch
 
-// The tile shapes in use
-using Cfg128 = Cfg<2, 2, 2, 2, 3, 1>;  // 128 x 128, four waves
-using Cfg64 = Cfg<2, 2, 1, 1, 4, 2>;   // 64 x 64, four waves
-template <class C>
-constexpr bool shape_is(int c) { return C::TI == kTileI[c] && C::TJ == kTileJ[c]; }
-static_assert(shape_is<Cfg128>(k128) && shape_is<Cfg64>(k64), "the plan's tiles");
-static_assert(Cfg128::NT == kSmallThreads && Cfg64::NT == kSmallThreads, "the plan's limit");
+static_assert(kTileI[k128] == 128 && kTileJ[k128] == 128 && kTileI[k64] == 64 && kTileJ[k64] == 64 && kBK == 64, "the plan's tiles");
 
 int bias_chunks(int R) {
   const int c = (R + 63) / 64;
   return c > 256 ? 256 : c;
 }
 
-// Launches a product with tile shape c (128 or 64).
+// Launches a product with tile shape c (128 or 64).  Stages: more of them (10 at 64 x 64 with one workgroup per CU, 5 at 128 x 128)
+// gain nothing, the loads are there in time, and cost 0.5 - 1 us of start-up; 4 at 64 x 64 lose 10 % on long contractions.
 template <bool PTR, bool QTR, bool PARTIAL>
-hipError_t launch_small(int c, const GemmArgs& g, hipStream_t st) {
-  const dim3 grid((unsigned)small_workgroups(g.nz * tiles_of(c, g.I, g.J)));
-  if (c == k64) hipLaunchKernelGGL((gemm_small_kernel<PTR, QTR, PARTIAL, Cfg64>), grid, dim3(Cfg64::NT), 0, st, g);
-  else hipLaunchKernelGGL((gemm_small_kernel<PTR, QTR, PARTIAL, Cfg128>), grid, dim3(Cfg128::NT), 0, st, g);
+hipError_t launch_small(int c, GemmArgs g, hipStream_t st) {
+  const dim3 grid((unsigned)small_workgroups(g.nz * tiles_of(c, g.I, g.J))), block(kSmallThreads);
+  g.set_divisors(c, PARTIAL);
+  if (c == k128) hipLaunchKernelGGL((gemm_small_kernel<PTR, QTR, PARTIAL, 128, 4, 1>), grid, block, 0, st, g);
+  else hipLaunchKernelGGL((gemm_small_kernel<PTR, QTR, PARTIAL, 64, 5, 2>), grid, block, 0, st, g);
   return hipGetLastError();
 }
 

@@ -33,80 +33,8 @@
 namespace tvm {
 namespace {
 
-typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
-
 constexpr int kWI = 4;                         // 32-row blocks of a wave
 constexpr unsigned kPTile = 32768;             // LDS: three P tiles, then two Q tiles
-constexpr unsigned kNowhere = 0x80000000u;     // a byte offset that every bounds check refuses
-
-// One operand's contraction tile of 64 entries x N output rows (or columns).
-//   row access: [N][64], 128 bytes a row; 16-byte chunk c of row s sits at position c ^ ((s >> 1) & 7) of its row
-//   transposed: [64][N], 2 N bytes a row; 64-byte group g of row s sits at g ^ (s & 3) (N = 256) or g ^ ((s >> 1) & 1) (N = 192)
-// Both fragment reads (16-byte reads of 16 consecutive rows, the transposing read of 4 rows x 64 bytes) then touch every
-// bank once, without padding, and a wave-load fetches whole 128-byte lines.
-template <bool TR, int N>
-struct Operand {
-  static constexpr int LOADS = N / 32;                     // wave-loads per wave and tile (four waves)
-  static constexpr int NV = TR && N == 192 ? 3 : 1;        // different lane offsets among them
-  static constexpr int ROWS_STEP = TR ? (N == 192 ? 32 : 8) : 32;  // rows from load x to load x + NV
-  static constexpr int PITCH = TR ? 2 * N : 128;
-  static constexpr int NB = N / 64;                        // blocks of 32 per wave (two waves side by side)
-  static constexpr int NA = TR ? NB : 4;                   // read addresses: per block, or per contraction step
-  unsigned voff[NV];
-  unsigned half;                                           // row access: kNowhere for lanes of the tile's second half
-  unsigned addr[NA];
-  __device__ __forceinline__ static int group(int g, int s) { return N == 192 ? g ^ ((s >> 1) & 1) : g ^ (s & 3); }
-  __device__ __forceinline__ void setup(unsigned lds, int w, int wave, int lane, unsigned pitch) {
-    const int ic = lane & 31, hh = lane >> 5;
-    half = 0;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const int pos = (wave + 4 * v) * 64 + lane;
-      if (TR) {
-        const int s = pos / (N / 8), c = pos - s * (N / 8);
-        voff[v] = (unsigned)s * pitch + (unsigned)(group(c >> 2, s) * 4 + (c & 3)) * 16u;
-      } else {
-        const int s = pos >> 3, c = (pos & 7) ^ ((s >> 1) & 7);
-        voff[v] = (unsigned)s * pitch + (unsigned)c * 16u;
-        half = c >= 4 ? kNowhere : 0u;
-      }
-    }
-#pragma unroll
-    for (int n = 0; n < NA; ++n) {
-      if (TR) {
-        const int i = ic & 15, y = 2 * (ic >> 4) + ((i & 3) >> 1), r = 8 * hh + (i >> 2);
-        addr[n] = lds + (unsigned)(r * PITCH + group(w * NB + n, r) * 64 + y * 16 + (i & 1) * 8);
-      } else {
-        addr[n] = lds + (unsigned)((w * NB * 32 + ic) * 128 + ((2 * n + hh) ^ ((ic >> 1) & 7)) * 16);
-      }
-    }
-  }
-  // fragment of block b, contraction step kk
-  __device__ __forceinline__ bf16x8 frag(int b, int kk) const {
-    if (TR) return lds_read_tr(addr[b], addr[b] + 4 * PITCH, kk * 16 * PITCH);
-    return lds_read16(addr[kk], b * 32 * 128);
-  }
-  __device__ __forceinline__ void move(unsigned by) {
-#pragma unroll
-    for (int n = 0; n < NA; ++n) addr[n] += by;
-  }
-};
-
-// Bounds-checked asynchronous global->LDS load, 16 bytes per lane: lanes whose offset is not below the descriptor's size
-// write zeros.  (The vector addition is also the wait state due between the scalar write of M0 and the load.)
-__device__ __forceinline__ void load_lds(u32x4 srd, unsigned voff, unsigned add, unsigned lds, int imm) {
-  unsigned t;
-  asm volatile(
-      "s_add_u32 m0, %1, %5\n\t"
-      "v_add_u32 %0, %2, %3\n\t"
-      "buffer_load_dwordx4 %0, %4, 0 offen lds"
-      : "=&v"(t)
-      : "s"(lds), "s"(add), "v"(voff), "s"(srd), "n"(imm)
-      : "memory", "m0", "scc");
-}
-__device__ __forceinline__ u32x4 descriptor(unsigned long long base, unsigned bytes) {
-  return u32x4{(unsigned)base, (unsigned)(base >> 32), bytes, 0x00027000u};
-}
 
 // Eight accumulator values, rounded to bf16.  (Assembly: plain conversions of all accumulators would be hoisted to one place;
 // reads first, so that no conversion waits for the one before it.)
@@ -128,20 +56,6 @@ __device__ __forceinline__ void acc_to_bf16(unsigned& r0, unsigned& r1, unsigned
       "v_cvt_pk_bf16_f32 %3, %3, %7"
       : "=&v"(r0), "=&v"(r1), "=&v"(r2), "=&v"(r3), "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3)
       : "a"(a0), "a"(a1), "a"(a2), "a"(a3), "a"(a4), "a"(a5), "a"(a6), "a"(a7));
-}
-
-struct Quotient {
-  unsigned q, r;
-};
-// n / d for n < 2^31, in scalar registers: the estimate from the reciprocal is at most one too small.
-__device__ __forceinline__ Quotient divide(unsigned n, Divisor by) {
-  Quotient o{__umulhi(n, by.m), 0u};
-  o.r = n - o.q * by.d;
-  if (o.r >= by.d) {
-    o.r -= by.d;
-    ++o.q;
-  }
-  return o;
 }
 
 // Slots of a contraction step: slot m is the gap behind its product m.  The NF fragment reads are spread over the slots from
@@ -525,11 +439,7 @@ int persistent_grid(int tiles) {
 }
 template <bool PTR, bool QTR, bool PARTIAL>
 hipError_t launch(int shape, GemmArgs g, hipStream_t st) {
-  const unsigned nI = (unsigned)((g.I + kTileI[shape] - 1) / kTileI[shape]), nJ = (unsigned)((g.J + kTileJ[shape] - 1) / kTileJ[shape]);
-  g.by_set = Divisor::of(nI * nJ);
-  g.by_group = Divisor::of(kGI * nJ);
-  g.by_rest = Divisor::of(nI % kGI == 0 ? 1u : nI % kGI);
-  g.by_splits = Divisor::of((unsigned)(PARTIAL ? g.splits : 1));
+  g.set_divisors(shape, PARTIAL);
   const dim3 grid(persistent_grid((int)(g.nz * tiles_of(shape, g.I, g.J))));
   if (shape == k192) hipLaunchKernelGGL((gemm_pipe_kernel<PTR, QTR, PARTIAL, 3>), grid, dim3(256), 0, st, g);
   else hipLaunchKernelGGL((gemm_pipe_kernel<PTR, QTR, PARTIAL, 4>), grid, dim3(256), 0, st, g);

@@ -25,18 +25,18 @@ inline bool grid_fits(int c, long long tiles) { return c < k128 || small_workgro
 // 65536 rows, widths 32 ... 4608 either way.  From a contraction of 288 on the choice is 0.2 % behind the fastest shape on
 // average (forward; at most 9 %), below, where nearly all of a product is start-up and stores, 4 %; grad x 0.2 and 0.3 %.
 // Some of the times (us; 256 | 192 | 128 | 64):
-//   forward, 500 x 768 -> 768:       18 |  15 |  12 |   8     few tiles: small ones fill the chip
-//   forward, 1024 x 1152 -> 1152:    24 |  20 |  16 |  18
-//   forward, 2048 x 768 -> 2304:     23 |  20 |  33 |  35     the small shapes' fixed part, round after round
-//   forward, 2048 x 512 -> 3072:     19 |  20 |  28 |  38
-//   forward, 16384 x 64 -> 1152:     20 |  18 |  39 |  48     short contraction: first operands and stores
-//   forward, 16384 x 768 -> 3072:   135 | 140 | 256 | 345
-//   forward, 8192 x 4608 -> 1152:   183 | 152 | 236 | 288     long contraction, and 1152 = 6 x 192: no padded columns
+//   forward, 500 x 768 -> 768:       18 |  15 |  11 |   6     few tiles: small ones fill the chip
+//   forward, 1024 x 1152 -> 1152:    24 |  20 |  14 |  15
+//   forward, 2048 x 768 -> 2304:     23 |  20 |  29 |  29     the small shapes' fixed part, round after round
+//   forward, 2048 x 512 -> 3072:     19 |  20 |  25 |  32
+//   forward, 16384 x 64 -> 1152:     20 |  18 |  33 |  43     short contraction: first operands and stores
+//   forward, 16384 x 768 -> 3072:   135 | 140 | 230 | 283
+//   forward, 8192 x 4608 -> 1152:   183 | 152 | 202 | 244     long contraction, and 1152 = 6 x 192: no padded columns
 struct ShapeCost {
   int start, fixed, step;
 };
-constexpr ShapeCost kCostRow[kShapes] = {{0, 6943, 1600}, {1984, 6784, 1153}, {1762, 5408, 641}, {2165, 2397, 277}};
-constexpr ShapeCost kCostTr[kShapes] = {{4487, 11999, 1106}, {0, 10232, 804}, {3294, 4464, 598}, {3385, 2146, 198}};
+constexpr ShapeCost kCostRow[kShapes] = {{0, 7018, 1600}, {2454, 6784, 1088}, {1523, 4770, 539}, {2305, 2000, 210}};
+constexpr ShapeCost kCostTr[kShapes] = {{3632, 13659, 1047}, {806, 10481, 823}, {3535, 4645, 458}, {3090, 2010, 162}};
 inline long long product_ns(const ShapeCost& c, long long tiles, int steps) {
   return c.start + (tiles + 255) / 256 * (c.fixed + (long long)steps * c.step);
 }
@@ -77,15 +77,15 @@ inline int dw_splits(int F, int K, int R) {
 // grad W: time of `tiles` output tiles of shape c over `steps` contraction tiles each, in units of about 17 ns (the 256 x 256
 // shape takes 1.2 us per contraction tile on an idle chip, 1.6 on a full one).
 inline long long dw_cost(int c, long long tiles, int steps) {
-  constexpr int kStep[kShapes] = {86, 72, 48, 28}, kFixed[kShapes] = {75, 100, 70, 66};
+  constexpr int kStep[kShapes] = {108, 86, 46, 27}, kFixed[kShapes] = {49, 87, 58, 54};
   return (tiles + 255) / 256 * ((long long)steps * kStep[c] + kFixed[c]);
 }
 // Shape and number of contraction splits of grad W: what the partial tiles cost on top is two passes over them at
 // 5 TB/s and a launch (3 us).  The 128 and 64 shapes write bf16 directly when there is one split.  Never more splits
 // than dw_splits: the workspace is sized for those.
-// (us of grad W alone, 256 | 192 | 128 | 64: R 500 768 -> 768 19 | 17 | 16 | 10; R 4096 768 -> 3072 53 | 48 | 73 | 122; R 16384
-// 1152 -> 3456 252 | 220 | 352 | 685.  At 189 layers of 288 ... 4608 and R = 64 ... 16384 the choice is 2 % behind the fastest
-// shape on average.)
+// (us of grad W alone, 256 | 192 | 128 | 64: R 500 768 -> 768 19 | 17 | 16 | 7; R 4096 768 -> 3072 53 | 48 | 62 | 71; R 16384
+// 1152 -> 3456 252 | 220 | 292 | 503.  At 189 layers of 288 ... 4608 and R = 64 ... 16384 the choice is 5 % behind the fastest
+// shape on average: it is late to turn to 64 x 64, by up to 5 us.)
 struct DwPlan {
   int shape, splits;
 };

@@ -20,9 +20,9 @@ LINEAR = [
 LINEAR_PIPE = [
     ((4097, 32, 1184), (256, 64, 64)),
     ((8191, 64, 416), (256, 64, 64)),
-    ((66000, 32, 32), (256, 64, 64)),
+    ((33025, 32, 128), (256, 64, 64)),
     ((5000, 96, 800), (256, 64, 128)),
-    ((33025, 96, 96), (192, 128, 64)),
+    ((33025, 96, 160), (192, 128, 64)),
     ((6145, 608, 352), (192, 192, 128)),
     ((12289, 768, 800), (192, 192, 192)),
     ((3001, 4640, 1184), (192, 256, 192)),
