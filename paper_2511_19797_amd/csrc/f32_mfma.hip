@@ -19,10 +19,10 @@
 //   * Fixed-side operands sit in LDS in the order the lanes read them (one 16-byte read per four contraction steps).
 //   * Streamed rows are read with bounds-checked buffer loads: rows beyond the end and columns beyond the head dim
 //     read as zero.
-// A float32 training step at B4 H12 N256 d64 (8.5 GFLOP): 130 us, 65 TFLOP/s by the algorithmic
-// count and 84 by the executed one (the backward's two kernels both form the score tiles), against 3590 us on the plain-ALU
-// kernels, whose lanes each walked a row of their own with 4-byte loads.  The smallest call (B1 H2 N64 d32), where launches
-// and latency count: 54 us against 76.
+// A float32 training step at B4 H12 N256 d64 (8.5 GFLOP): 105 us (130 before the backward's loads were put in stages), 81
+// TFLOP/s by the algorithmic count and 104 by the executed one (the backward's two kernels both form the score tiles), against
+// 3590 us on the plain-ALU kernels, whose lanes each walked a row of their own with 4-byte loads.  The smallest call (B1 H2
+// N64 d32), where launches and latency count: 23 us.
 #include "f32_mfma.h"
 #include "mfma_tiles.h"
 
@@ -51,6 +51,9 @@ struct Head {
   }
   __device__ __forceinline__ f32x4 ld4(unsigned off) const {
     return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+  }
+  __device__ __forceinline__ float ld1(unsigned off) const {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
   }
   __device__ __forceinline__ f32x2 ld2(unsigned off) const {
     return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
@@ -281,9 +284,15 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(Shape s, const float* _
 }
 
 // Query side of the backward: dq, dtq of 16 queries, and Step 1's row scalars for the key side behind it.
+// The loads are put in stages, each sent off a group of products before it is used (the scheduling barriers hold the
+// compiler to that), so that few fragments live at once: 251 registers instead of 280 at DP = 128, two waves per SIMD
+// instead of one.  With a tangent there are products enough behind the next tile's first rows to load them one tile ahead.
+// Both upstream gradients, B2 H16 N256 d128: 62 us before, 48 now; B2 H8 N1024 d64: 185 before, 167 now.  Without
+// the tangent there is little to put behind a stage's loads: B4 H12 N256 d64 18.4 us with all loads first, 18.8 in stages
+// and 20.2 with the next tile's rows ahead, so there all loads come first.
 // MODE as in BwdArgs: 0 both upstream gradients, 1 gO only, 2 gTO only.
 template <int DP, int MODE>
-__global__ __launch_bounds__(256, DP <= 64 ? 2 : 1) void bwd_row_f32_kernel(
+__global__ __launch_bounds__(256, MODE == 1 ? (DP <= 64 ? 2 : 1) : DP <= 32 ? 4 : DP <= 64 ? 3 : 2) void bwd_row_f32_kernel(
     Shape s, const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     const float* __restrict__ tq, const float* __restrict__ tk, const float* __restrict__ tv, const float* __restrict__ o,
     const float* __restrict__ to, const float* __restrict__ lse, const float* __restrict__ stats,
@@ -350,30 +359,60 @@ __global__ __launch_bounds__(256, DP <= 64 ? 2 : 1) void bwd_row_f32_kernel(
   typename G::Acc aq = G::zero(), atq = G::zero();
   __syncthreads();
   const float dsig_i = rows[0][i], sig1_i = rows[1][i];
+  typename G::Rows kf, vf, tkf, tvf;
+  if constexpr (TAN) {
+    const unsigned first = wave * kR < s.N ? (unsigned)(wave * kR) * pitch : 0u;
+    kf = geo.rows(hk, first);
+    tkf = geo.rows(htk, first);
+  }
   for (int j0 = wave * kR; j0 < s.N; j0 += kNW * kR) {
     const unsigned tile = (unsigned)j0 * pitch;
-    typename G::Rows kf = geo.rows(hk, tile), vf = geo.rows(hv, tile), tkf, tvf;
-    if constexpr (TAN) {
-      tkf = geo.rows(htk, tile);
-      tvf = geo.rows(htv, tile);
-    }
-    typename G::Cols kc = geo.cols(hk, tile, pitch), tkc;
-    if constexpr (TAN) tkc = geo.cols(htk, tile, pitch);
+    const unsigned next = j0 + kNW * kR < s.N ? tile + (unsigned)(kNW * kR) * pitch : tile;
+    if constexpr (!TAN) kf = geo.rows(hk, tile);
+    vf = geo.rows(hv, tile);
+    typename G::Cols kc, tkc;
+    if constexpr (!TAN) kc = geo.cols(hk, tile, pitch);
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     f32x4 z = zero, za = zero, zb = zero, da = zero, db = zero, e = zero;
+    if constexpr (TAN) {
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int t = 0; t < G::NT; ++t) {
-      const f32x4 fq = fixed[t * 64 + lane];
-      TVM_F32_STEP(z, kf.t[t], fq);
-      if constexpr (TAN) {
-        const f32x4 ftq = fixed[G::FIX + t * 64 + lane], ftg = fixed[3 * G::FIX + t * 64 + lane];
+      for (int t = 0; t < G::NT; ++t) {
+        const f32x4 fq = fixed[t * 64 + lane], ftq = fixed[G::FIX + t * 64 + lane];
+        TVM_F32_STEP(z, kf.t[t], fq);
         TVM_F32_STEP(za, kf.t[t], ftq);
         TVM_F32_STEP(zb, tkf.t[t], fq);
-        TVM_F32_STEP(db, tvf.t[t], ftg);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      tvf = geo.rows(htv, tile);
+      kc = geo.cols(hk, tile, pitch);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < G::NT; ++t) {
+        const f32x4 ftg = fixed[3 * G::FIX + t * 64 + lane];
+        if constexpr (GO) {
+          const f32x4 fg = fixed[2 * G::FIX + t * 64 + lane];
+          TVM_F32_STEP(da, vf.t[t], fg);
+        }
         TVM_F32_STEP(e, vf.t[t], ftg);
       }
-      if constexpr (GO) {
-        const f32x4 fg = fixed[2 * G::FIX + t * 64 + lane];
+      __builtin_amdgcn_sched_barrier(0);
+      tkc = geo.cols(htk, tile, pitch);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < G::NT; ++t) {
+        const f32x4 ftg = fixed[3 * G::FIX + t * 64 + lane];
+        TVM_F32_STEP(db, tvf.t[t], ftg);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      kf = geo.rows(hk, next);
+      tkf = geo.rows(htk, next);
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
+#pragma unroll
+      for (int t = 0; t < G::NT; ++t) {
+        const f32x4 fq = fixed[t * 64 + lane], fg = fixed[2 * G::FIX + t * 64 + lane];
+        TVM_F32_STEP(z, kf.t[t], fq);
         TVM_F32_STEP(da, vf.t[t], fg);
       }
     }
@@ -407,8 +446,14 @@ __global__ __launch_bounds__(256, DP <= 64 ? 2 : 1) void bwd_row_f32_kernel(
 }
 
 // Key side: dk, dtk, dv, dtv of 16 keys, the queries streamed.
+// The loads are put in stages here too: the products of q and tq run while the rows of gO and gTO come in, and so on.  With
+// all rows of a tile loaded at once and 64-bit addresses for its row scalars the kernel took 200 registers at DP = 64, two
+// waves per SIMD: a short sequence's 768 workgroups were a full round and a half-empty one.  It takes 168 now (DP = 96: 243,
+// was 304), one wave more.  Both upstream gradients: B4 H12 N256 d64 75.6 us before, 51 now (its products alone: 31); B2 H8
+// N1024 d64 278 and 224; B2 H16 N256 d96 66 and 48, d128 82 and 69.  At DP = 128 two waves would spill 24
+// registers and cost 73 us.
 template <int DP, int MODE>
-__global__ __launch_bounds__(256, DP <= 64 ? 2 : 1) void bwd_col_f32_kernel(
+__global__ __launch_bounds__(256, DP <= 64 ? 3 : DP <= 96 ? 2 : 1) void bwd_col_f32_kernel(
     Shape s, const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     const float* __restrict__ tq, const float* __restrict__ tk, const float* __restrict__ tv, const float* __restrict__ lse,
     const float* __restrict__ stats, const float* __restrict__ gO, const float* __restrict__ gTO,
@@ -430,6 +475,9 @@ __global__ __launch_bounds__(256, DP <= 64 ? 2 : 1) void bwd_col_f32_kernel(
   const Head hq = Head::make(q + qbase, s.M, pitch, s.D);
   const Head htq = TAN ? Head::make(tq + qbase, s.M, pitch, s.D) : hq;
   const Head hg = GO ? Head::make(gO + qbase, s.M, pitch, s.D) : hq, htg = TAN ? Head::make(gTO + qbase, s.M, pitch, s.D) : hq;
+  const long long rbase = (long long)bh * s.M;
+  const Head hl = Head::make(lse + rbase, s.M, 4, 1), hd = Head::make(dsig + rbase, s.M, 4, 1);
+  const Head hs = TAN ? Head::make(stats + rbase, s.M, 4, 1) : hl, h1 = TAN ? Head::make(sig1 + rbase, s.M, 4, 1) : hl;
   G geo;
   geo.init(lane, s.D, pitch);
   const int i = geo.i, g = geo.g;
@@ -437,38 +485,54 @@ __global__ __launch_bounds__(256, DP <= 64 ? 2 : 1) void bwd_col_f32_kernel(
   __syncthreads();
   for (int i0 = wave * kR; i0 < s.M; i0 += kNW * kR) {
     const unsigned tile = (unsigned)i0 * pitch;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 z = zero, za = zero, zb = zero, da = zero, db = zero, e = zero;
     typename G::Rows qf = geo.rows(hq, tile), tqf, gf, tgf;
-    if constexpr (TAN) {
-      tqf = geo.rows(htq, tile);
-      tgf = geo.rows(htg, tile);
-    }
+    if constexpr (TAN) tqf = geo.rows(htq, tile);
     if constexpr (GO) gf = geo.rows(hg, tile);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < G::NT; ++t) {
+      const f32x4 fk = fixed[t * 64 + lane];
+      TVM_F32_STEP(z, qf.t[t], fk);
+      if constexpr (TAN) {
+        const f32x4 ftk = fixed[G::FIX + t * 64 + lane];
+        TVM_F32_STEP(zb, qf.t[t], ftk);
+        TVM_F32_STEP(za, tqf.t[t], fk);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (TAN) tgf = geo.rows(htg, tile);
     f32x4 vl, vs, vd, v1;  // row scalars of queries i0 + 4g + r
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const long long x = (long long)bh * s.M + min(i0 + 4 * g + r, s.M - 1);
-      vl[r] = lse[x];
-      vd[r] = dsig[x];
+      const unsigned x = (unsigned)(i0 + 4 * g + r) * 4u;
+      vl[r] = hl.ld1(x);
+      vd[r] = hd.ld1(x);
       if constexpr (TAN) {
-        vs[r] = stats[x];
-        v1[r] = sig1[x];
+        vs[r] = hs.ld1(x);
+        v1[r] = h1.ld1(x);
       }
     }
-    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    f32x4 z = zero, za = zero, zb = zero, da = zero, db = zero, e = zero;
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < G::NT; ++t) {
-      const f32x4 fk = fixed[t * 64 + lane], fv = fixed[2 * G::FIX + t * 64 + lane];
-      TVM_F32_STEP(z, qf.t[t], fk);
+      const f32x4 fv = fixed[2 * G::FIX + t * 64 + lane];
+      if constexpr (GO) TVM_F32_STEP(da, gf.t[t], fv);
+    }
+    const typename G::Cols qc = geo.cols(hq, tile, pitch);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < G::NT; ++t) {
       if constexpr (TAN) {
-        const f32x4 ftk = fixed[G::FIX + t * 64 + lane], ftv = fixed[3 * G::FIX + t * 64 + lane];
-        TVM_F32_STEP(za, tqf.t[t], fk);
-        TVM_F32_STEP(zb, qf.t[t], ftk);
+        const f32x4 fv = fixed[2 * G::FIX + t * 64 + lane], ftv = fixed[3 * G::FIX + t * 64 + lane];
         TVM_F32_STEP(db, tgf.t[t], ftv);
         TVM_F32_STEP(e, tgf.t[t], fv);
       }
-      if constexpr (GO) TVM_F32_STEP(da, gf.t[t], fv);
     }
+    typename G::Cols tqc;
+    if constexpr (TAN) tqc = geo.cols(htq, tile, pitch);
+    __builtin_amdgcn_sched_barrier(0);
     f32x4 p, pd, gz, gzt;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -483,21 +547,18 @@ __global__ __launch_bounds__(256, DP <= 64 ? 2 : 1) void bwd_col_f32_kernel(
       }
       gz[r] = ok ? x : 0.f;
     }
-    {
-      const typename G::Cols qc = geo.cols(hq, tile, pitch);
-      G::out(ak, qc, gz);
-      if constexpr (TAN) G::out(atk, qc, gzt);
-    }
+    typename G::Cols gc, tgc;
+    if constexpr (GO) gc = geo.cols(hg, tile, pitch);
+    __builtin_amdgcn_sched_barrier(0);
+    G::out(ak, qc, gz);
     if constexpr (TAN) {
-      const typename G::Cols tqc = geo.cols(htq, tile, pitch);
+      G::out(atk, qc, gzt);
+      tgc = geo.cols(htg, tile, pitch);
+      __builtin_amdgcn_sched_barrier(0);
       G::out(ak, tqc, gzt);
     }
-    if constexpr (GO) {
-      const typename G::Cols gc = geo.cols(hg, tile, pitch);
-      G::out(av, gc, p);
-    }
+    if constexpr (GO) G::out(av, gc, p);
     if constexpr (TAN) {
-      const typename G::Cols tgc = geo.cols(htg, tile, pitch);
       G::out(atv, tgc, p);
       G::out(av, tgc, pd);
     }
