@@ -22,9 +22,9 @@ inline bool f32_mfma_reads(const Shape& s, int dtype) {  // false for a dtype wi
 //            16 x 1:   1 head, d 128 7.6 / 8.3;  2048 heads, d 128 67 / 41
 //            1 x 16:   4096 heads, d 100 66 / 78;  2048 heads, d 128 52 / 42
 //   backward, both gradients, 1 x 1:  1 head: d 4 8.6 / 10.9, d 64 21 / 13;  16384 heads: d 16 99 / 161, d 64 298 / 429
-//            4 x 4:    1 head: d 4 9.8 / 10.8, d 16 12.4 / 10.9;  16384 heads: d 16 178 / 212, d 32 269 / 215, d 64 459 / 424,
+//            4 x 4:    1 head: d 4 9.8 / 10.8, d 16 12.4 / 10.9;  16384 heads: d 16 178 / 212, d 32 269 / 170, d 64 459 / 330,
 //                      d 128 1014 / 1820      6 x 6: here, but for d 4 on one head (the same)
-//   backward, gO alone: here at every size (1 x 1: 16384 heads, d 128 450 / 418)
+//   backward, gO alone: here at every size (1 x 1: 16384 heads, d 128 450 / 384)
 inline bool f32_mfma_fwd(const Shape& s, int dtype) {
   if (!f32_mfma_reads(s, dtype)) return false;
   const long long heads = (long long)s.B * s.H;

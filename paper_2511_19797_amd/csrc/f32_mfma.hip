@@ -286,7 +286,9 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(Shape s, const float* _
 // Query side of the backward: dq, dtq of 16 queries, and Step 1's row scalars for the key side behind it.
 // The loads are put in stages, each sent off a group of products before it is used (the scheduling barriers hold the
 // compiler to that), so that few fragments live at once: 251 registers instead of 280 at DP = 128, two waves per SIMD
-// instead of one.  With a tangent there are products enough behind the next tile's first rows to load them one tile ahead.
+// instead of one.  With a tangent there are products enough behind the next tile's first rows to load them one tile ahead
+// (a wave without one asks for an offset out of range: reading its own tile once more cost 7 % of a backward of 64 x 64 at
+// DP = 128, and a branch around the loads spills).  DP = 32 has the registers to take the second stage's loads with the first.
 // Both upstream gradients, B2 H16 N256 d128: 62 us before, 48 now; B2 H8 N1024 d64: 185 before, 167 now.  Without
 // the tangent there is little to put behind a stage's loads: B4 H12 N256 d64 18.4 us with all loads first, 18.8 in stages
 // and 20.2 with the next tile's rows ahead, so there all loads come first.
@@ -361,13 +363,13 @@ __global__ __launch_bounds__(256, MODE == 1 ? (DP <= 64 ? 2 : 1) : DP <= 32 ? 4 
   const float dsig_i = rows[0][i], sig1_i = rows[1][i];
   typename G::Rows kf, vf, tkf, tvf;
   if constexpr (TAN) {
-    const unsigned first = wave * kR < s.N ? (unsigned)(wave * kR) * pitch : 0u;
+    const unsigned first = wave * kR < s.N ? (unsigned)(wave * kR) * pitch : kOut;
     kf = geo.rows(hk, first);
     tkf = geo.rows(htk, first);
   }
   for (int j0 = wave * kR; j0 < s.N; j0 += kNW * kR) {
     const unsigned tile = (unsigned)j0 * pitch;
-    const unsigned next = j0 + kNW * kR < s.N ? tile + (unsigned)(kNW * kR) * pitch : tile;
+    const unsigned next = j0 + kNW * kR < s.N ? tile + (unsigned)(kNW * kR) * pitch : kOut;
     if constexpr (!TAN) kf = geo.rows(hk, tile);
     vf = geo.rows(hv, tile);
     typename G::Cols kc, tkc;
@@ -375,6 +377,10 @@ __global__ __launch_bounds__(256, MODE == 1 ? (DP <= 64 ? 2 : 1) : DP <= 32 ? 4 
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     f32x4 z = zero, za = zero, zb = zero, da = zero, db = zero, e = zero;
     if constexpr (TAN) {
+      if constexpr (DP <= 32) {
+        tvf = geo.rows(htv, tile);
+        kc = geo.cols(hk, tile, pitch);
+      }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int t = 0; t < G::NT; ++t) {
@@ -384,9 +390,11 @@ __global__ __launch_bounds__(256, MODE == 1 ? (DP <= 64 ? 2 : 1) : DP <= 32 ? 4 
         TVM_F32_STEP(zb, tkf.t[t], fq);
       }
       __builtin_amdgcn_sched_barrier(0);
-      tvf = geo.rows(htv, tile);
-      kc = geo.cols(hk, tile, pitch);
-      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (DP > 32) {
+        tvf = geo.rows(htv, tile);
+        kc = geo.cols(hk, tile, pitch);
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
       for (int t = 0; t < G::NT; ++t) {
         const f32x4 ftg = fixed[3 * G::FIX + t * 64 + lane];
@@ -451,9 +459,10 @@ __global__ __launch_bounds__(256, MODE == 1 ? (DP <= 64 ? 2 : 1) : DP <= 32 ? 4 
 // waves per SIMD: a short sequence's 768 workgroups were a full round and a half-empty one.  It takes 168 now (DP = 96: 243,
 // was 304), one wave more.  Both upstream gradients: B4 H12 N256 d64 75.6 us before, 51 now (its products alone: 31); B2 H8
 // N1024 d64 278 and 224; B2 H16 N256 d96 66 and 48, d128 82 and 69.  At DP = 128 two waves would spill 24
-// registers and cost 73 us.
+// registers and cost 73 us.  DP = 32 loads the second stage with the first: 128 registers, four waves (backward of 16384 heads
+// of 6 x 6, d 32: 225 us before, 203 with 136 registers, 182 now).
 template <int DP, int MODE>
-__global__ __launch_bounds__(256, DP <= 64 ? 3 : DP <= 96 ? 2 : 1) void bwd_col_f32_kernel(
+__global__ __launch_bounds__(256, DP <= 32 ? 4 : DP <= 64 ? 3 : DP <= 96 ? 2 : 1) void bwd_col_f32_kernel(
     Shape s, const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     const float* __restrict__ tq, const float* __restrict__ tk, const float* __restrict__ tv, const float* __restrict__ lse,
     const float* __restrict__ stats, const float* __restrict__ gO, const float* __restrict__ gTO,
@@ -490,6 +499,21 @@ __global__ __launch_bounds__(256, DP <= 64 ? 3 : DP <= 96 ? 2 : 1) void bwd_col_
     typename G::Rows qf = geo.rows(hq, tile), tqf, gf, tgf;
     if constexpr (TAN) tqf = geo.rows(htq, tile);
     if constexpr (GO) gf = geo.rows(hg, tile);
+    f32x4 vl, vs, vd, v1;  // row scalars of queries i0 + 4g + r
+    const auto second = [&] {  // what the second group of products and the pointwise part need
+      if constexpr (TAN) tgf = geo.rows(htg, tile);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const unsigned x = (unsigned)(i0 + 4 * g + r) * 4u;
+        vl[r] = hl.ld1(x);
+        vd[r] = hd.ld1(x);
+        if constexpr (TAN) {
+          vs[r] = hs.ld1(x);
+          v1[r] = h1.ld1(x);
+        }
+      }
+    };
+    if constexpr (DP <= 32) second();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < G::NT; ++t) {
@@ -502,18 +526,7 @@ __global__ __launch_bounds__(256, DP <= 64 ? 3 : DP <= 96 ? 2 : 1) void bwd_col_
       }
     }
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (TAN) tgf = geo.rows(htg, tile);
-    f32x4 vl, vs, vd, v1;  // row scalars of queries i0 + 4g + r
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const unsigned x = (unsigned)(i0 + 4 * g + r) * 4u;
-      vl[r] = hl.ld1(x);
-      vd[r] = hd.ld1(x);
-      if constexpr (TAN) {
-        vs[r] = hs.ld1(x);
-        v1[r] = h1.ld1(x);
-      }
-    }
+    if constexpr (DP > 32) second();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < G::NT; ++t) {
