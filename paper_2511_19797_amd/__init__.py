@@ -1,6 +1,6 @@
 """MI355X-native fused attention with a JVP tangent and its backward (see include/tvmattn.h).
 
-The Python layer is a ctypes binding with the C entry points' names; importing the
+The Python layer has functions of the C entry points' names that marshal arguments; importing the
 package does not load the shared library, calling any entry point does (and raises if
 it has not been built).
 """
