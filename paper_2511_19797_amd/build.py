@@ -50,18 +50,22 @@ def _run(cmd, verbose):
         print(err)
 
 
-def build_fastcall(verbose=False):
-    """Host code only, against the torch that is installed and the library beside it."""
+def fastcall_command(src, out, libs):
+    """Host code only, against the torch and the Python that are installed."""
     import sysconfig
 
     import torch
     from torch.utils import cpp_extension
     tlib = cpp_extension.library_paths()[0]
-    _run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-w", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-          "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-I{sysconfig.get_paths()['include']}", "-I/opt/rocm/include",
-          *[f"-I{d}" for d in cpp_extension.include_paths()], os.path.join(HERE, "csrc", "fastcall.cpp"), "-o", FASTCALL,
-          f"-L{tlib}", "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10", f"-L{HERE}", "-l:libtvmattn.so",
-          "-Wl,-rpath,$ORIGIN", f"-Wl,-rpath,{tlib}"], verbose)
+    return ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-w", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-I{sysconfig.get_paths()['include']}", "-I/opt/rocm/include",
+            *[f"-I{d}" for d in cpp_extension.include_paths()], src, "-o", out,
+            f"-L{tlib}", "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10", *libs, f"-Wl,-rpath,{tlib}"]
+
+
+def build_fastcall(verbose=False):
+    _run(fastcall_command(os.path.join(HERE, "csrc", "fastcall.cpp"), FASTCALL, [f"-L{HERE}", "-l:libtvmattn.so", "-Wl,-rpath,$ORIGIN"]),
+         verbose)
 
 
 def build(verbose=False, extra=(), jobs=None):

@@ -118,11 +118,13 @@ void* ptr(const Tensor* t) { return t == nullptr ? nullptr : t->data_ptr(); }
 void* ptr(const Tensor& t) { return t.data_ptr(); }
 void* stream() { return (void*)c10::hip::getCurrentHIPStream().stream(); }
 
-// The library's entry points never touch Python objects.
-template <class F>
-int released(F&& f) {
+// An entry point with the interpreter released: it never touches Python objects.  Its arguments are raw pointers and numbers,
+// worked out before: a data pointer may throw (storages that refuse access) or copy a storage (copy-on-write), and that has to
+// happen while the interpreter is held.
+template <class... P, class... A>
+int released(int (*entry)(P...), A... a) {
   int rc;
-  Py_BEGIN_ALLOW_THREADS rc = f();
+  Py_BEGIN_ALLOW_THREADS rc = entry(a...);
   Py_END_ALLOW_THREADS
   return rc;
 }
@@ -165,10 +167,8 @@ PyObject* jvp_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     Tensor o[4] = {like(*q), like(*q)};
     if (save) o[2] = row_vector(*q), o[3] = row_vector(*q);
     void* const st = stream();
-    const int rc = released([&] {
-      return tvmattn_jvp_fwd(&d, ptr(q), ptr(k), ptr(v), ptr(tq), ptr(tk), ptr(tv), ptr(o[0]), ptr(o[1]),
-                             save ? (float*)ptr(o[2]) : nullptr, save ? (float*)ptr(o[3]) : nullptr, st);
-    });
+    const int rc = released(tvmattn_jvp_fwd, &d, ptr(q), ptr(k), ptr(v), ptr(tq), ptr(tk), ptr(tv), ptr(o[0]), ptr(o[1]),
+                            save ? (float*)ptr(o[2]) : nullptr, save ? (float*)ptr(o[3]) : nullptr, st);
     return result(rc, o);
   });
 }
@@ -191,11 +191,9 @@ PyObject* jvp_bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const Tensor ws = bytes(*q, need);
     auto out = [&](int i) { return r[i].defined() ? ptr(r[i]) : nullptr; };
     void* const st = stream();
-    const int rc = released([&] {
-      return tvmattn_jvp_bwd(&d, ptr(q), ptr(k), ptr(v), ptr(tq), ptr(tk), ptr(tv), ptr(o), ptr(to), (const float*)ptr(lse),
-                             (const float*)ptr(stats), ptr(gO), ptr(gTO), out(0), out(1), out(2), out(3), out(4), out(5), ptr(ws), need,
-                             st);
-    });
+    const int rc = released(tvmattn_jvp_bwd, &d, ptr(q), ptr(k), ptr(v), ptr(tq), ptr(tk), ptr(tv), ptr(o), ptr(to),
+                            (const float*)ptr(lse), (const float*)ptr(stats), ptr(gO), ptr(gTO), out(0), out(1), out(2), out(3),
+                            out(4), out(5), ptr(ws), need, st);
     return result(rc, r);
   });
 }
@@ -216,10 +214,8 @@ PyObject* qknorm_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
       NOT_MINE;
     Tensor o[4] = {like(*q), like(*q), like(*k), like(*k)};
     void* const st = stream();
-    const int rc = released([&] {
-      return tvmattn_qknorm_jvp_fwd(&d, ptr(q), ptr(tq), ptr(k), ptr(tk), (const float*)ptr(gq), (const float*)ptr(gk), (float)eps,
-                                    ptr(o[0]), ptr(o[1]), ptr(o[2]), ptr(o[3]), st);
-    });
+    const int rc = released(tvmattn_qknorm_jvp_fwd, &d, ptr(q), ptr(tq), ptr(k), ptr(tk), (const float*)ptr(gq),
+                            (const float*)ptr(gk), (float)eps, ptr(o[0]), ptr(o[1]), ptr(o[2]), ptr(o[3]), st);
     return result(rc, o);
   });
 }
@@ -242,12 +238,10 @@ PyObject* bwd_qknorm(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const size_t need = tvmattn_jvp_bwd_qknorm_workspace_bytes(&d), size = need > 16 ? need : 16;
     const Tensor ws = bytes(*q, size);
     void* const st = stream();
-    const int rc = released([&] {
-      return tvmattn_jvp_bwd_qknorm(&d, ptr(q), ptr(tq), ptr(k), ptr(tk), (const float*)ptr(gq), (const float*)ptr(gk), (float)eps,
-                                    ptr(qn), ptr(tqn), ptr(kn), ptr(tkn), ptr(v), ptr(tv), ptr(o), ptr(to), (const float*)ptr(lse),
-                                    (const float*)ptr(stats), ptr(gO), ptr(gTO), ptr(r[0]), ptr(r[1]), ptr(r[2]), ptr(r[3]), ptr(r[4]),
-                                    ptr(r[5]), (float*)ptr(r[6]), (float*)ptr(r[7]), ptr(ws), size, st);
-    });
+    const int rc = released(tvmattn_jvp_bwd_qknorm, &d, ptr(q), ptr(tq), ptr(k), ptr(tk), (const float*)ptr(gq),
+                            (const float*)ptr(gk), (float)eps, ptr(qn), ptr(tqn), ptr(kn), ptr(tkn), ptr(v), ptr(tv), ptr(o),
+                            ptr(to), (const float*)ptr(lse), (const float*)ptr(stats), ptr(gO), ptr(gTO), ptr(r[0]), ptr(r[1]),
+                            ptr(r[2]), ptr(r[3]), ptr(r[4]), ptr(r[5]), (float*)ptr(r[6]), (float*)ptr(r[7]), ptr(ws), size, st);
     return PyLong_FromLong(rc);
   });
 }
@@ -278,10 +272,8 @@ PyObject* adaln_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (!g.ok || !token_args(*x, *tx, {s, ts, b, tb}, dt)) NOT_MINE;
     Tensor o[2] = {like(*x), like(*x)};
     void* const st = stream();
-    const int rc = released([&] {
-      return tvmattn_adaln_jvp_fwd(DIMS(x), dt, ptr(x), ptr(tx), (const float*)ptr(s), (const float*)ptr(ts), (const float*)ptr(b),
-                                   (const float*)ptr(tb), (float)eps, ptr(o[0]), ptr(o[1]), st);
-    });
+    const int rc = released(tvmattn_adaln_jvp_fwd, DIMS(x), dt, ptr(x), ptr(tx), (const float*)ptr(s), (const float*)ptr(ts),
+                            (const float*)ptr(b), (const float*)ptr(tb), (float)eps, ptr(o[0]), ptr(o[1]), st);
     return result(rc, o);
   });
 }
@@ -301,12 +293,10 @@ PyObject* adaln_bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const size_t need = tvmattn_adaln_jvp_bwd_workspace_bytes(DIMS(x), dt), size = need > 16 ? need : 16;
     const Tensor ws = bytes(*x, size);
     void* const st = stream();
-    const int rc = released([&] {
-      return tvmattn_adaln_jvp_bwd_residual(DIMS(x), dt, ptr(x), ptr(tx), (const float*)ptr(s), (const float*)ptr(ts), (const float*)ptr(b),
-                                            (const float*)ptr(tb), (float)eps, ptr(gy), ptr(gty), ptr(gres), ptr(gtres), ptr(o[0]),
-                                            ptr(o[1]), (float*)ptr(o[2]), (float*)ptr(o[3]), (float*)ptr(o[4]), (float*)ptr(o[5]), ptr(ws),
-                                            size, st);
-    });
+    const int rc = released(tvmattn_adaln_jvp_bwd_residual, DIMS(x), dt, ptr(x), ptr(tx), (const float*)ptr(s),
+                            (const float*)ptr(ts), (const float*)ptr(b), (const float*)ptr(tb), (float)eps, ptr(gy), ptr(gty),
+                            ptr(gres), ptr(gtres), ptr(o[0]), ptr(o[1]), (float*)ptr(o[2]), (float*)ptr(o[3]), (float*)ptr(o[4]),
+                            (float*)ptr(o[5]), ptr(ws), size, st);
     return result(rc, o);
   });
 }
@@ -321,10 +311,8 @@ PyObject* gate_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (!g.ok || !token_args(*x, *tx, {c, tc}, dt) || !looks_like(*x, *h, *th)) NOT_MINE;
     Tensor o[2] = {like(*x), like(*x)};
     void* const st = stream();
-    const int rc = released([&] {
-      return tvmattn_gate_jvp_fwd(DIMS(x), dt, ptr(x), ptr(tx), ptr(h), ptr(th), (const float*)ptr(c), (const float*)ptr(tc), (float)eps,
-                                  ptr(o[0]), ptr(o[1]), st);
-    });
+    const int rc = released(tvmattn_gate_jvp_fwd, DIMS(x), dt, ptr(x), ptr(tx), ptr(h), ptr(th), (const float*)ptr(c),
+                            (const float*)ptr(tc), (float)eps, ptr(o[0]), ptr(o[1]), st);
     return result(rc, o);
   });
 }
@@ -341,10 +329,9 @@ PyObject* gate_bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const size_t need = tvmattn_gate_jvp_bwd_workspace_bytes(DIMS(h), dt), size = need > 16 ? need : 16;
     const Tensor ws = bytes(*h, size);
     void* const st = stream();
-    const int rc = released([&] {
-      return tvmattn_gate_jvp_bwd(DIMS(h), dt, ptr(h), ptr(th), (const float*)ptr(c), (const float*)ptr(tc), (float)eps, ptr(gz), ptr(gtz),
-                                  ptr(o[0]), ptr(o[1]), (float*)ptr(o[2]), (float*)ptr(o[3]), ptr(ws), size, st);
-    });
+    const int rc = released(tvmattn_gate_jvp_bwd, DIMS(h), dt, ptr(h), ptr(th), (const float*)ptr(c), (const float*)ptr(tc),
+                            (float)eps, ptr(gz), ptr(gtz), ptr(o[0]), ptr(o[1]), (float*)ptr(o[2]), (float*)ptr(o[3]), ptr(ws),
+                            size, st);
     return result(rc, o);
   });
 }
@@ -364,7 +351,7 @@ PyObject* gelu_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (!g.ok || !pointwise(*u, {tu}, dt)) NOT_MINE;
     Tensor o[2] = {like(*u), like(*u)};
     void* const st = stream();
-    const int rc = released([&] { return tvmattn_gelu_jvp_fwd(u->numel(), dt, ptr(u), ptr(tu), ptr(o[0]), ptr(o[1]), st); });
+    const int rc = released(tvmattn_gelu_jvp_fwd, u->numel(), dt, ptr(u), ptr(tu), ptr(o[0]), ptr(o[1]), st);
     return result(rc, o);
   });
 }
@@ -377,9 +364,7 @@ PyObject* gelu_bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (!g.ok || !pointwise(*u, {tu, ga, gta}, dt)) NOT_MINE;
     Tensor o[2] = {like(*u), like(*u)};
     void* const st = stream();
-    const int rc = released([&] {
-      return tvmattn_gelu_jvp_bwd(u->numel(), dt, ptr(u), ptr(tu), ptr(ga), ptr(gta), ptr(o[0]), ptr(o[1]), st);
-    });
+    const int rc = released(tvmattn_gelu_jvp_bwd, u->numel(), dt, ptr(u), ptr(tu), ptr(ga), ptr(gta), ptr(o[0]), ptr(o[1]), st);
     return result(rc, o);
   });
 }
@@ -416,10 +401,8 @@ PyObject* linear_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     shape.back() = F;
     Tensor o[2] = {at::empty(shape, x->options()), at::empty(shape, x->options())};
     void* const st = stream();
-    const int rc = released([&] {
-      return tvmattn_linear_jvp_fwd((int)R, (int)w->size(1), (int)F, dt, ptr(x), ptr(tx), ldx, ptr(w), ptr(bias), ptr(o[0]), ptr(o[1]), F,
-                                    st);
-    });
+    const int rc = released(tvmattn_linear_jvp_fwd, (int)R, (int)w->size(1), (int)F, dt, ptr(x), ptr(tx), ldx, ptr(w), ptr(bias),
+                            ptr(o[0]), ptr(o[1]), F, st);
     return result(rc, o);
   });
 }
@@ -441,10 +424,8 @@ PyObject* linear_bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const size_t need = tvmattn_linear_jvp_bwd_workspace_bytes((int)R, K, F, dt), size = need > 16 ? need : 16;
     const Tensor ws = bytes(*x, size);
     void* const st = stream();
-    const int rc = released([&] {
-      return tvmattn_linear_jvp_bwd((int)R, K, F, dt, ptr(x), ptr(tx), ldx, ptr(w), ptr(gy), ptr(gty), ldy, ptr(o[0]), ptr(o[1]), ptr(o[2]),
-                                    bias_grad ? ptr(o[3]) : nullptr, ptr(ws), size, st);
-    });
+    const int rc = released(tvmattn_linear_jvp_bwd, (int)R, K, F, dt, ptr(x), ptr(tx), ldx, ptr(w), ptr(gy), ptr(gty), ldy,
+                            ptr(o[0]), ptr(o[1]), ptr(o[2]), bias_grad ? ptr(o[3]) : nullptr, ptr(ws), size, st);
     return result(rc, o);
   });
 }
