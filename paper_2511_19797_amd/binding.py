@@ -7,6 +7,8 @@ or a call fails, an exception is raised.
 """
 import ctypes
 import os
+import sys
+import warnings
 
 import torch
 
@@ -105,18 +107,37 @@ def lib():
 _fast = None
 
 
+class _PythonOnly:
+    """In the native module's place: takes nothing."""
+
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
+def native_target():
+    """What the native module is tied to (it goes by torch's C++ objects and by CPython's): compiled into it as built_for."""
+    return f"torch {torch.__version__}, {sys.implementation.cache_tag}"
+
+
 def _load_fast():
     """The module that takes the ordinary calls in native code (csrc/fastcall.cpp): each of its functions does what the
     function here that calls it does, for plain tensors that pass the checks, and returns None for anything else, which
-    then goes through the Python below."""
+    then goes through the Python below.  All calls do where there is no module for this torch and this Python (with one
+    warning), or where the library in use is not the one beside the module, which the module calls."""
     global _fast
-    lib()
+    if os.path.realpath(lib()._name) != os.path.realpath(os.path.join(_HERE, "libtvmattn.so")):
+        _fast = _PythonOnly()
+        return _fast
     try:
         from . import _fastcall
+        built_for = getattr(_fastcall, "built_for", "something else")
+        trouble = None if built_for == native_target() else f"is built for {built_for}, this is {native_target()}"
     except ImportError as e:
-        raise ImportError(f"{os.path.join(_HERE, '_fastcall.so')} cannot be loaded ({e}): run `python -m "
-                          "paper_2511_19797_amd.build` (or __graft_entry__.build()) first") from e
-    _fast = _fastcall
+        trouble = f"cannot be loaded ({e})"
+    if trouble is not None:
+        warnings.warn(f"{os.path.join(_HERE, '_fastcall.so')} {trouble}: ordinary calls take 10 to 20 us more each, in Python.  "
+                      "`python -m paper_2511_19797_amd.build` builds it.", RuntimeWarning, stacklevel=3)
+    _fast = _fastcall if trouble is None else _PythonOnly()
     return _fast
 
 

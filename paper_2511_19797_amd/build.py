@@ -1,6 +1,7 @@
 """Compiles csrc/*.hip into libtvmattn.so for gfx950 with hipcc (in-tree, beside this file)."""
 import glob
 import os
+import shutil
 import subprocess
 import sys
 import tempfile
@@ -56,14 +57,22 @@ def fastcall_command(src, out, libs):
 
     import torch
     from torch.utils import cpp_extension
+
+    from .binding import native_target
     tlib = cpp_extension.library_paths()[0]
     return ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-w", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-I{sysconfig.get_paths()['include']}", "-I/opt/rocm/include",
+            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f'-DTVM_BUILT_FOR="{native_target()}"', f"-I{sysconfig.get_paths()['include']}", "-I/opt/rocm/include",
             *[f"-I{d}" for d in cpp_extension.include_paths()], src, "-o", out,
             f"-L{tlib}", "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10", *libs, f"-Wl,-rpath,{tlib}"]
 
 
 def build_fastcall(verbose=False):
+    """Without a host compiler there is no module, and the binding does these calls in Python."""
+    if os.path.exists(FASTCALL):
+        os.remove(FASTCALL)
+    if shutil.which("g++") is None:
+        print("no g++: _fastcall.so is not built, ordinary calls go through Python", file=sys.stderr)
+        return
     _run(fastcall_command(os.path.join(HERE, "csrc", "fastcall.cpp"), FASTCALL, [f"-L{HERE}", "-l:libtvmattn.so", "-Wl,-rpath,$ORIGIN"]),
          verbose)
 

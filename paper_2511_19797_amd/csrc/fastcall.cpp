@@ -438,4 +438,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, 
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fastcall() { return PyModule_Create(&module); }
+// built_for: the torch and the Python that this was compiled against; binding.py uses the module with no other.
+PyMODINIT_FUNC PyInit__fastcall() {
+  PyObject* m = PyModule_Create(&module);
+  if (m != nullptr && PyModule_AddStringConstant(m, "built_for", TVM_BUILT_FOR) != 0) Py_CLEAR(m);
+  return m;
+}

@@ -1,5 +1,10 @@
 """The binding's native calls (csrc/fastcall.cpp) against its Python: same results, same refusals.  The native module returns
 None for what it does not take, so the comparison is with a binding whose module takes nothing."""
+import shutil
+import sys
+import types
+import warnings
+
 import pytest
 import torch
 
@@ -52,6 +57,64 @@ def test_takes_no_cpu_tensors_numbers_or_missing_arguments():
         tvm.tvmattn_jvp_fwd(t, t, t, t, t, t)
     with pytest.raises(ValueError):
         tvm.tvmattn_gelu_jvp_fwd(t, t)
+
+
+MODULE = "paper_2511_19797_amd._fastcall"
+# no module; one that cannot be loaded; one that is built for another torch or Python (or says nothing of it)
+UNUSABLE = [None, "not a module", types.SimpleNamespace(built_for="torch 1.0, cpython-30"), types.SimpleNamespace()]
+
+
+def without_module(mp, instead):
+    mp.setattr(binding, "_fast", None)
+    mp.delattr(tvm, "_fastcall", raising=False)
+    if isinstance(instead, str):
+        mp.setattr(tvm, "__path__", [instead])
+        mp.delitem(sys.modules, MODULE, raising=False)
+    else:
+        mp.setitem(sys.modules, MODULE, instead)
+
+
+@pytest.mark.parametrize("instead", UNUSABLE)
+def test_calls_without_a_usable_module_go_through_python(monkeypatch, tmp_path, instead):
+    """One warning, and what Python does from there on (here: its refusal of CPU tensors)."""
+    t = torch.zeros(1, 1, 4, 8)
+    with monkeypatch.context() as mp:
+        if isinstance(instead, str):
+            (tmp_path / "_fastcall.so").write_text(instead)
+            instead = str(tmp_path)
+        without_module(mp, instead)
+        with pytest.warns(RuntimeWarning, match="_fastcall.so") as seen:
+            for _ in range(2):
+                with pytest.raises(ValueError, match="device tensors required"):
+                    tvm.tvmattn_jvp_fwd(t, t, t, t, t, t)
+        assert len(seen) == 1
+    assert binding._load_fast().built_for == binding.native_target()
+
+
+def test_native_calls_stay_with_the_library_beside_the_module(monkeypatch, tmp_path):
+    """Another library in LIB_PATH serves all calls: the module, which is linked to the one beside it, takes none."""
+    other = str(tmp_path / "libother.so")
+    shutil.copy(binding.LIB_PATH, other)
+    with monkeypatch.context() as mp, warnings.catch_warnings():
+        warnings.simplefilter("error")
+        mp.setattr(binding, "LIB_PATH", other)
+        mp.setattr(binding, "_lib", None)
+        mp.setattr(binding, "_fast", None)
+        assert binding._load_fast() is not sys.modules.get(MODULE) and binding.lib()._name == other
+        assert binding._load_fast().gelu_fwd() is None
+    assert binding._load_fast() is sys.modules[MODULE]
+
+
+@pytest.mark.gpu
+def test_results_without_a_module(monkeypatch):
+    x, tx = torch.randn(4, 64, device="cuda"), torch.randn(4, 64, device="cuda")
+    want = tvm.tvmattn_gelu_jvp_fwd(x, tx)
+    with monkeypatch.context() as mp:
+        without_module(mp, None)
+        with pytest.warns(RuntimeWarning, match="_fastcall.so"):
+            got = tvm.tvmattn_gelu_jvp_fwd(x, tx)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
 
 
 def _attention(dtype, strided, seed=0):
