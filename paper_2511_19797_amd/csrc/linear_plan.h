@@ -21,21 +21,21 @@ inline bool grid_fits(int c, long long tiles) { return c < k128 || small_workgro
 
 // Time of a product (ns): `tiles` output tiles of shape c over `steps` contraction tiles each are rounds of 256 workgroups, each
 // its steps and a fixed part (first operands, results), behind a start-up.  The weights are fits to kernel times of all four
-// shapes at 378 products of the forward and 378 of grad x (whose second operand is read transposed: other weights), R = 64 ...
-// 65536 rows, widths 32 ... 4608 either way.  From a contraction of 288 on the choice is 0.2 % behind the fastest shape on
-// average (forward; at most 9 %), below, where nearly all of a product is start-up and stores, 4 %; grad x 0.2 and 0.3 %.
-// Some of the times (us; 256 | 192 | 128 | 64):
-//   forward, 500 x 768 -> 768:       18 |  15 |  11 |   6     few tiles: small ones fill the chip
-//   forward, 1024 x 1152 -> 1152:    24 |  20 |  14 |  15
-//   forward, 2048 x 768 -> 2304:     23 |  20 |  29 |  29     the small shapes' fixed part, round after round
-//   forward, 2048 x 512 -> 3072:     19 |  20 |  25 |  32
-//   forward, 16384 x 64 -> 1152:     20 |  18 |  33 |  43     short contraction: first operands and stores
-//   forward, 16384 x 768 -> 3072:   135 | 140 | 230 | 283
-//   forward, 8192 x 4608 -> 1152:   183 | 152 | 202 | 244     long contraction, and 1152 = 6 x 192: no padded columns
+// shapes, R = 40 ... 65536 rows, widths 32 ... 4608 either way (so weights only: the choice matters, not the time): 1144 products
+// of the forward, where the choice is 0.03 % behind the fastest shape on average and 4.8 % at most; grad x (whose second operand
+// is read transposed: other weights) costs a whole backward 0.01 % on average of 551 products, 1.1 % at most.
+// Some of the times, back to back (us; 256 | 192 | 128 | 64):
+//   forward, 500 x 768 -> 768:       17 |  14 |  10 | 5.6     few tiles: small ones fill the chip
+//   forward, 1024 x 1152 -> 1152:    24 |  20 |  14 |  14
+//   forward, 2048 x 768 -> 3072:     23 |  21 |  31 |  38     the small shapes' fixed part, round after round
+//   forward, 8192 x 64 -> 1152:      15 |  13 |  21 |  23     short contraction: first operands and stores
+//   forward, 5000 x 96 -> 1312:      12 |  14 |  19 |  20     ... where 192 columns need one round more
+//   forward, 16384 x 768 -> 3072:   126 | 130 | 244 | 295
+//   forward, 8192 x 4608 -> 1152:   182 | 149 | 211 | 247     long contraction, and 1152 = 6 x 192: no padded columns
 struct ShapeCost {
   int start, fixed, step;
 };
-constexpr ShapeCost kCostRow[kShapes] = {{0, 7018, 1600}, {2454, 6784, 1088}, {1523, 4770, 539}, {2305, 2000, 210}};
+constexpr ShapeCost kCostRow[kShapes] = {{2231, 7416, 929}, {638, 5645, 750}, {0, 4184, 482}, {622, 1455, 173}};
 constexpr ShapeCost kCostTr[kShapes] = {{3632, 13659, 1047}, {806, 10481, 823}, {3535, 4645, 458}, {3090, 2010, 162}};
 inline long long product_ns(const ShapeCost& c, long long tiles, int steps) {
   return c.start + (tiles + 255) / 256 * (c.fixed + (long long)steps * c.step);
@@ -74,8 +74,8 @@ inline int dw_splits(int F, int K, int R) {
   }
   return best;
 }
-// grad W: time of `tiles` output tiles of shape c over `steps` contraction tiles each, in units of about 17 ns (the 256 x 256
-// shape takes 1.2 us per contraction tile on an idle chip, 1.6 on a full one).
+// grad W: time of `tiles` output tiles of shape c over `steps` contraction tiles each, in units of 1/60 us (weights of a fit: a
+// contraction tile of 256 x 256 counts 1.8 us; it takes 1.2 us on an idle chip and 1.6 on a full one).
 inline long long dw_cost(int c, long long tiles, int steps) {
   constexpr int kStep[kShapes] = {108, 86, 46, 27}, kFixed[kShapes] = {49, 87, 58, 54};
   return (tiles + 255) / 256 * ((long long)steps * kStep[c] + kFixed[c]);

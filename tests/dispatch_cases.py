@@ -9,7 +9,8 @@ LINEAR = [
     ((1, 480, 3232), (64, 64, 128), False),
     ((214, 96, 96), (64, 64, 64), True),
     ((4709, 288, 224), (128, 128, 128), True),
-    ((8243, 224, 288), (256, 192, 128), True),
+    ((8243, 224, 288), (192, 192, 128), True),
+    ((4100, 224, 1568), (256, 128, 128), True),
     ((3890, 1632, 544), (192, 256, 192), True),
     ((3114, 4192, 288), (64, 256, 256), True),
 ]
@@ -18,10 +19,14 @@ LINEAR = [
 # a last row tile of one row, of all but one; a last column tile of one block of 32; several output tiles per workgroup with
 # contractions shorter than the loads run ahead; grad W with the border between the two row sets inside a part.
 LINEAR_PIPE = [
-    ((4097, 32, 1184), (256, 64, 64)),
-    ((8191, 64, 416), (256, 64, 64)),
-    ((33025, 32, 128), (256, 64, 64)),
-    ((5000, 96, 800), (256, 64, 128)),
+    ((4097, 32, 1184), (192, 64, 64)),
+    ((8191, 64, 416), (192, 64, 64)),
+    ((33025, 32, 128), (192, 64, 64)),
+    ((5000, 96, 800), (192, 64, 128)),
+    ((4097, 32, 1568), (256, 64, 64)),
+    ((8191, 64, 800), (256, 64, 64)),
+    ((33025, 32, 224), (256, 64, 64)),
+    ((5000, 96, 2592), (256, 64, 128)),
     ((33025, 96, 160), (192, 128, 64)),
     ((6145, 608, 352), (192, 192, 128)),
     ((12289, 768, 800), (192, 192, 192)),

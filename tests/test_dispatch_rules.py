@@ -52,21 +52,23 @@ def test_linear_tiles_fit_one_launch(R):
                 assert -(-tiles // 8) * 8 * 256 < 2 ** 32, (R, K, F, shape)
 
 
-# R, K, F and the measured times (us) of the 256, 192, 128 and 64 tiles: the forward, and a whole backward without bias whose
-# grad x takes the shape
+# R, K, F and the measured times (us, graphs of calls back to back) of the 256, 192, 128 and 64 tiles: the forward, and a whole
+# backward without bias whose grad x takes the shape
 MEASURED_FORWARD = [
-    (2048, 768, 1536, (26.1, 25.2, 28.4, 31.1)), (4096, 1152, 768, (33.6, 32.9, 36.4, 40.3)),
-    (4096, 768, 768, (26.0, 25.2, 28.6, 30.3)), (2048, 384, 1536, (17.5, 17.4, 20.5, 21.2)),
-    (8192, 384, 384, (17.7, 17.2, 20.7, 21.3)), (256, 4608, 1152, (101.7, 97.7, 51.0, 30.6)),
-    (1024, 1536, 1152, (40.3, 38.2, 23.9, 27.1)), (2048, 1152, 3456, (37.9, 60.7, 66.5, 81.4)),
-    (16384, 384, 1152, (45.8, 47.5, 79.3, 101.5)), (500, 768, 768, (23.5, 22.0, 15.2, 10.3)),
-    (64, 768, 768, (22.6, 21.4, 14.7, 9.6)), (65536, 32, 128, (19.2, 21.6, 26.9, 32.7)),
-    (8192, 256, 32, (11.9, 11.4, 8.9, 6.7)), (16384, 64, 1152, (25.9, 29.7, 53.7, 66.8)),
+    (2048, 768, 1536, (21.4, 18.5, 21.2, 21.6)), (4096, 1152, 768, (25.7, 22.1, 26.0, 25.4)),
+    (4096, 768, 768, (19.6, 17.0, 19.5, 18.8)), (2048, 384, 1536, (13.7, 12.2, 13.9, 14.2)),
+    (8192, 384, 384, (13.3, 11.6, 13.8, 13.7)), (256, 4608, 1152, (72.5, 58.0, 38.0, 18.8)),
+    (1024, 1536, 1152, (29.5, 24.2, 17.0, 17.3)), (2048, 1152, 3456, (32.8, 41.8, 53.7, 58.1)),
+    (16384, 384, 1152, (37.3, 33.0, 59.4, 70.5)), (500, 768, 768, (17.2, 14.1, 9.6, 5.6)),
+    (64, 768, 768, (17.1, 14.1, 9.5, 5.3)), (65536, 32, 128, (14.9, 13.8, 17.9, 21.8)),
+    (8192, 256, 32, (9.8, 8.2, 5.8, 3.8)), (16384, 64, 1152, (19.8, 18.4, 33.7, 42.9)),
+    (2048, 64, 4608, (14.7, 12.6, 20.5, 23.9)), (8192, 64, 1152, (14.8, 12.6, 20.5, 23.4)),
+    (8192, 4608, 1152, (181.6, 149.2, 211.0, 246.5)), (5000, 96, 1312, (11.9, 13.9, 18.5, 19.9)),
 ]
 MEASURED_BACKWARD = [
-    (4096, 768, 384, (38.1, 37.2, 40.8, 42.5)), (16384, 1152, 1152, (211.5, 201.6, 249.7, 304.3)),
-    (8192, 96, 1536, (61.6, 56.8, 44.5, 40.5)), (500, 768, 768, (32.5, 30.2, 23.5, 19.0)),
-    (2048, 768, 768, (43.5, 41.4, 35.7, 37.7)), (1024, 768, 1152, (47.3, 44.4, 34.5, 31.0)),
+    (4096, 768, 384, (34.5, 32.6, 35.2, 36.2)), (16384, 1152, 1152, (177.2, 164.2, 222.5, 244.0)),
+    (8192, 96, 1536, (51.0, 44.8, 37.2, 35.3)), (500, 768, 768, (24.6, 21.0, 16.5, 12.2)),
+    (2048, 768, 768, (36.2, 32.9, 29.5, 29.8)), (1024, 768, 1152, (34.8, 30.0, 23.7, 20.7)),
 ]
 
 
