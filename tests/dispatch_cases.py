@@ -34,6 +34,14 @@ LINEAR_PIPE = [
     ((2049, 1184, 4640), (192, 192, 256)),
 ]
 
+# The 256-row tiles with row pitches other than the widths: both of them in every product
+LINEAR_PITCHED = [
+    ((4097, 608, 1568), (256, 192, 192)),
+    ((12289, 768, 800), (192, 192, 192)),
+    ((3001, 4640, 1184), (192, 256, 192)),
+    ((2049, 1184, 4640), (192, 192, 256)),
+]
+
 # Forward: heads, M, N.  Eight waves on 256 rows (512 keys and more, more than 128 queries, head dims up to 96), with a whole and
 # with a ragged last key tile, workgroups whose upper waves hold no row, M != N either way round
 FORWARD_EIGHT_WAVES = [(33, 512, 512), (33, 513, 513), (32, 543, 543), (17, 1000, 1000), (60, 257, 512), (52, 300, 543), (25, 700, 600),

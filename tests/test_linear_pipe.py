@@ -39,7 +39,7 @@ def test_instruction_stream():
     assert text.count("offen lds") > 100 and "scratch_" not in text
 
 
-@pytest.mark.parametrize("shape,tiles", dc.LINEAR_PIPE)
+@pytest.mark.parametrize("shape,tiles", dc.LINEAR_PIPE + dc.LINEAR_PITCHED)
 def test_routes(shape, tiles):
     (y, gx, gw, _), = ask([("linear", *shape)])
     assert tuple((256, 192, 128, 64)[c] for c in (y, gx, gw)) == tiles
