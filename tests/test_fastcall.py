@@ -1,5 +1,6 @@
 """The binding's native calls (csrc/fastcall.cpp) against its Python: same results, same refusals.  The native module returns
-None for what it does not take, so the comparison is with a binding whose module takes nothing."""
+None for what it does not take, so the comparison is with a binding whose module takes nothing; each call says whether the
+native function has to take it."""
 import shutil
 import sys
 import types
@@ -26,11 +27,31 @@ def outcome(fn, *a, **kw):
     return r
 
 
-def both(monkeypatch, fn, *a, **kw):
-    fast = outcome(fn, *a, **kw)
+class _Recorder:
+    """The native module, noting which of its functions took their call."""
+
+    def __init__(self):
+        self.module = binding._load_fast()
+        self.calls = []
+
+    def __getattr__(self, name):
+        def call(*a):
+            r = getattr(self.module, name)(*a)
+            self.calls.append((name, "python" if r is None else "native"))
+            return r
+        return call
+
+
+def both(monkeypatch, name, route, fn, *a, **kw):
+    """The call as it is, whose native function `name` has to take it ("native") or to leave it ("python"), against the call in
+    Python."""
+    seen = _Recorder()
     with monkeypatch.context() as mp:
+        mp.setattr(binding, "_fast", seen)
+        fast = outcome(fn, *a, **kw)
         mp.setattr(binding, "_fast", _Nothing())
         slow = outcome(fn, *a, **kw)
+    assert seen.calls == [(name, route)]
     assert len(fast) == len(slow)
     for f, s in zip(fast, slow):
         if isinstance(s, torch.Tensor):
@@ -133,36 +154,36 @@ def test_attention(monkeypatch, dtype, strided):
     six = (q, k, v, tq, tk, tv)
     assert took("jvp_fwd", *six, 0.0, True, 0)
     for kw in ({}, {"save": False}, {"scale": 0.3}, {"flags": tvm.TVMATTN_FLAG_PLAIN_ALU}, {"flags": 64}):
-        both(monkeypatch, tvm.tvmattn_jvp_fwd, *six, **kw)
+        both(monkeypatch, "jvp_fwd", "native", tvm.tvmattn_jvp_fwd, *six, **kw)
     saved = tvm.tvmattn_jvp_fwd(*six)
     for a, b in ((gO, gTO), (gO, None), (None, gTO), (None, None)):
-        both(monkeypatch, tvm.tvmattn_jvp_bwd, *six, *saved, a, b)
-    both(monkeypatch, tvm.tvmattn_jvp_bwd, q, k, v, None, None, None, saved[0], None, saved[2], None, gO, None)
+        both(monkeypatch, "jvp_bwd", "native", tvm.tvmattn_jvp_bwd, *six, *saved, a, b)
+    both(monkeypatch, "jvp_bwd", "native", tvm.tvmattn_jvp_bwd, q, k, v, None, None, None, saved[0], None, saved[2], None, gO, None)
     half = q[:, :, :35]                         # fewer queries than keys, and layouts that do not match
-    both(monkeypatch, tvm.tvmattn_jvp_fwd, half, k, v, tq[:, :, :35], tk, tv)
-    both(monkeypatch, tvm.tvmattn_jvp_fwd, half, k, v, tq, tk, tv)
-    both(monkeypatch, tvm.tvmattn_jvp_fwd, q, k, v.contiguous(), tq, tk, tv)
-    both(monkeypatch, tvm.tvmattn_jvp_fwd, q.half(), k, v, tq.half(), tk, tv)
-    both(monkeypatch, tvm.tvmattn_jvp_fwd, *[t.transpose(2, 3) for t in six])
-    both(monkeypatch, tvm.tvmattn_jvp_fwd, *[t[..., :20] for t in six])       # alignment: refused by the entry point
-    both(monkeypatch, tvm.tvmattn_jvp_fwd, *[t[0] for t in six])
-    both(monkeypatch, tvm.tvmattn_jvp_fwd, *[t.detach().requires_grad_() for t in six])
+    both(monkeypatch, "jvp_fwd", "native", tvm.tvmattn_jvp_fwd, half, k, v, tq[:, :, :35], tk, tv)
+    both(monkeypatch, "jvp_fwd", "python", tvm.tvmattn_jvp_fwd, half, k, v, tq, tk, tv)
+    both(monkeypatch, "jvp_fwd", "python" if strided else "native", tvm.tvmattn_jvp_fwd, q, k, v.contiguous(), tq, tk, tv)
+    both(monkeypatch, "jvp_fwd", "python", tvm.tvmattn_jvp_fwd, q.half(), k, v, tq.half(), tk, tv)
+    both(monkeypatch, "jvp_fwd", "python", tvm.tvmattn_jvp_fwd, *[t.transpose(2, 3) for t in six])
+    both(monkeypatch, "jvp_fwd", "native", tvm.tvmattn_jvp_fwd, *[t[..., :20] for t in six])       # alignment: refused by the entry point
+    both(monkeypatch, "jvp_fwd", "python", tvm.tvmattn_jvp_fwd, *[t[0] for t in six])
+    both(monkeypatch, "jvp_fwd", "native", tvm.tvmattn_jvp_fwd, *[t.detach().requires_grad_() for t in six])
 
 
 @pytest.mark.gpu
 def test_norm_and_fused_backward(monkeypatch):
     q, k, v, tq, tk, tv, gO, gTO = _attention(torch.bfloat16, True, 1)
     gq, gk = torch.rand(24, device="cuda") + 0.5, torch.rand(24, device="cuda") + 0.5
-    qn, tqn, kn, tkn = both(monkeypatch, tvm.tvmattn_qknorm_jvp_fwd, q, tq, k, tk, gq, gk, 1e-6)
-    both(monkeypatch, tvm.tvmattn_qknorm_jvp_fwd, q, tq, k, tk, gq.bfloat16(), gk, 1e-6)
-    both(monkeypatch, tvm.tvmattn_qknorm_jvp_fwd, q, tq, k, tk, gq[:16], gk, 1e-6)
+    qn, tqn, kn, tkn = both(monkeypatch, "qknorm_fwd", "native", tvm.tvmattn_qknorm_jvp_fwd, q, tq, k, tk, gq, gk, 1e-6)
+    both(monkeypatch, "qknorm_fwd", "python", tvm.tvmattn_qknorm_jvp_fwd, q, tq, k, tk, gq.bfloat16(), gk, 1e-6)
+    both(monkeypatch, "qknorm_fwd", "python", tvm.tvmattn_qknorm_jvp_fwd, q, tq, k, tk, gq[:16], gk, 1e-6)
     saved = tvm.tvmattn_jvp_fwd(qn, kn, v, tqn, tkn, tv)
     make = lambda: tuple(binding._like(t) for t in (q, k, v, tq, tk, tv)) + (torch.empty_like(gq), torch.empty_like(gk))
     args = (q, tq, k, tk, gq, gk, 1e-6, qn, tqn, kn, tkn, v, tv, *saved, gO, gTO)
     out = make()
     assert tvm.tvmattn_jvp_bwd_qknorm(*args, out=out) is out
-    both(monkeypatch, lambda: tvm.tvmattn_jvp_bwd_qknorm(*args, out=make()))
-    both(monkeypatch, lambda: tvm.tvmattn_jvp_bwd_qknorm(*args, out=make()[:6] + (gq.bfloat16(), torch.empty_like(gk))))
+    both(monkeypatch, "bwd_qknorm", "native", lambda: tvm.tvmattn_jvp_bwd_qknorm(*args, out=make()))
+    both(monkeypatch, "bwd_qknorm", "python", lambda: tvm.tvmattn_jvp_bwd_qknorm(*args, out=make()[:6] + (gq.bfloat16(), torch.empty_like(gk))))
 
 
 @pytest.mark.gpu
@@ -171,19 +192,20 @@ def test_token_calls(monkeypatch, dtype):
     g = torch.Generator(device="cuda").manual_seed(3)
     x, tx, h, th, gy, gty, r, tr = (torch.randn(2, 33, 64, generator=g, device="cuda").to(dtype) for _ in range(8))
     m = [torch.randn(2, 64, generator=g, device="cuda") for _ in range(4)]
-    for a in ((x, tx, *m), (x, tx[:, :32], *m), (x.transpose(0, 1), tx.transpose(0, 1), *m), (x, tx, m[0].to(dtype).double(), *m[1:]),
-              (x, tx, *m[:3], m[3][:1]), (x[..., :61].contiguous(), tx[..., :61].contiguous(), *[t[:, :61].contiguous() for t in m])):
-        both(monkeypatch, tvm.tvmattn_adaln_jvp_fwd, *a, 1e-6)
-    both(monkeypatch, tvm.tvmattn_adaln_jvp_bwd, x, tx, *m, 1e-6, gy, gty)
-    both(monkeypatch, tvm.tvmattn_adaln_jvp_bwd, x, tx, *m, 1e-6, gy, gty, gres=r, gtres=tr)
-    both(monkeypatch, tvm.tvmattn_adaln_jvp_bwd, x, tx, *m, 1e-6, gy, gty, gres=r)
-    both(monkeypatch, tvm.tvmattn_gate_jvp_fwd, x, tx, h, th, *m[:2], 1e-6)
-    both(monkeypatch, tvm.tvmattn_gate_jvp_fwd, x, tx, h[:1], th[:1], *m[:2], 1e-6)
-    both(monkeypatch, tvm.tvmattn_gate_jvp_bwd, h, th, *m[:2], 1e-6, gy, gty)
-    both(monkeypatch, tvm.tvmattn_gelu_jvp_fwd, x, tx)
-    both(monkeypatch, tvm.tvmattn_gelu_jvp_fwd, x[:, ::2], tx[:, ::2])
-    both(monkeypatch, tvm.tvmattn_gelu_jvp_bwd, x, tx, gy, gty)
-    both(monkeypatch, tvm.tvmattn_gelu_jvp_bwd, x, tx, gy, gty.double())
+    for route, a in (("native", (x, tx, *m)), ("python", (x, tx[:, :32], *m)), ("python", (x.transpose(0, 1), tx.transpose(0, 1), *m)),
+                     ("python", (x, tx, m[0].to(dtype).double(), *m[1:])), ("python", (x, tx, *m[:3], m[3][:1])),
+                     ("native", (x[..., :61].contiguous(), tx[..., :61].contiguous(), *[t[:, :61].contiguous() for t in m]))):
+        both(monkeypatch, "adaln_fwd", route, tvm.tvmattn_adaln_jvp_fwd, *a, 1e-6)
+    both(monkeypatch, "adaln_bwd", "native", tvm.tvmattn_adaln_jvp_bwd, x, tx, *m, 1e-6, gy, gty)
+    both(monkeypatch, "adaln_bwd", "native", tvm.tvmattn_adaln_jvp_bwd, x, tx, *m, 1e-6, gy, gty, gres=r, gtres=tr)
+    both(monkeypatch, "adaln_bwd", "python", tvm.tvmattn_adaln_jvp_bwd, x, tx, *m, 1e-6, gy, gty, gres=r)
+    both(monkeypatch, "gate_fwd", "native", tvm.tvmattn_gate_jvp_fwd, x, tx, h, th, *m[:2], 1e-6)
+    both(monkeypatch, "gate_fwd", "python", tvm.tvmattn_gate_jvp_fwd, x, tx, h[:1], th[:1], *m[:2], 1e-6)
+    both(monkeypatch, "gate_bwd", "native", tvm.tvmattn_gate_jvp_bwd, h, th, *m[:2], 1e-6, gy, gty)
+    both(monkeypatch, "gelu_fwd", "native", tvm.tvmattn_gelu_jvp_fwd, x, tx)
+    both(monkeypatch, "gelu_fwd", "python", tvm.tvmattn_gelu_jvp_fwd, x[:, ::2], tx[:, ::2])
+    both(monkeypatch, "gelu_bwd", "native", tvm.tvmattn_gelu_jvp_bwd, x, tx, gy, gty)
+    both(monkeypatch, "gelu_bwd", "python", tvm.tvmattn_gelu_jvp_bwd, x, tx, gy, gty.double())
 
 
 @pytest.mark.gpu
@@ -192,15 +214,17 @@ def test_linear(monkeypatch):
     rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
     x, tx, w, b, gy, gty = rnd(2, 50, 96), rnd(2, 50, 96), rnd(64, 96), rnd(64), rnd(100, 64), rnd(100, 64)
     wide, twide = rnd(100, 200), rnd(100, 200)
-    for a in ((x, tx, w, b), (x, tx, w, None), (wide[:, :96], twide[:, :96], w, b), (x[:, ::2], tx[:, ::2], w, b), (x, tx, w.t(), b),
-              (x, tx[:1], w, b), (x, tx, w, b[:32]), (x.float(), tx.float(), w.float(), None), (x[..., :40], tx[..., :40], w[:, :40].contiguous(), None),
-              (x[:0], tx[:0], w, b)):
-        both(monkeypatch, tvm.tvmattn_linear_jvp_fwd, *a)
+    for route, a in (("native", (x, tx, w, b)), ("native", (x, tx, w, None)), ("native", (wide[:, :96], twide[:, :96], w, b)),
+                     ("python", (x[:, ::2], tx[:, ::2], w, b)), ("python", (x, tx, w.t(), b)), ("python", (x, tx[:1], w, b)),
+                     ("python", (x, tx, w, b[:32])), ("native", (x.float(), tx.float(), w.float(), None)),
+                     ("python", (x[..., :40], tx[..., :40], w[:, :40].contiguous(), None)), ("native", (x[:0], tx[:0], w, b))):
+        both(monkeypatch, "linear_fwd", route, tvm.tvmattn_linear_jvp_fwd, *a)
     x2, tx2 = x.view(100, 96), tx.view(100, 96)
-    for a in ((x2, tx2, w, gy, gty), (x, tx, w, gy, gty), (wide[:, :96], twide[:, :96], w, gy, gty), (x2, tx2, w, wide[:, :64], twide[:, :64]),
-              (x2, tx2, w, gy[:50], gty[:50]), (x2, tx2, w, gy, gty.float())):
-        both(monkeypatch, tvm.tvmattn_linear_jvp_bwd, *a)
-    r = both(monkeypatch, tvm.tvmattn_linear_jvp_bwd, x2, tx2, w, gy, gty, bias_grad=False)
+    for route, a in (("native", (x2, tx2, w, gy, gty)), ("native", (x, tx, w, gy, gty)), ("native", (wide[:, :96], twide[:, :96], w, gy, gty)),
+                     ("native", (x2, tx2, w, wide[:, :64], twide[:, :64])), ("python", (x2, tx2, w, gy[:50], gty[:50])),
+                     ("python", (x2, tx2, w, gy, gty.float()))):
+        both(monkeypatch, "linear_bwd", route, tvm.tvmattn_linear_jvp_bwd, *a)
+    r = both(monkeypatch, "linear_bwd", "native", tvm.tvmattn_linear_jvp_bwd, x2, tx2, w, gy, gty, bias_grad=False)
     assert r[3] is None
 
 
