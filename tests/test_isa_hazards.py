@@ -1,7 +1,7 @@
 """Static check of the hand-scheduled kernels' instruction streams (no GPU needed).
 
 The hand-scheduled translation units issue their matrix-core products from inline assembly, which
-the compiler's hazard recognizer does not look into.  Four hazards are therefore ours to keep out
+the compiler's hazard recognizer does not look into.  Five hazards are therefore ours to keep out
 (the hardware interlocks neither):
   1. a matrix-core instruction must not read a register that a VALU instruction wrote in one of
      the two issue slots before it (s_nop N fills N+1 slots);
@@ -13,6 +13,8 @@ the compiler's hazard recognizer does not look into.  Four hazards are therefore
      a register copy right behind an assembly statement that ends in one.
   4. the asynchronous global->LDS loads take their LDS address from M0: one wait state between the scalar
      write of M0 and the load (both sit in one assembly statement, out of the compiler's sight).
+  5. a load must not read a scalar register (descriptor, base) that a VALU instruction (v_readfirstlane_b32, ...)
+     wrote in one of the five issue slots before it.
 The compiler is free to put register copies right in front of or right behind an inline-assembly
 statement (at a loop exit, say), so this is checked on the generated assembly of every
 instantiation rather than argued from the source.
@@ -134,6 +136,34 @@ def m0_violations(asm_text):
             if op.startswith("s_mov") and ops and ops[0] == "m0" and "load_lds" in ins[i + 1][0]]
 
 
+SREG = re.compile(r"\bs(?:(\d+)|\[(\d+):(\d+)\])")
+
+
+def scalar_regs(operand):
+    out = {r for r in ("m0", "vcc") if r in operand}
+    for m in SREG.finditer(operand):
+        out.update([int(m.group(1))] if m.group(1) is not None else range(int(m.group(2)), int(m.group(3)) + 1))
+    return out
+
+
+def scalar_violations(asm_text):
+    """Hazard 5: (index, VALU write, load) for every load that reads a scalar register written too shortly before."""
+    ins = list(instructions(asm_text))
+    bad = []
+    for i, (op, ops) in enumerate(ins):
+        if not op.startswith(("buffer_", "global_load_lds")):
+            continue
+        read = set().union(*[scalar_regs(o) for o in ops])
+        slots, j = 0, i - 1
+        while j >= 0 and slots < 5:
+            pop, pops = ins[j]
+            if pop.startswith("v_") and pops and (scalar_regs(pops[0]) | (scalar_regs(pops[1]) if "_co_" in pop else set())) & read:
+                bad.append((i, " ".join([pop] + pops), " ".join([op] + ops)))
+            slots += int(pops[0], 0) + 1 if pop == "s_nop" else 1
+            j -= 1
+    return bad
+
+
 def test_parser_flags_a_planted_hazard():
     planted = """
     v_accvgpr_write_b32 a4, v9
@@ -168,6 +198,11 @@ def test_parser_flags_a_planted_hazard():
     assert trans_violations("v_exp_f32 v3, v4\n v_exp_f32 v5, v3") == []
     assert len(m0_violations("s_mov_b32 m0, s3\n global_load_lds_dwordx4 v1, s[4:5]")) == 1
     assert m0_violations("s_mov_b32 m0, s3\n s_nop 0\n global_load_lds_dwordx4 v1, s[4:5]") == []
+    early = "v_readfirstlane_b32 s6, v9\n s_add_u32 m0, s3, 0\n v_add_u32 v1, s2, v3\n buffer_load_dwordx4 v1, s[4:7], 0 offen lds"
+    assert len(scalar_violations(early)) == 1
+    assert len(scalar_violations(early.replace("s_add", "s_nop 1\n s_add"))) == 1
+    assert scalar_violations(early.replace("s_add", "s_nop 2\n s_add")) == []
+    assert scalar_violations(early.replace("s6, v9", "s8, v9")) == []
 
 
 @pytest.mark.parametrize("name", HAND_SCHEDULED)
@@ -187,3 +222,4 @@ def test_no_valu_write_feeds_next_matrix_instruction(name):
     bad = trans_violations(text)
     assert not bad, f"{len(bad)} reads of a transcendental result in the next slot, first: {bad[:3]}"
     assert text.count("load_lds") > 10 and not m0_violations(text)
+    assert scalar_violations(text) == []

@@ -1,5 +1,5 @@
-"""The hand-scheduled 256-row tiles of the linear layers (csrc/linear_pipe.hip): instruction stream and routes on the CPU,
-results on the GPU against the float64 oracle."""
+"""The hand-scheduled 256-row tiles of the linear layers (csrc/linear_pipe.hip): instruction stream (of the loads in the small
+tiles' kernels too, csrc/linear.hip) and routes on the CPU, results on the GPU against the float64 oracle."""
 import os
 import subprocess
 import tempfile
@@ -25,17 +25,28 @@ def test_lds_load_check_sees_a_planted_hazard():
     assert lds_load_violations(bad.replace("\n", "\n v_add_u32 v1, s2, v3\n")) == []
 
 
-def test_instruction_stream():
-    """The rules that no interlock keeps (test_isa_hazards.py), and that nothing spills."""
-    name = "linear_pipe.hip"
+def generated(name):
     with tempfile.TemporaryDirectory() as tmp:
         out = os.path.join(tmp, name + ".s")
-        r = subprocess.run(["hipcc", *build.COMMON, *build.PER_FILE[name], "--cuda-device-only", "-S",
+        r = subprocess.run(["hipcc", *build.COMMON, *build.PER_FILE.get(name, []), "--cuda-device-only", "-S",
                             os.path.join(isa.CSRC, name), "-o", out], capture_output=True, text=True)
         assert r.returncode == 0, r.stderr[-2000:]
-        text = open(out).read()
+        return open(out).read()
+
+
+def test_instruction_stream():
+    """The rules that no interlock keeps (test_isa_hazards.py), and that nothing spills."""
+    text = generated("linear_pipe.hip")
     assert text.count("v_mfma") > 6 * 48
     assert isa.violations(text) == [] and isa.result_violations(text) == [] and lds_load_violations(text) == []
+    assert isa.scalar_violations(text) == []
+    assert text.count("offen lds") > 100 and "scratch_" not in text
+
+
+def test_loads_of_the_small_tiles():
+    """The 64 and 128 tiles' kernels are the compiler's but for the loads into LDS, which are assembly there too."""
+    text = generated("linear.hip")
+    assert lds_load_violations(text) == [] and isa.scalar_violations(text) == []
     assert text.count("offen lds") > 100 and "scratch_" not in text
 
 
