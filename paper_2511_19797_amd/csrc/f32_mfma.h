@@ -15,16 +15,19 @@ inline bool f32_mfma_reads(const Shape& s, int dtype) {  // false for a dtype wi
   return dtype == 0 && s.D % 4 == 0 && s.D <= 128 && fits(s.N, s.sn) && fits(s.M, s.qsn);
 }
 // Of those calls the plain-ALU kernels keep the ones with a handful of rows: a tile here is 16 rows whatever there is of them, and
-// a workgroup sets up and adds four waves' accumulators for it, where a plain-ALU workgroup is four rows.  The lines lie
-// between the measured sizes, heads = B * H (us, plain / here; d = head dim):
-//   forward, 1 x 1:    1 head, d 16 4.0 / 4.5;  16384 heads: d 16 28 / 44, d 64 63 / 86, d 128 120 / 293
-//            4 x 4:    2048 heads: d 16 8.9 / 9.0, d 32 11.3 / 9.3, d 64 15.5 / 13.5, d 128 29 / 33;  16384: d 64 86 / 95
-//            16 x 1:   1 head, d 128 7.6 / 8.3;  2048 heads, d 128 67 / 41
-//            1 x 16:   4096 heads, d 100 66 / 78;  2048 heads, d 128 52 / 42
-//   backward, both gradients, 1 x 1:  1 head: d 4 8.6 / 10.9, d 64 21 / 13;  16384 heads: d 16 99 / 161, d 64 298 / 429
-//            4 x 4:    1 head: d 4 9.8 / 10.8, d 16 12.4 / 10.9;  16384 heads: d 16 178 / 212, d 32 269 / 170, d 64 459 / 330,
-//                      d 128 1014 / 1820      6 x 6: here, but for d 4 on one head (the same)
-//   backward, gO alone: here at every size (1 x 1: 16384 heads, d 128 450 / 384)
+// a workgroup sets up and adds four waves' accumulators for it, where a plain-ALU workgroup is four rows.  Measured, heads = B * H
+// (us, plain / here, graphs of calls back to back; d = head dim):
+//   forward, 1 x 1:    1 head, d 16 3.5 / 3.9;  16384 heads: d 16 29 / 43, d 64 65 / 88, d 128 126 / 297
+//            4 x 4:    2048 heads: d 16 8.4 / 8.3, d 32 10.8 / 8.7, d 64 15.4 / 12.8, d 128 28 / 34;  16384: d 64 88 / 98
+//            16 x 1:   1 head, d 128 7.3 / 7.6
+//            1 x 16:   2048 heads, d 128 53 / 43
+//   backward, both gradients, 1 x 1:  1 head: d 4 8.4 / 9.0, d 64 21 / 12;  16384 heads: d 16 104 / 148, d 64 303 / 326
+//            4 x 4:    1 head: d 4 9.4 / 9.0, d 16 12.0 / 9.1;  16384 heads: d 16 181 / 167, d 32 272 / 170, d 64 469 / 332,
+//                      d 128 1023 / 1224      6 x 6: here (d 4 on one head 10.5 / 8.8)
+//   backward, gO alone: here at every size (1 x 1: 16384 heads, d 128 458 / 385)
+// The backward's lines are on the plain kernels' side of where the times meet (4 x 4: d 96 on 1024 heads 57 / 38, d 16 on 16384
+// above; 4 x 1, d 64 on 4096 heads 106 / 86): with so few rows the plain kernels' sums are the more exact ones.  Relative error of
+// dv against 64 bits, plain / here: 4 x 4, d 96 2.1e-7 / 3.3e-7; 4 x 1 0.7e-7 / 3.8e-7 (dq, dk: 5e-7 on both).
 inline bool f32_mfma_fwd(const Shape& s, int dtype) {
   if (!f32_mfma_reads(s, dtype)) return false;
   const long long heads = (long long)s.B * s.H;

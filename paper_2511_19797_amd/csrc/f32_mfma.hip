@@ -285,10 +285,11 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(Shape s, const float* _
 
 // Query side of the backward: dq, dtq of 16 queries, and Step 1's row scalars for the key side behind it.
 // The loads are put in stages, each sent off a group of products before it is used (the scheduling barriers hold the
-// compiler to that), so that few fragments live at once: 251 registers instead of 280 at DP = 128, two waves per SIMD
+// compiler to that), so that few fragments live at once: 253 registers instead of 280 at DP = 128, two waves per SIMD
 // instead of one.  With a tangent there are products enough behind the next tile's first rows to load them one tile ahead
-// (a wave without one asks for an offset out of range: reading its own tile once more cost 7 % of a backward of 64 x 64 at
-// DP = 128, and a branch around the loads spills).  DP = 32 has the registers to take the second stage's loads with the first.
+// (a wave without one asks for an offset out of range, and for the head's first bytes, unused, in lanes beyond the head dim, where
+// kOut + kOut is 0: reading its own tile once more cost 7 % of a backward of 64 x 64 at DP = 128, and a branch around the loads
+// spills).  DP = 32 has the registers to take the second stage's loads with the first.
 // Both upstream gradients, B2 H16 N256 d128: 62 us before, 48 now; B2 H8 N1024 d64: 185 before, 167 now.  Without
 // the tangent there is little to put behind a stage's loads: B4 H12 N256 d64 18.4 us with all loads first, 18.8 in stages
 // and 20.2 with the next tile's rows ahead, so there all loads come first.
@@ -456,7 +457,7 @@ __global__ __launch_bounds__(256, MODE == 1 ? (DP <= 64 ? 2 : 1) : DP <= 32 ? 4 
 // Key side: dk, dtk, dv, dtv of 16 keys, the queries streamed.
 // The loads are put in stages here too: the products of q and tq run while the rows of gO and gTO come in, and so on.  With
 // all rows of a tile loaded at once and 64-bit addresses for its row scalars the kernel took 200 registers at DP = 64, two
-// waves per SIMD: a short sequence's 768 workgroups were a full round and a half-empty one.  It takes 168 now (DP = 96: 243,
+// waves per SIMD: a short sequence's 768 workgroups were a full round and a half-empty one.  It takes 168 now (DP = 96: 241,
 // was 304), one wave more.  Both upstream gradients: B4 H12 N256 d64 75.6 us before, 51 now (its products alone: 31); B2 H8
 // N1024 d64 278 and 224; B2 H16 N256 d96 66 and 48, d128 82 and 69.  At DP = 128 two waves would spill 24
 // registers and cost 73 us.  DP = 32 loads the second stage with the first: 128 registers, four waves (backward of 16384 heads
