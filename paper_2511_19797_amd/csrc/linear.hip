@@ -56,8 +56,9 @@ __device__ __forceinline__ void store_partial(const GemmArgs& g, const f32x16 (&
 // The products for shapes with few 256-row tiles: workgroups of four waves on 64 x 64 or 128 x 128 output tiles (N), one tile
 // each.  What bounds a contraction tile of 64 is LDS: at N = 64 32 KB of fragment reads and 16 KB that land there, 384 cycles at
 // 128 bytes a cycle, next to 128 cycles of products per wave (N = 128: 96 KB, 768 and 512).  So a wave reads the fragments of
-// the next tile between the products of this one, the loads run NST - 2 tiles ahead, counted rather than drained, and their
-// descriptors move by additions: a tile takes 430 cycles (900), against 740 (1500) with reads, then products, and descriptors
+// the next tile between the products of this one, the loads run NST - 2 tiles ahead, in the loop counted rather than drained (at the
+// start the compiler, which sees the bias load and not the assembly's, waits for all first stages in front of the bias product, with
+// or without a bias; split grad W has no such wait), and their descriptors move by additions: a tile takes 430 cycles (900), against 740 (1500) with reads, then products, and descriptors
 // worked out anew for every tile.  us before / now: forward 256 x 1152 -> 1152 9.6 / 7.5, 256 x 4608 -> 1152 26.8 / 18.2, 500 x 3072
 // -> 768 19.1 / 13.6, 500 x 1152 -> 3456 (128) 17.8 / 15.0; grad x 256 x 1152 -> 4608 28.2 / 17.4; grad W 500 x 768 -> 3072 (128) 16.2 / 13.6.
 // Operand tiles as in linear_pipe.hip (Operand: whole cache lines, no padding, zeros beyond the edges).  Contraction tiles are

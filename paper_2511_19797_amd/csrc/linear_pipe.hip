@@ -18,6 +18,8 @@
 //   - tile positions by multiplication with reciprocals (five integer divisions per output tile were 3 k cycles).
 // Accumulators start from bias x 1 as one more product, exactly the bias: every shape, these and the small ones, adds an output
 // element's products in the same order.
+// (The bias load is the newest of all when an output tile ends, and the compiler waits for it, in grad x without a bias too: the
+// results' first store then stands behind every tile load in flight.  Grad W has no such wait.)
 // Measured, DiT-XL/2 at 16 x 1024 tokens, against 8 waves of 4 x 2 blocks on tiles staged as 64-byte rows, us (TFLOP/s):
 //   1152 -> 3456  forward 257 -> 225 (1160), grad x 287 -> 210 (1245), grad W 281 -> 211 (1235)
 //   1152 -> 1152          94 ->  75 (1160),        105 ->  77 (1125),        102 ->  87 (1005)

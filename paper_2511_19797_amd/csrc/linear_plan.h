@@ -85,7 +85,8 @@ inline long long dw_cost(int c, long long tiles, int steps) {
 // than dw_splits: the workspace is sized for those.
 // (us of grad W alone, 256 | 192 | 128 | 64: R 500 768 -> 768 19 | 17 | 16 | 7; R 4096 768 -> 3072 53 | 48 | 62 | 71; R 16384
 // 1152 -> 3456 252 | 220 | 292 | 503.  At 189 layers of 288 ... 4608 and R = 64 ... 16384 the choice is 5 % behind the fastest
-// shape on average: it is late to turn to 64 x 64, by up to 5 us.)
+// shape on average: it is late to turn to 64 x 64, by up to 5 us, as rounds of 256 are counted for a shape that runs two
+// workgroups per CU.)
 struct DwPlan {
   int shape, splits;
 };
